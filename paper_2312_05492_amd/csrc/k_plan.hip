@@ -214,11 +214,19 @@ __device__ void make_pass(FieldPlan& p, const PlanIn& in, uint32_t n0, uint32_t 
             // lines sit at multiples of s along dimensions this level has
             // already passed over, of 2 s along the others
             auto shift = [&](int j) { return pos[j] < k ? lvl - 1 : lvl; };
+            // at the finest level no later pass reads the far face of a
+            // dimension already passed (its lines neither hold owned points
+            // nor lie along a dimension still to come), so those lines are
+            // left out: 477 four-target tasks a 3D window instead of 562 in
+            // the order z, y, x, and a last pass of 64 whole lines
+            auto lines = [&](int j, int sh) {
+                return (uint32_t)((W[j] >> sh) + (lvl == 1 && pos[j] < k ? 0 : 1));
+            };
             const int she = shift(e);
             q.d = d;
             q.spl = in.spline[d];
             q.sh = lvl - 1;
-            q.ne = (uint32_t)((W[e] >> she) + 1);
+            q.ne = lines(e, she);
             q.le = ST[e] << she;
             q.de = e;
             q.she = she;
@@ -227,7 +235,7 @@ __device__ void make_pass(FieldPlan& p, const PlanIn& in, uint32_t n0, uint32_t 
             q.rne = (1 << she) - 1;
             if (g >= 0) {
                 const int shg = shift(g);
-                q.nlines = q.ne * (uint32_t)((W[g] >> shg) + 1);
+                q.nlines = q.ne * lines(g, shg);
                 q.lf = ST[g] << shg;
                 q.dg = g;
                 q.shg = shg;
