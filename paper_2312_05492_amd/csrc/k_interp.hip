@@ -378,9 +378,9 @@ __device__ __forceinline__ float predict(bool m3, bool p1, bool p3, float a, flo
 template <int K>
 struct Task {
     int base;       // LDS index of the segment start
-    uint32_t gl;    // its global offset from the window origin
-    uint32_t seg;
-    bool own;       // the line lies in the window's owned part
+    uint32_t gl;    // compression: its global offset from the window origin
+    uint32_t t;     // the task's number
+    bool own;       // the line lies in the window's owned part (compression)
     float kn[K + 3];
     float xt[K];
     uint32_t ct[K];
@@ -395,8 +395,31 @@ struct PassOut {
     uint32_t* hist;           // LDS histogram (compression)
 };
 
+// a * b modulo 2^32 for a < 2^16, from 24-bit multiplies (full rate; a
+// 32-bit multiply issues at a quarter of it), the halves of b uniform (the
+// empty asm keeps the compiler from joining them to the 32-bit product)
+__device__ __forceinline__ uint32_t mul16x32(uint32_t a, uint32_t b) {
+    uint32_t hi = __umul24(a, b >> 16);
+    asm("" : "+v"(hi));
+    return __umul24(a, b & 0xFFFFu) + (hi << 16);
+}
+
+// Targets per task: a lane reads K + 3 knowns for K targets, so long tasks
+// save LDS reads and task set-up where a pass has many lines (stride 1),
+// and short ones fill the wave where it has few: at the coarse strides a
+// pass has less than a wave of targets, and each task's time is its K
+// predictions one after another.  x-lines stop at 4 at stride 1 (against 8:
+// fewer live registers, 18 % faster in 2D and 7-9 % in 3D).
+template <int T, int SH, int D>
+constexpr int task_targets() {
+    constexpr int most = SH == 0 ? (D == 0 ? 4 : 8) : (SH == 1 ? 2 : 1);
+    return T < most ? T : most;
+}
+
 // One pass: dimension D, stride s = 1 << SH, spline SPL.  FULL: the window
-// interval along D is the whole block, so the stencil flags are constants.
+// interval along D is the whole block, so the stencil flags are constants
+// (in whole lines) or follow from the segment.  store: the pass's values
+// are read by a later one (compression only; the last pass's are not).
 // Tasks are software-pipelined: the LDS reads of a lane's next task are
 // issued before the current one is computed.  Within a pass no task reads a
 // point another task writes (targets never neighbour each other along D and
@@ -405,26 +428,31 @@ struct PassOut {
 // The block holds a value at every known point.  In the replay a point not
 // yet reconstructed holds its quant-code instead (as the bits of the
 // float), which the pass reading it as a target replaces by the value.
+//
+// Bound by instruction issue (about 2000 vector and 1200 scalar
+// instructions a 3D window), so the common case is kept short: one test per
+// task decides whether every target of every lane is in range and inside
+// the bound in FP32; only otherwise are outliers and the FP64 test looked
+// at target by target.
 template <int ND, int D, int SH, int SPL, bool COMP, bool FULL>
 __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDesc& pd,
                                            const Win& wi, int ed, int R, const PassOut& po,
-                                           uint32_t& cntR) {
+                                           bool store) {
     using G = Geo<ND>;
     constexpr int s = 1 << SH;
     constexpr int W = D == 0 ? G::W0 : (D == 1 ? G::W1 : G::W2);
     constexpr int SD = D == 0 ? 1 : (D == 1 ? G::SY : G::SZ);
     constexpr int T = W / (2 * s);   // targets per line
-    // targets per task: x-lines take 4 (fewer live registers: the 2D
-    // four-wave variant fits 128 VGPRs without spills; against 8, interp
-    // and replay are 18 % faster on 2D fields and 7-9 % on 3D ones)
-    constexpr int KMAX = D == 0 ? 4 : 8;
-    constexpr int K = T > KMAX ? KMAX : T;
+    constexpr int K = task_targets<T, SH, D>();
     constexpr int NSEG = T / K;
-    static_assert(NSEG == 1 || D == 0, "lines split into segments run along x only");
-    static_assert(NSEG == 1 || 2 * s <= kPad, "guard band narrower than the stencil");
+    static_assert(NSEG * K == T && (NSEG & (NSEG - 1)) == 0, "whole power-of-two segments");
+    // a split line's end segments have knowns past the line: along x at
+    // small strides the guard band or the next row absorbs the read, else
+    // it is moved onto the line (the flags drop the value either way)
+    constexpr bool kGuard = D == 0 && 2 * s <= kPad;
     const uint32_t ntask = pd.nlines * (uint32_t)NSEG;
     const uint32_t ne = pd.ne, magic = pd.magic;
-    const int le = pd.le, lf = pd.lf;
+    const uint32_t le = (uint32_t)pd.le, lf = (uint32_t)pd.lf;
     const float ebx2 = pd.ebx2, inv = pd.inv, Rf = (float)R;
     const float el = pd.el;
     const uint32_t ge = pd.ge, gf = pd.gf;
@@ -435,21 +463,46 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDe
     const int own0 = (int)((((wi.op >> pd.obe) & 255u) + (uint32_t)pd.rne) >> pd.she);
     const int own1 = ND == 2 ? 1 : (int)((((wi.op >> pd.obg) & 255u) + (uint32_t)pd.rng) >> pd.shg);
 
-    auto fetch = [&](uint32_t t, Task<K>& tk) {
-        tk.seg = NSEG > 1 ? (t & (uint32_t)(NSEG - 1)) : 0u;
-        const uint32_t ln = NSEG > 1 ? t / (uint32_t)NSEG : t;
-        const uint32_t i1 = __umulhi(ln, magic);   // ln / ne (ne >= 2, ln < 2^16)
-        const uint32_t i0 = ln - i1 * ne;
-        tk.base = (int)i0 * le + (int)i1 * lf + (int)tk.seg * (2 * K * s) * SD;
-        tk.gl = i0 * ge + i1 * gf + tk.seg * (uint32_t)(2 * K * s) * gsd;
-        if (COMP) tk.own = (int)i0 < own0 && (int)i1 < own1;
+    auto seg_of = [&](uint32_t t) SZI_INLINE { return NSEG > 1 ? (t & (uint32_t)(NSEG - 1)) : 0u; };
+    auto line_of = [&](uint32_t t, uint32_t& i0, uint32_t& i1) SZI_INLINE {
+        const uint32_t ln = t / (uint32_t)NSEG;
+        i1 = ND == 2 ? 0u : __umul24(ln, magic) >> 16;   // ln / ne
+        i0 = ND == 2 ? ln : ln - __umul24(i1, ne);
+    };
+    // global offset of the segment start from the window origin: along x
+    // (dimension e where D is not x) the spacing is small
+    auto global_of = [&](uint32_t i0, uint32_t i1, uint32_t seg) SZI_INLINE {
+        uint32_t g = seg * (uint32_t)(2 * K * s) * gsd;
+        g += D == 0 ? mul16x32(i0, ge) : __umul24(i0, ge);
+        if (ND == 3) g += mul16x32(i1, gf);
+        return g;
+    };
+
+    auto fetch = [&](uint32_t t, Task<K>& tk) SZI_INLINE {
+        uint32_t i0, i1;
+        line_of(t, i0, i1);
+        const uint32_t seg = seg_of(t);
+        tk.t = t;
+        uint32_t base = __umul24(i0, le) + seg * (uint32_t)(2 * K * s * SD);
+        if (ND == 3) base += __umul24(i1, lf);
+        tk.base = (int)base;
+        if (COMP) {
+            tk.gl = global_of(i0, i1, seg);
+            tk.own = (int)i0 < own0 && (ND == 2 || (int)i1 < own1);
+        }
         // knowns at (2i - 2) s from the segment start; whole lines read only
-        // the ones inside the block, split lines all of them (the guard band
-        // and the neighbouring line absorb the ends; the flags drop them)
+        // the ones inside the block
 #pragma unroll
         for (int i = 0; i < K + 3; ++i) {
             const int pos = (2 * i - 2) * s;
-            tk.kn[i] = (NSEG > 1 || (pos >= 0 && pos <= W)) ? v[tk.base + pos * SD] : 0.0f;
+            if (NSEG == 1) {
+                tk.kn[i] = pos >= 0 && pos <= W ? v[tk.base + pos * SD] : 0.0f;
+            } else if (kGuard || (i > 0 && i < K + 2)) {
+                tk.kn[i] = v[tk.base + pos * SD];
+            } else {
+                const bool in = i == 0 ? seg > 0u : seg < (uint32_t)(NSEG - 1);
+                tk.kn[i] = v[tk.base + (in ? pos : (i == 0 ? 0 : pos - 2 * s)) * SD];
+            }
         }
 #pragma unroll
         for (int j = 0; j < K; ++j) {
@@ -461,14 +514,15 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDe
         }
     };
 
-    auto compute = [&](const Task<K>& tk) {
-        const int p0 = (int)tk.seg * (2 * K * s);   // segment start along D
+    auto compute = [&](const Task<K>& tk) SZI_INLINE {
+        const uint32_t seg = seg_of(tk.t);
+        const int p0 = (int)seg * (2 * K * s);   // segment start along D
         float pr[K], nm[K];
 #pragma unroll
         for (int j = 0; j < K; ++j) {
             const int pos = (2 * j + 1) * s;   // target position in the segment
-            const bool m3 = NSEG > 1 ? (j >= 1 || tk.seg > 0u) : (j >= 1);
-            bool p3 = NSEG > 1 ? (j <= K - 2 || tk.seg < (uint32_t)(NSEG - 1))
+            const bool m3 = NSEG > 1 ? (j >= 1 || seg > 0u) : (j >= 1);
+            bool p3 = NSEG > 1 ? (j <= K - 2 || seg < (uint32_t)(NSEG - 1))
                                : ((2 * j + 4) * s <= W);
             bool p1 = true;
             if (!FULL) {   // the window interval ends at ed - 1
@@ -479,10 +533,11 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDe
                                  nm[j]);
         }
         if (SPL == SPL_NAT) {   // numerators below the fast division's range: rare
-            bool need = false;
+            // (a NaN passes the minimum by: either division keeps it a NaN)
+            float least = fabsf(nm[0]);
 #pragma unroll
-            for (int j = 0; j < K; ++j) need = need || !(fabsf(nm[j]) >= 0x1p-123f);
-            if (wave_any(need)) {
+            for (int j = 1; j < K; ++j) least = fminf(least, fabsf(nm[j]));
+            if (wave_any(!(least >= 0x1p-123f))) {
 #pragma unroll
                 for (int j = 0; j < K; ++j)
                     if (!(fabsf(nm[j]) >= 0x1p-123f)) pr[j] = nm[j] / 40.0f;
@@ -490,84 +545,79 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDe
         }
         float* vb = v + tk.base;
         if (COMP) {
-            float qr[K], xr[K], vv[K];
+            // closed-loop quantisation against e_l (Sec. III-A): with
+            // e_l = 0, inv = 0 gives q = 0 and xr = p + 0, so only exact
+            // predictions pass the bound test
+            float qr[K], xr[K], dm = 0.0f, qm = 0.0f;
             uint32_t cd[K];
-            bool need = false;
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                // closed-loop quantisation against e_l (Sec. III-A): with
-                // e_l = 0, inv = 0 gives q = 0 and xr = p + 0, so only exact
-                // predictions pass the bound test below
                 const float p = pr[j], xv = tk.xt[j];
                 qr[j] = rintf((xv - p) * inv);   // round half to even
                 xr[j] = p + qr[j] * ebx2;        // (float)(int)q == q in range
-                // |rint(qf)| < R holds iff |qf| < R and |q| < R; NaN fails it.
-                // The FP64 bound test |x - xr| <= e_l is decided in FP32
-                // where the rounded difference is below e_l (then so is the
-                // exact one), in FP64 otherwise (below).
-                const bool inr = fabsf(qr[j]) < Rf;
-                const bool good = inr && fabsf(xv - xr[j]) < el;
-                vv[j] = good ? xr[j] : xv;
-                cd[j] = good ? (uint32_t)((int)qr[j] + R) : 0u;
-                need = need || (good != inr);
+                // the largest |q| and |x - xr| of the task; the maximum
+                // keeps a NaN (a prediction past the largest float)
+                const bool in = FULL || p0 + (2 * j + 1) * s < ed;
+                qm = __builtin_elementwise_maximum(qm, in ? fabsf(qr[j]) : 0.0f);
+                dm = __builtin_elementwise_maximum(dm, in ? fabsf(xv - xr[j]) : 0.0f);
+                cd[j] = (uint32_t)((int)qr[j] + R);
             }
-            if (wave_any(need)) {
+            // |rint(qf)| < R holds iff |qf| < R and |q| < R; NaN fails it.
+            // The FP64 bound test |x - xr| <= e_l is decided in FP32 where
+            // the rounded difference is below e_l (then so is the exact
+            // one), in FP64 otherwise.
+            if (wave_any(!(dm < el && qm < Rf))) {
 #pragma unroll
                 for (int j = 0; j < K; ++j) {
                     const float xv = tk.xt[j];
-                    if (fabsf(qr[j]) < Rf && !(fabsf(xv - xr[j]) < el) &&
-                        fabs((double)xv - (double)xr[j]) <= (double)el) {
-                        vv[j] = xr[j];
-                        cd[j] = (uint32_t)((int)qr[j] + R);
-                    }
+                    // (no short-circuits: selects only, no nested branches)
+                    const bool inr = fabsf(qr[j]) < Rf;
+                    const bool in32 = fabsf(xv - xr[j]) < el;
+                    const bool in64 = fabs((double)xv - (double)xr[j]) <= (double)el;
+                    const bool good = inr & (in32 | in64);
+                    xr[j] = good ? xr[j] : xv;
+                    cd[j] = good ? cd[j] : 0u;
                 }
             }
+            if (store) {
 #pragma unroll
-            for (int j = 0; j < K; ++j) vb[(2 * j + 1) * s * SD] = vv[j];
-            // owned targets' quant-codes: the window interval along D ends
-            // at ed - 1
+                for (int j = 0; j < K; ++j) vb[(2 * j + 1) * s * SD] = xr[j];
+            }
+            // owned targets: the quant-codes, and the histogram, where the
+            // centre code goes to a bin of the lane's own past the 2R
+            // symbols (no two lanes share an address).  The window interval
+            // along D ends at ed - 1.
             if (tk.own) {
-                SZI_G char* cbb = (SZI_G char*)po.cb + (uint64_t)(2u * tk.gl);
+                const uint32_t rb = (uint32_t)(2 * R) + lane;
 #pragma unroll
                 for (int j = 0; j < K; ++j) {
                     const int pos = (2 * j + 1) * s;
                     if (FULL || p0 + pos < ed) {
-                        if (D == 0) *(SZI_G uint16_t*)(cbb + 2 * pos) = (uint16_t)cd[j];
-                        else *(SZI_G uint16_t*)(cbb + (uint64_t)(2u * (uint32_t)pos * gsd)) = (uint16_t)cd[j];
+                        // a uniform base per target and the lane's 32-bit offset
+                        SZI_G uint16_t* cj = po.cb + (uint64_t)((uint32_t)pos * gsd);
+                        *at(cj, tk.gl) = (uint16_t)cd[j];
+                        atomicAdd(&po.hist[cd[j] != (uint32_t)R ? cd[j] : rb], 1u);
                     }
                 }
             }
-            // histogram without branches: every target adds one; the centre
-            // code and targets the window does not own go to a bin of the
-            // lane's own past the 2R symbols (no two lanes share an
-            // address), and the count of the latter is taken off the centre
-            // bin when the histogram is flushed
-            const uint32_t rb = (uint32_t)(2 * R) + lane;
-            if (FULL) cntR += (uint32_t)(K * __popcll(wave_ballot(!tk.own)));
-#pragma unroll
-            for (int j = 0; j < K; ++j) {
-                const int pos = (2 * j + 1) * s;
-                const bool ot = tk.own && (FULL || p0 + pos < ed);
-                if (!FULL) cntR += (uint32_t)__popcll(wave_ballot(!ot));
-                const uint32_t bin = ot && cd[j] != (uint32_t)R ? cd[j] : rb;
-                atomicAdd(&po.hist[bin], 1u);
-            }
         } else {
-            bool out = false;
+            uint32_t least = tk.ct[0];
 #pragma unroll
             for (int j = 0; j < K; ++j) {
-                const uint32_t code = tk.ct[j];
-                pr[j] = pr[j] + (float)((int)code - R) * ebx2;
-                out = out || code == 0u;
+                pr[j] = pr[j] + (float)((int)tk.ct[j] - R) * ebx2;
+                least = tk.ct[j] < least ? tk.ct[j] : least;
             }
             // code 0: an outlier, whose value the scatter step put in the
             // output array (points outside the field hold a code no point
             // takes, so the load stays inside it); rare, so one uniform test
-            if (wave_any(out)) {
+            if (wave_any(least == 0u)) {
+                uint32_t i0, i1;
+                line_of(tk.t, i0, i1);
+                const uint32_t gl = global_of(i0, i1, seg);
 #pragma unroll
                 for (int j = 0; j < K; ++j) {
                     const int pos = (2 * j + 1) * s;
-                    if (tk.ct[j] == 0u) pr[j] = *at(po.ob, tk.gl + (uint32_t)pos * gsd);
+                    if (tk.ct[j] == 0u) pr[j] = *at(po.ob, gl + (uint32_t)pos * gsd);
                 }
             }
 #pragma unroll
@@ -597,25 +647,25 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDe
 
 template <int ND, int D, int SH, bool COMP>
 __device__ __forceinline__ void run_pass(float* v, uint32_t lane, const PassDesc& pd, const Win& wi,
-                                         int R, const PassOut& po, uint32_t& cntR) {
+                                         int R, const PassOut& po, bool store) {
     using G = Geo<ND>;
     constexpr int W = D == 0 ? G::W0 : (D == 1 ? G::W1 : G::W2);
     const int ed = D == 0 ? wi.e0 : (D == 1 ? wi.e1 : wi.e2);
     // the stencil flags depend on the extent along D only
     if (ed == W + 1) {
         if (pd.spl == SPL_LIN)
-            pass_lines<ND, D, SH, SPL_LIN, COMP, true>(v, lane, pd, wi, ed, R, po, cntR);
+            pass_lines<ND, D, SH, SPL_LIN, COMP, true>(v, lane, pd, wi, ed, R, po, store);
         else if (pd.spl == SPL_NAT)
-            pass_lines<ND, D, SH, SPL_NAT, COMP, true>(v, lane, pd, wi, ed, R, po, cntR);
+            pass_lines<ND, D, SH, SPL_NAT, COMP, true>(v, lane, pd, wi, ed, R, po, store);
         else
-            pass_lines<ND, D, SH, SPL_NAK, COMP, true>(v, lane, pd, wi, ed, R, po, cntR);
+            pass_lines<ND, D, SH, SPL_NAK, COMP, true>(v, lane, pd, wi, ed, R, po, store);
     } else {
         if (pd.spl == SPL_LIN)
-            pass_lines<ND, D, SH, SPL_LIN, COMP, false>(v, lane, pd, wi, ed, R, po, cntR);
+            pass_lines<ND, D, SH, SPL_LIN, COMP, false>(v, lane, pd, wi, ed, R, po, store);
         else if (pd.spl == SPL_NAT)
-            pass_lines<ND, D, SH, SPL_NAT, COMP, false>(v, lane, pd, wi, ed, R, po, cntR);
+            pass_lines<ND, D, SH, SPL_NAT, COMP, false>(v, lane, pd, wi, ed, R, po, store);
         else
-            pass_lines<ND, D, SH, SPL_NAK, COMP, false>(v, lane, pd, wi, ed, R, po, cntR);
+            pass_lines<ND, D, SH, SPL_NAK, COMP, false>(v, lane, pd, wi, ed, R, po, store);
     }
 }
 
@@ -630,25 +680,26 @@ __device__ __forceinline__ void wave_sync() {
 // The passes of one level (stride 1 << SH), in the planned order.
 template <int ND, int SH, bool COMP>
 __device__ __forceinline__ void run_level(float* v, uint32_t lane, const FieldPlan& pl, int R,
-                                          const Win& wi, const PassOut& po, uint32_t& cntR) {
+                                          const Win& wi, const PassOut& po) {
     constexpr int L = ND == 3 ? 3 : 4;
 #pragma unroll 1
     for (int k = 0; k < ND; ++k) {
         const PassDesc pd = pl.pass[(L - 1 - SH) * ND + k];
-        if (pd.d == 0) run_pass<ND, 0, SH, COMP>(v, lane, pd, wi, R, po, cntR);
-        else if (ND == 2 || pd.d == 1) run_pass<ND, 1, SH, COMP>(v, lane, pd, wi, R, po, cntR);
-        else if constexpr (ND == 3) run_pass<ND, 2, SH, COMP>(v, lane, pd, wi, R, po, cntR);
+        const bool store = SH > 0 || k + 1 < ND;   // the last pass's values are read by none
+        if (pd.d == 0) run_pass<ND, 0, SH, COMP>(v, lane, pd, wi, R, po, store);
+        else if (ND == 2 || pd.d == 1) run_pass<ND, 1, SH, COMP>(v, lane, pd, wi, R, po, store);
+        else if constexpr (ND == 3) run_pass<ND, 2, SH, COMP>(v, lane, pd, wi, R, po, store);
         wave_sync();
     }
 }
 
 template <int ND, bool COMP>
 __device__ __forceinline__ void run_levels(float* v, uint32_t lane, const FieldPlan& pl, int R,
-                                           const Win& wi, const PassOut& po, uint32_t& cntR) {
-    if constexpr (ND == 2) run_level<ND, 3, COMP>(v, lane, pl, R, wi, po, cntR);
-    run_level<ND, 2, COMP>(v, lane, pl, R, wi, po, cntR);
-    run_level<ND, 1, COMP>(v, lane, pl, R, wi, po, cntR);
-    run_level<ND, 0, COMP>(v, lane, pl, R, wi, po, cntR);
+                                           const Win& wi, const PassOut& po) {
+    if constexpr (ND == 2) run_level<ND, 3, COMP>(v, lane, pl, R, wi, po);
+    run_level<ND, 2, COMP>(v, lane, pl, R, wi, po);
+    run_level<ND, 1, COMP>(v, lane, pl, R, wi, po);
+    run_level<ND, 0, COMP>(v, lane, pl, R, wi, po);
 }
 
 // ---------------------------------------------------------------- write-out
@@ -879,7 +930,7 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
             wave_sync();
             const FieldDesc& fd = F[fc];
             const PassOut po{gp(fd.codes) + wc.gbase, nullptr, hist};
-            run_levels<ND, true>(v, lane, P[fc], fd.R, wc, po, cntR);
+            run_levels<ND, true>(v, lane, P[fc], fd.R, wc, po);
             write_anchors<ND>(v, lane, fd, wc, hist);
             wave_sync();
         }
@@ -950,7 +1001,7 @@ SZI_WINDOW_KERNEL void k_decompress(const FieldDesc* __restrict__ F,
             wave_sync();
             const FieldDesc& fd = F[fc];
             const PassOut po{nullptr, gp((const float*)fd.out) + wc.gbase, nullptr};
-            run_levels<ND, false>(v, lane, P[fc], fd.R, wc, po, unused);
+            run_levels<ND, false>(v, lane, P[fc], fd.R, wc, po);
             if (wc.full) write_values<ND, true>(v, lane, fd, wc);
             else write_values<ND, false>(v, lane, fd, wc);
             wave_sync();

@@ -249,7 +249,7 @@ __device__ void make_pass(FieldPlan& p, const PlanIn& in, uint32_t n0, uint32_t 
                 q.shg = 0;
                 q.gf = 0;
             }
-            q.magic = kMagic.v[q.ne];
+            q.magic = (kMagic.v[q.ne] + 0xFFFFu) >> 16;   // ceil(2^16 / ne)
             q.el = in.el[lvl - 1];
             q.ebx2 = in.ebx2[lvl - 1];
             q.inv = q.el == 0.0f ? 0.0f : in.inv[lvl - 1];

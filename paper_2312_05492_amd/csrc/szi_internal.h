@@ -69,7 +69,7 @@ constexpr int kMaxPasses = 12;
 struct PassDesc {
     int32_t d, spl, sh;        // dimension, spline, log2 of the stride
     uint32_t nlines, ne;
-    uint32_t magic;            // multiply-high constant for division by ne
+    uint32_t magic;            // ceil(2^16 / ne): line / ne = line * magic >> 16 (lines < 300)
     int32_t le, lf;
     float el, ebx2, inv;       // level bound, 2 e_l, 1 / (2 e_l) (0 when e_l = 0)
     int32_t de, dg;            // the other dimensions (dg = de in 2D)

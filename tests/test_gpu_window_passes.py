@@ -1,0 +1,62 @@
+"""The window passes at the edges of their tasks, against the CPU oracle: every pass order (which lines of the far
+faces a finest-level pass leaves out follows from it), fields that end on, one short of and one past a window, and
+values that send a task down its rare branches (outliers, the FP64 bound test, predictions past the largest float)."""
+import itertools
+
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_2312_05492_amd as szi
+from paper_2312_05492_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    O.build(force=False)
+    c = szi.Context(0)
+    yield c
+    c.close()
+
+
+def check(ctx, x, **kw):
+    import torch
+    print("\n[passes] %s %s" % (x.shape, kw), flush=True)
+    ref = O.compress(x, O.Params(shape=x.shape, **kw))
+    res = ctx.compress(torch.from_numpy(np.ascontiguousarray(x)).cuda(), **kw)
+    try:
+        assert np.array_equal(res.read(szi.SEC_CODES), ref.codes.ravel())
+        assert res.blob() == ref.blob()
+        y = ctx.decompress(res).cpu().numpy()
+        assert np.array_equal(y.view(np.uint32), ref.recon.view(np.uint32))
+    finally:
+        res.free()
+
+
+@pytest.mark.parametrize("order", list(itertools.permutations(range(3))))
+@pytest.mark.parametrize("shape", [(16, 16, 64), (17, 9, 65), (18, 15, 63)])
+def test_orders_3d(ctx, order, shape):
+    check(ctx, synth.spectral_field(shape, seed=101), order=order, interp=(2, 1, 2), eb=1e-4)
+
+
+@pytest.mark.parametrize("order", [(0, 1), (1, 0)])
+@pytest.mark.parametrize("shape", [(32, 128), (33, 129), (31, 130)])
+def test_orders_2d(ctx, order, shape):
+    check(ctx, synth.spectral_field(shape, seed=102), order=order, interp=(1, 2), eb=1e-4)
+
+
+@pytest.mark.parametrize("shape", [(20, 30, 70), (50, 140)])
+def test_rare_branches(ctx, shape):
+    rng = np.random.default_rng(103)
+    x = synth.spectral_field(shape, seed=103)
+    # spikes: scattered outliers; a bound of a few ulps of the offset field: differences that round to the bound
+    check(ctx, np.where(rng.random(shape) < 0.01, x + np.float32(1e3), x).astype(np.float32), eb=1e-3, eb_mode=0)
+    check(ctx, x + np.float32(1000.0), eb=2.0 ** -12, eb_mode=0, interp=(2,) * len(shape))
+    # predictions that overflow
+    big = np.where(rng.random(shape) < 0.5, np.float32(3e38), np.float32(-3e38)).astype(np.float32)
+    check(ctx, big, eb=1e30, eb_mode=0, interp=(2,) * len(shape))
