@@ -697,6 +697,9 @@ void fill_desc(const Geometry& g, const sz_params* p, FieldDesc& f) {
         f.interp[k] = k < g.ndim ? p->interp[k] : 0;
         f.order_req[k] = (p->order[0] >= 0 && k < g.ndim) ? p->order[k] : -1;
     }
+    const uint64_t m0 = (uint64_t)g.nwin[0], m01 = m0 * (uint64_t)g.nwin[1];
+    f.wmag[0] = m0 > 1 ? (uint32_t)((1ull << 32) / m0) : UINT32_MAX;
+    f.wmag[1] = m01 > 1 ? (uint32_t)((1ull << 32) / m01) : UINT32_MAX;
     f.S = g.S;
     f.L = g.L;
     f.R = g.R;

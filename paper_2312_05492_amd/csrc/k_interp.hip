@@ -52,10 +52,18 @@ __device__ __forceinline__ Win make_win(const FieldDesc& f, uint32_t w) {
     Win wi;
     const uint32_t nw0 = (uint32_t)f.nwin[0];
     const uint32_t nw01 = nw0 * (uint32_t)f.nwin[1];
-    const uint32_t wz = w / nw01;
-    const uint32_t r = w - wz * nw01;
-    const uint32_t wy = r / nw0;
-    const uint32_t wx = r - wy * nw0;
+    // w / nw01 and r / nw0: the product with floor(2^32 / m) is the
+    // quotient or one less
+    uint32_t wz = __umulhi(w, f.wmag[1]), r = w - wz * nw01;
+    if (r >= nw01) {
+        ++wz;
+        r -= nw01;
+    }
+    uint32_t wy = __umulhi(r, f.wmag[0]), wx = r - wy * nw0;
+    if (wx >= nw0) {
+        ++wy;
+        wx -= nw0;
+    }
     wi.n0 = (uint32_t)f.n[0];
     wi.n01 = wi.n0 * (uint32_t)f.n[1];
     wi.lo0 = (int)wx * G::W0;
@@ -372,6 +380,33 @@ __device__ __forceinline__ float predict(bool m3, bool p1, bool p3, float a, flo
     return p1 ? p : b;
 }
 
+// Makes the compiler wait here for loads into these registers, so that it
+// places no wait for them further on (where it would also hold for every
+// store and load issued since).
+template <class T, int N>
+__device__ __forceinline__ void settle(T (&r)[N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) asm volatile("" : "+v"(r[k]));
+}
+
+// A pass's descriptor in scalar registers, from the wave's register that
+// holds the passes of its field a word a lane (a scalar load per pass would
+// cost its latency nine times a window).
+struct Pass {
+    uint32_t kind, lines, magic;
+    float el, ebx2, inv;
+};
+__device__ __forceinline__ Pass get_pass(uint32_t words, int np) {
+    const int l = np * kPassWords;
+    auto rd = [&](int i) SZI_INLINE { return (uint32_t)__builtin_amdgcn_readlane((int)words, l + i); };
+    return Pass{rd(0), rd(1), rd(2), __uint_as_float(rd(3)), __uint_as_float(rd(4)), __uint_as_float(rd(5))};
+}
+__device__ __forceinline__ uint32_t load_passes(const FieldPlan& p, uint32_t lane) {
+    uint32_t w[1] = {gp(reinterpret_cast<const uint32_t*>(p.pass))[lane]};
+    settle(w);
+    return w[0];
+}
+
 // LDS values of one task: K targets of one line (segment seg, starting at
 // LDS index base), the K + 3 knowns around them and the targets' original
 // values (compression) or quant-codes (decompression).
@@ -408,11 +443,13 @@ __device__ __forceinline__ uint32_t mul16x32(uint32_t a, uint32_t b) {
 // save LDS reads and task set-up where a pass has many lines (stride 1),
 // and short ones fill the wave where it has few: at the coarse strides a
 // pass has less than a wave of targets, and each task's time is its K
-// predictions one after another.  x-lines stop at 4 at stride 1 (against 8:
-// fewer live registers, 18 % faster in 2D and 7-9 % in 3D).
-template <int T, int SH, int D>
+// predictions one after another.  At stride 1 four; in 2D compression two
+// (24 climate fields: interpolation 349 us against 391-402 with four and 413
+// with eight along y; the replay 301 with four against 317 and 357; in 3D
+// two take 337 and 268 us at 512^3 against 330 and 246).
+template <int ND, bool COMP, int T, int SH>
 constexpr int task_targets() {
-    constexpr int most = SH == 0 ? (D == 0 ? 4 : 8) : (SH == 1 ? 2 : 1);
+    constexpr int most = SH == 0 ? (ND == 2 && COMP ? 2 : 4) : (SH == 1 ? 2 : 1);
     return T < most ? T : most;
 }
 
@@ -435,7 +472,7 @@ constexpr int task_targets() {
 // the bound in FP32; only otherwise are outliers and the FP64 test looked
 // at target by target.
 template <int ND, int D, int SH, int SPL, bool COMP, bool FULL>
-__device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDesc& pd,
+__device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const Pass& pd,
                                            const Win& wi, int ed, int R, const PassOut& po,
                                            bool store) {
     using G = Geo<ND>;
@@ -443,52 +480,52 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDe
     constexpr int W = D == 0 ? G::W0 : (D == 1 ? G::W1 : G::W2);
     constexpr int SD = D == 0 ? 1 : (D == 1 ? G::SY : G::SZ);
     constexpr int T = W / (2 * s);   // targets per line
-    constexpr int K = task_targets<T, SH, D>();
+    constexpr int K = task_targets<ND, COMP, T, SH>();
     constexpr int NSEG = T / K;
     static_assert(NSEG * K == T && (NSEG & (NSEG - 1)) == 0, "whole power-of-two segments");
     // a split line's end segments have knowns past the line: along x at
     // small strides the guard band or the next row absorbs the read, else
     // it is moved onto the line (the flags drop the value either way)
     constexpr bool kGuard = D == 0 && 2 * s <= kPad;
-    const uint32_t ntask = pd.nlines * (uint32_t)NSEG;
-    const uint32_t ne = pd.ne, magic = pd.magic;
-    const uint32_t le = (uint32_t)pd.le, lf = (uint32_t)pd.lf;
+    // the dimensions of the lines, e < g: LDS strides, global strides,
+    // owned extents
+    constexpr int DE = D == 0 ? 1 : 0, DG = D == 2 ? 1 : 2;
+    constexpr uint32_t SE = DE == 0 ? 1 : G::SY, SG = DG == 1 ? G::SY : G::SZ;
+    const uint32_t gse = DE == 0 ? 1u : wi.n0, gsg = DG == 1 ? wi.n0 : wi.n01;
+    const uint32_t owne = (uint32_t)wi.own(DE), owng = (uint32_t)wi.own(DG);
+    const uint32_t ne = pd.lines >> 16, magic = pd.magic;
+    const uint32_t she = (pd.kind >> 4) & 15u, shg = (pd.kind >> 8) & 15u;
+    const uint32_t ntask = (pd.lines & 0xFFFFu) * (uint32_t)NSEG;
     const float ebx2 = pd.ebx2, inv = pd.inv, Rf = (float)R;
     const float el = pd.el;
-    const uint32_t ge = pd.ge, gf = pd.gf;
     const uint32_t gsd = D == 0 ? 1u : (D == 1 ? wi.n0 : wi.n01);   // global stride along D
-    // owned lines: i0 << she below the owned extent along de, i1 << shg
-    // below the one along dg (the extents come out of the packed word by
-    // the descriptor's bit offsets: four scalar operations a count)
-    const int own0 = (int)((((wi.op >> pd.obe) & 255u) + (uint32_t)pd.rne) >> pd.she);
-    const int own1 = ND == 2 ? 1 : (int)((((wi.op >> pd.obg) & 255u) + (uint32_t)pd.rng) >> pd.shg);
 
     auto seg_of = [&](uint32_t t) SZI_INLINE { return NSEG > 1 ? (t & (uint32_t)(NSEG - 1)) : 0u; };
-    auto line_of = [&](uint32_t t, uint32_t& i0, uint32_t& i1) SZI_INLINE {
+    // coordinates of a task's line along e and g
+    auto line_of = [&](uint32_t t, uint32_t& ce, uint32_t& cg) SZI_INLINE {
         const uint32_t ln = t / (uint32_t)NSEG;
-        i1 = ND == 2 ? 0u : __umul24(ln, magic) >> 16;   // ln / ne
-        i0 = ND == 2 ? ln : ln - __umul24(i1, ne);
+        const uint32_t i1 = ND == 2 ? 0u : __umul24(ln, magic) >> 16;   // ln / ne
+        ce = (ND == 2 ? ln : ln - __umul24(i1, ne)) << she;
+        cg = i1 << shg;
     };
-    // global offset of the segment start from the window origin: along x
-    // (dimension e where D is not x) the spacing is small
-    auto global_of = [&](uint32_t i0, uint32_t i1, uint32_t seg) SZI_INLINE {
-        uint32_t g = seg * (uint32_t)(2 * K * s) * gsd;
-        g += D == 0 ? mul16x32(i0, ge) : __umul24(i0, ge);
-        if (ND == 3) g += mul16x32(i1, gf);
+    // global offset of the segment start from the window origin
+    auto global_of = [&](uint32_t ce, uint32_t cg, uint32_t seg) SZI_INLINE {
+        uint32_t g = seg * (uint32_t)(2 * K * s) * gsd + (DE == 0 ? ce : mul16x32(ce, gse));
+        if (ND == 3) g += mul16x32(cg, gsg);
         return g;
     };
 
     auto fetch = [&](uint32_t t, Task<K>& tk) SZI_INLINE {
-        uint32_t i0, i1;
-        line_of(t, i0, i1);
+        uint32_t ce, cg;
+        line_of(t, ce, cg);
         const uint32_t seg = seg_of(t);
         tk.t = t;
-        uint32_t base = __umul24(i0, le) + seg * (uint32_t)(2 * K * s * SD);
-        if (ND == 3) base += __umul24(i1, lf);
+        uint32_t base = (SE == 1 ? ce : __umul24(ce, SE)) + __umul24(seg, (uint32_t)(2 * K * s * SD));
+        if (ND == 3) base += __umul24(cg, SG);
         tk.base = (int)base;
         if (COMP) {
-            tk.gl = global_of(i0, i1, seg);
-            tk.own = (int)i0 < own0 && (ND == 2 || (int)i1 < own1);
+            tk.gl = global_of(ce, cg, seg);
+            tk.own = ce < owne && (ND == 2 || cg < owng);
         }
         // knowns at (2i - 2) s from the segment start; whole lines read only
         // the ones inside the block
@@ -611,14 +648,19 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDe
             // output array (points outside the field hold a code no point
             // takes, so the load stays inside it); rare, so one uniform test
             if (wave_any(least == 0u)) {
-                uint32_t i0, i1;
-                line_of(tk.t, i0, i1);
-                const uint32_t gl = global_of(i0, i1, seg);
+                uint32_t ce, cg;
+                line_of(tk.t, ce, cg);
+                const uint32_t gl = global_of(ce, cg, seg);
 #pragma unroll
                 for (int j = 0; j < K; ++j) {
                     const int pos = (2 * j + 1) * s;
                     if (tk.ct[j] == 0u) pr[j] = *at(po.ob, gl + (uint32_t)pos * gsd);
                 }
+                // the values are waited for in here: a wait behind the
+                // branch would hold every task for the next window's loads
+                // (replay 254 -> 246 us at 512^3 with it here and
+                // below, the passes in a register and the shorter index sums)
+                settle(pr);
             }
 #pragma unroll
             for (int j = 0; j < K; ++j) vb[(2 * j + 1) * s * SD] = pr[j];
@@ -646,23 +688,24 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const PassDe
 }
 
 template <int ND, int D, int SH, bool COMP>
-__device__ __forceinline__ void run_pass(float* v, uint32_t lane, const PassDesc& pd, const Win& wi,
+__device__ __forceinline__ void run_pass(float* v, uint32_t lane, const Pass& pd, const Win& wi,
                                          int R, const PassOut& po, bool store) {
     using G = Geo<ND>;
     constexpr int W = D == 0 ? G::W0 : (D == 1 ? G::W1 : G::W2);
     const int ed = D == 0 ? wi.e0 : (D == 1 ? wi.e1 : wi.e2);
+    const uint32_t spl = (pd.kind >> 2) & 3u;
     // the stencil flags depend on the extent along D only
     if (ed == W + 1) {
-        if (pd.spl == SPL_LIN)
+        if (spl == SPL_LIN)
             pass_lines<ND, D, SH, SPL_LIN, COMP, true>(v, lane, pd, wi, ed, R, po, store);
-        else if (pd.spl == SPL_NAT)
+        else if (spl == SPL_NAT)
             pass_lines<ND, D, SH, SPL_NAT, COMP, true>(v, lane, pd, wi, ed, R, po, store);
         else
             pass_lines<ND, D, SH, SPL_NAK, COMP, true>(v, lane, pd, wi, ed, R, po, store);
     } else {
-        if (pd.spl == SPL_LIN)
+        if (spl == SPL_LIN)
             pass_lines<ND, D, SH, SPL_LIN, COMP, false>(v, lane, pd, wi, ed, R, po, store);
-        else if (pd.spl == SPL_NAT)
+        else if (spl == SPL_NAT)
             pass_lines<ND, D, SH, SPL_NAT, COMP, false>(v, lane, pd, wi, ed, R, po, store);
         else
             pass_lines<ND, D, SH, SPL_NAK, COMP, false>(v, lane, pd, wi, ed, R, po, store);
@@ -679,27 +722,28 @@ __device__ __forceinline__ void wave_sync() {
 
 // The passes of one level (stride 1 << SH), in the planned order.
 template <int ND, int SH, bool COMP>
-__device__ __forceinline__ void run_level(float* v, uint32_t lane, const FieldPlan& pl, int R,
+__device__ __forceinline__ void run_level(float* v, uint32_t lane, uint32_t passes, int R,
                                           const Win& wi, const PassOut& po) {
     constexpr int L = ND == 3 ? 3 : 4;
 #pragma unroll 1
     for (int k = 0; k < ND; ++k) {
-        const PassDesc pd = pl.pass[(L - 1 - SH) * ND + k];
+        const Pass pd = get_pass(passes, (L - 1 - SH) * ND + k);
         const bool store = SH > 0 || k + 1 < ND;   // the last pass's values are read by none
-        if (pd.d == 0) run_pass<ND, 0, SH, COMP>(v, lane, pd, wi, R, po, store);
-        else if (ND == 2 || pd.d == 1) run_pass<ND, 1, SH, COMP>(v, lane, pd, wi, R, po, store);
+        const uint32_t d = pd.kind & 3u;
+        if (d == 0) run_pass<ND, 0, SH, COMP>(v, lane, pd, wi, R, po, store);
+        else if (ND == 2 || d == 1) run_pass<ND, 1, SH, COMP>(v, lane, pd, wi, R, po, store);
         else if constexpr (ND == 3) run_pass<ND, 2, SH, COMP>(v, lane, pd, wi, R, po, store);
         wave_sync();
     }
 }
 
 template <int ND, bool COMP>
-__device__ __forceinline__ void run_levels(float* v, uint32_t lane, const FieldPlan& pl, int R,
+__device__ __forceinline__ void run_levels(float* v, uint32_t lane, uint32_t passes, int R,
                                            const Win& wi, const PassOut& po) {
-    if constexpr (ND == 2) run_level<ND, 3, COMP>(v, lane, pl, R, wi, po);
-    run_level<ND, 2, COMP>(v, lane, pl, R, wi, po);
-    run_level<ND, 1, COMP>(v, lane, pl, R, wi, po);
-    run_level<ND, 0, COMP>(v, lane, pl, R, wi, po);
+    if constexpr (ND == 2) run_level<ND, 3, COMP>(v, lane, passes, R, wi, po);
+    run_level<ND, 2, COMP>(v, lane, passes, R, wi, po);
+    run_level<ND, 1, COMP>(v, lane, passes, R, wi, po);
+    run_level<ND, 0, COMP>(v, lane, passes, R, wi, po);
 }
 
 // ---------------------------------------------------------------- write-out
@@ -785,12 +829,14 @@ __device__ __forceinline__ void write_values(const float* v, uint32_t lane, cons
 struct GroupSeq {
     uint64_t lo, end;   // the L2 domain's groups
     uint32_t S, j, k;   // workgroups in the domain, this one's index, round
-    uint64_t g;         // the round's group (increasing; past end: done)
-    __device__ __forceinline__ void set() { g = lo + (uint64_t)k * S + (j + k) % S; }
+    uint32_t rot;       // (j + k) mod S
+    uint64_t g;         // the round's group, lo + k S + rot (increasing; past end: done)
     __device__ __forceinline__ bool ok() const { return g < end; }
     __device__ __forceinline__ void next() {
         ++k;
-        set();
+        const bool wrap = rot + 1u == S;
+        rot = wrap ? 0u : rot + 1u;
+        g += wrap ? 1u : S + 1u;   // S further, and the rotation's step
     }
     // the window slot of a wave in the round's group
     __device__ __forceinline__ uint32_t slot(int wave) const {
@@ -830,7 +876,8 @@ __device__ __forceinline__ GroupSeq group_seq(uint64_t ngroups) {
         s.j = b;
     }
     s.k = 0;
-    s.set();
+    s.rot = s.j;   // j < S
+    s.g = s.lo + s.j;
     return s;
 }
 
@@ -906,7 +953,7 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
     };
     fetch();
     int hf = -1;         // field whose histogram the workgroup accumulates
-    uint32_t cntR = 0;   // targets counted in the lane bins that the windows do not own
+    uint32_t cntR = 0, passes = 0;
     while (true) {
         const int fc = f;
         const Win wc = wn;
@@ -916,6 +963,7 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
             clear_hist(hist, F[fc].R);
             __syncthreads();
             hf = fc;
+            passes = load_passes(P[fc], lane);
         }
         if (vc) {
             if (qc) commit_quads<ND>(v, pre, qm, lane, wc.n01);
@@ -930,7 +978,7 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
             wave_sync();
             const FieldDesc& fd = F[fc];
             const PassOut po{gp(fd.codes) + wc.gbase, nullptr, hist};
-            run_levels<ND, true>(v, lane, P[fc], fd.R, wc, po);
+            run_levels<ND, true>(v, lane, passes, fd.R, wc, po);
             write_anchors<ND>(v, lane, fd, wc, hist);
             wave_sync();
         }
@@ -975,11 +1023,16 @@ SZI_WINDOW_KERNEL void k_decompress(const FieldDesc* __restrict__ F,
         }
     };
     fetch();
-    uint32_t unused = 0;
+    int pf = -1;   // the field that passes belongs to
+    uint32_t passes = 0;
     while (true) {
         const int fc = f;
         const Win wc = wn;
         const bool vc = valid;
+        if (fc != pf) {
+            passes = load_passes(P[fc], lane);
+            pf = fc;
+        }
         if (vc) {
             // every point of the block takes its code (as float bits), those
             // outside the field the value kNone; the anchors then their values
@@ -1001,7 +1054,11 @@ SZI_WINDOW_KERNEL void k_decompress(const FieldDesc* __restrict__ F,
             wave_sync();
             const FieldDesc& fd = F[fc];
             const PassOut po{nullptr, gp((const float*)fd.out) + wc.gbase, nullptr};
-            run_levels<ND, false>(v, lane, P[fc], fd.R, wc, po);
+            run_levels<ND, false>(v, lane, passes, fd.R, wc, po);
+            // the next block's codes are here by now: waited for ahead of
+            // the stores of this window's values, not behind them
+            settle(pre);
+            asm volatile("" : "+v"(apre));
             if (wc.full) write_values<ND, true>(v, lane, fd, wc);
             else write_values<ND, false>(v, lane, fd, wc);
             wave_sync();

@@ -187,7 +187,7 @@ struct PlanIn {
 // the descriptors past the last pass are cleared.  Passes are independent:
 // one thread each, or a loop.
 template <int ND>
-__device__ void make_pass(FieldPlan& p, const PlanIn& in, uint32_t n0, uint32_t n01, int np) {
+__device__ void make_pass(FieldPlan& p, const PlanIn& in, int np) {
     using G = Geo<ND>;
     constexpr int L = G::SHS;
     if (np >= L * ND) {
@@ -195,73 +195,43 @@ __device__ void make_pass(FieldPlan& p, const PlanIn& in, uint32_t n0, uint32_t 
         return;
     }
     const int W[3] = {G::W0, G::W1, G::W2};
-    const int ST[3] = {1, G::SY, G::SZ};
-    const uint32_t GS[3] = {1u, n0, n01};
     int pos[3] = {0, 0, 0};   // place of each dimension in the order
 #pragma unroll
     for (int k = 0; k < ND; ++k)
 #pragma unroll
         for (int j = 0; j < ND; ++j)
             if (in.order[k] == j) pos[j] = k;
-    {
-        const int lvl = L - np / ND, k = np % ND;
-        {
-            PassDesc q{};
-            const int d = in.order[k];
-            // the other dimensions, ascending
-            const int e = d == 0 ? 1 : 0;
-            const int g = ND == 2 ? -1 : (d == 2 ? 1 : 2);
-            // lines sit at multiples of s along dimensions this level has
-            // already passed over, of 2 s along the others
-            auto shift = [&](int j) { return pos[j] < k ? lvl - 1 : lvl; };
-            // at the finest level no later pass reads the far face of a
-            // dimension already passed (its lines neither hold owned points
-            // nor lie along a dimension still to come), so those lines are
-            // left out: 477 four-target tasks a 3D window instead of 562 in
-            // the order z, y, x, and a last pass of 64 whole lines
-            auto lines = [&](int j, int sh) {
-                return (uint32_t)((W[j] >> sh) + (lvl == 1 && pos[j] < k ? 0 : 1));
-            };
-            const int she = shift(e);
-            q.d = d;
-            q.spl = in.spline[d];
-            q.sh = lvl - 1;
-            q.ne = lines(e, she);
-            q.le = ST[e] << she;
-            q.de = e;
-            q.she = she;
-            q.ge = GS[e] << she;
-            q.obe = 8u * (uint32_t)e;
-            q.rne = (1 << she) - 1;
-            if (g >= 0) {
-                const int shg = shift(g);
-                q.nlines = q.ne * lines(g, shg);
-                q.lf = ST[g] << shg;
-                q.dg = g;
-                q.shg = shg;
-                q.gf = GS[g] << shg;
-                q.obg = 8u * (uint32_t)g;
-                q.rng = (1 << shg) - 1;
-            } else {
-                q.nlines = q.ne;
-                q.lf = 0;
-                q.dg = e;
-                q.shg = 0;
-                q.gf = 0;
-            }
-            q.magic = (kMagic.v[q.ne] + 0xFFFFu) >> 16;   // ceil(2^16 / ne)
-            q.el = in.el[lvl - 1];
-            q.ebx2 = in.ebx2[lvl - 1];
-            q.inv = q.el == 0.0f ? 0.0f : in.inv[lvl - 1];
-            p.pass[np] = q;
-        }
-    }
+    const int lvl = L - np / ND, k = np % ND;
+    const int d = in.order[k];
+    // the other dimensions, ascending
+    const int e = d == 0 ? 1 : 0;
+    const int g = ND == 2 ? -1 : (d == 2 ? 1 : 2);
+    // lines sit at multiples of s along dimensions this level has
+    // already passed over, of 2 s along the others
+    auto shift = [&](int j) { return pos[j] < k ? lvl - 1 : lvl; };
+    // at the finest level no later pass reads the far face of a
+    // dimension already passed (its lines neither hold owned points
+    // nor lie along a dimension still to come), so those lines are
+    // left out: 477 four-target tasks a 3D window instead of 562 in
+    // the order z, y, x, and a last pass of 64 whole lines
+    auto lines = [&](int j) {
+        return (uint32_t)((W[j] >> shift(j)) + (lvl == 1 && pos[j] < k ? 0 : 1));
+    };
+    const uint32_t ne = lines(e), nl = g >= 0 ? ne * lines(g) : ne;
+    PassDesc q{};
+    q.kind = (uint32_t)d | (uint32_t)in.spline[d] << 2 | (uint32_t)shift(e) << 4 |
+             (g >= 0 ? (uint32_t)shift(g) << 8 : 0u);
+    q.lines = nl | ne << 16;
+    q.magic = (kMagic.v[ne] + 0xFFFFu) >> 16;   // ceil(2^16 / ne)
+    q.el = in.el[lvl - 1];
+    q.ebx2 = in.ebx2[lvl - 1];
+    q.inv = q.el == 0.0f ? 0.0f : in.inv[lvl - 1];
+    p.pass[np] = q;
 }
 
 __device__ void make_pass(const FieldDesc& f, FieldPlan& p, const PlanIn& in, int np) {
-    const uint32_t n0 = (uint32_t)f.n[0], n01 = n0 * (uint32_t)f.n[1];
-    if (f.ndim == 3) make_pass<3>(p, in, n0, n01, np);
-    else if (f.ndim == 2) make_pass<2>(p, in, n0, n01, np);
+    if (f.ndim == 3) make_pass<3>(p, in, np);
+    else if (f.ndim == 2) make_pass<2>(p, in, np);
     // 1D: the line kernels take the level bounds and the spline directly
 }
 

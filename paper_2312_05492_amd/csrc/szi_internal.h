@@ -26,6 +26,7 @@ struct FieldDesc {
     int32_t n[3];          // n[0] fastest; unused dims 1
     int32_t w[3];          // window; unused dims 1
     int32_t nwin[3];       // windows per dimension
+    uint32_t wmag[2];      // floor(2^32 / m), m = nwin[0] and nwin[0] * nwin[1] (at most 2^32 - 1)
     int32_t na[3];         // anchors per dimension
     int32_t S, L, R;
     int32_t eb_mode;
@@ -59,26 +60,21 @@ struct FieldDesc {
 
 // One pass of the interpolation (Sec. V-A: levels from stride S/2 to 1, one
 // pass per dimension in the planned order), as the window kernels run it:
-// the points of the pass lie on nlines lines along dimension d, line
-// i0 + ne * i1 starting at LDS index i0 * le + i1 * lf of the block.
+// the points of the pass lie on nlines lines along dimension d, numbered
+// i0 + ne * i1 over the two other dimensions e < g (i1 = 0 in 2D); line
+// (i0, i1) lies at coordinate i0 << she along e and i1 << shg along g.  Six
+// words, so that the passes of a window (nine in 3D, eight in 2D) fit one
+// register of a wave, a word a lane.
 constexpr int kMaxPasses = 12;
-// Lines of a pass are numbered i0 + ne * i1 over the two other dimensions
-// e < g (i1 = 0 in 2D); line (i0, i1) lies at coordinate i0 << she along e
-// and i1 << shg along g, at LDS offset i0 le + i1 lf and global offset
-// i0 ge + i1 gf from the window origin.
 struct PassDesc {
-    int32_t d, spl, sh;        // dimension, spline, log2 of the stride
-    uint32_t nlines, ne;
-    uint32_t magic;            // ceil(2^16 / ne): line / ne = line * magic >> 16 (lines < 300)
-    int32_t le, lf;
+    uint32_t kind;             // d | spl << 2 | she << 4 | shg << 8
+    uint32_t lines;            // nlines | ne << 16
+    uint32_t magic;            // ceil(2^16 / ne): i1 = line * magic >> 16 (lines < 300)
     float el, ebx2, inv;       // level bound, 2 e_l, 1 / (2 e_l) (0 when e_l = 0)
-    int32_t de, dg;            // the other dimensions (dg = de in 2D)
-    int32_t she, shg;          // log2 of the line spacing along de and dg
-    uint32_t ge, gf;
-    uint32_t obe, obg;         // bit offsets of the owned extents along de and dg in a
-                               // window's packed extents (8 bits a dimension)
-    int32_t rne, rng;          // (1 << she) - 1 and (1 << shg) - 1
 };
+constexpr int kPassWords = sizeof(PassDesc) / 4;
+static_assert(kPassWords == 6 && 9 * kPassWords <= 64 && kMaxPasses * kPassWords >= 64,
+              "a word per lane, and a wave's load stays inside the array");
 
 // Per-field plan computed on the device from the range and the profile.
 struct FieldPlan {
