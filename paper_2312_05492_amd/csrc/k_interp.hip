@@ -380,6 +380,59 @@ __device__ __forceinline__ float predict(bool m3, bool p1, bool p3, float a, flo
     return p1 ? p : b;
 }
 
+// Natural cubics whose numerators lie below the fast division's range (a
+// NaN passes the minimum by: either division keeps it a NaN): rare, so one
+// test for all targets of all lanes.
+template <int K>
+__device__ __forceinline__ void divide_small(float (&pr)[K], const float (&nm)[K]) {
+    float least = fabsf(nm[0]);
+#pragma unroll
+    for (int j = 1; j < K; ++j) least = fminf(least, fabsf(nm[j]));
+    if (wave_any(!(least >= 0x1p-123f))) {
+#pragma unroll
+        for (int j = 0; j < K; ++j)
+            if (!(fabsf(nm[j]) >= 0x1p-123f)) pr[j] = nm[j] / 40.0f;
+    }
+}
+
+// Closed-loop quantisation of K targets of a lane against e_l (Sec. III-A):
+// reconstructed values xr and codes cd from predictions pr and originals
+// xv.  With e_l = 0, inv = 0 gives q = 0 and xr = p + 0, so only exact
+// predictions pass the bound test.  |rint(qf)| < R holds iff |qf| < R and
+// |q| < R; NaN fails it.  The FP64 bound test |x - xr| <= e_l is decided in
+// FP32 where the rounded difference is below e_l (then so is the exact one),
+// in FP64 otherwise.  One test of the largest |q| and |x - xr| of all
+// targets of all lanes (in[j] false: a target outside the field, left out)
+// decides whether any target has to be looked at by itself.
+template <int K>
+__device__ __forceinline__ void quantise(const float (&pr)[K], const float (&xv)[K],
+                                         const bool (&in)[K], float el, float ebx2, float inv,
+                                         int R, float (&xr)[K], uint32_t (&cd)[K]) {
+    const float Rf = (float)R;
+    float qr[K], dm = 0.0f, qm = 0.0f;
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        qr[j] = rintf((xv[j] - pr[j]) * inv);   // round half to even
+        xr[j] = pr[j] + qr[j] * ebx2;           // (float)(int)q == q in range
+        // this maximum keeps a NaN (a prediction past the largest float)
+        qm = __builtin_elementwise_maximum(qm, in[j] ? fabsf(qr[j]) : 0.0f);
+        dm = __builtin_elementwise_maximum(dm, in[j] ? fabsf(xv[j] - xr[j]) : 0.0f);
+        cd[j] = (uint32_t)((int)qr[j] + R);
+    }
+    if (wave_any(!(dm < el && qm < Rf))) {
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            // (no short-circuits: selects only, no nested branches)
+            const bool inr = fabsf(qr[j]) < Rf;
+            const bool in32 = fabsf(xv[j] - xr[j]) < el;
+            const bool in64 = fabs((double)xv[j] - (double)xr[j]) <= (double)el;
+            const bool good = inr & (in32 | in64);
+            xr[j] = good ? xr[j] : xv[j];
+            cd[j] = good ? cd[j] : 0u;
+        }
+    }
+}
+
 // Makes the compiler wait here for loads into these registers, so that it
 // places no wait for them further on (where it would also hold for every
 // store and load issued since).
@@ -496,7 +549,7 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const Pass& 
     const uint32_t ne = pd.lines >> 16, magic = pd.magic;
     const uint32_t she = (pd.kind >> 4) & 15u, shg = (pd.kind >> 8) & 15u;
     const uint32_t ntask = (pd.lines & 0xFFFFu) * (uint32_t)NSEG;
-    const float ebx2 = pd.ebx2, inv = pd.inv, Rf = (float)R;
+    const float ebx2 = pd.ebx2, inv = pd.inv;
     const float el = pd.el;
     const uint32_t gsd = D == 0 ? 1u : (D == 1 ? wi.n0 : wi.n01);   // global stride along D
 
@@ -569,53 +622,15 @@ __device__ __forceinline__ void pass_lines(float* v, uint32_t lane, const Pass& 
             pr[j] = predict<SPL>(m3, p1, p3, tk.kn[j], tk.kn[j + 1], tk.kn[j + 2], tk.kn[j + 3],
                                  nm[j]);
         }
-        if (SPL == SPL_NAT) {   // numerators below the fast division's range: rare
-            // (a NaN passes the minimum by: either division keeps it a NaN)
-            float least = fabsf(nm[0]);
-#pragma unroll
-            for (int j = 1; j < K; ++j) least = fminf(least, fabsf(nm[j]));
-            if (wave_any(!(least >= 0x1p-123f))) {
-#pragma unroll
-                for (int j = 0; j < K; ++j)
-                    if (!(fabsf(nm[j]) >= 0x1p-123f)) pr[j] = nm[j] / 40.0f;
-            }
-        }
+        if (SPL == SPL_NAT) divide_small<K>(pr, nm);
         float* vb = v + tk.base;
         if (COMP) {
-            // closed-loop quantisation against e_l (Sec. III-A): with
-            // e_l = 0, inv = 0 gives q = 0 and xr = p + 0, so only exact
-            // predictions pass the bound test
-            float qr[K], xr[K], dm = 0.0f, qm = 0.0f;
+            float xr[K];
             uint32_t cd[K];
+            bool in[K];
 #pragma unroll
-            for (int j = 0; j < K; ++j) {
-                const float p = pr[j], xv = tk.xt[j];
-                qr[j] = rintf((xv - p) * inv);   // round half to even
-                xr[j] = p + qr[j] * ebx2;        // (float)(int)q == q in range
-                // the largest |q| and |x - xr| of the task; the maximum
-                // keeps a NaN (a prediction past the largest float)
-                const bool in = FULL || p0 + (2 * j + 1) * s < ed;
-                qm = __builtin_elementwise_maximum(qm, in ? fabsf(qr[j]) : 0.0f);
-                dm = __builtin_elementwise_maximum(dm, in ? fabsf(xv - xr[j]) : 0.0f);
-                cd[j] = (uint32_t)((int)qr[j] + R);
-            }
-            // |rint(qf)| < R holds iff |qf| < R and |q| < R; NaN fails it.
-            // The FP64 bound test |x - xr| <= e_l is decided in FP32 where
-            // the rounded difference is below e_l (then so is the exact
-            // one), in FP64 otherwise.
-            if (wave_any(!(dm < el && qm < Rf))) {
-#pragma unroll
-                for (int j = 0; j < K; ++j) {
-                    const float xv = tk.xt[j];
-                    // (no short-circuits: selects only, no nested branches)
-                    const bool inr = fabsf(qr[j]) < Rf;
-                    const bool in32 = fabsf(xv - xr[j]) < el;
-                    const bool in64 = fabs((double)xv - (double)xr[j]) <= (double)el;
-                    const bool good = inr & (in32 | in64);
-                    xr[j] = good ? xr[j] : xv;
-                    cd[j] = good ? cd[j] : 0u;
-                }
-            }
+            for (int j = 0; j < K; ++j) in[j] = FULL || p0 + (2 * j + 1) * s < ed;
+            quantise<K>(pr, tk.xt, in, el, ebx2, inv, R, xr, cd);
             if (store) {
 #pragma unroll
                 for (int j = 0; j < K; ++j) vb[(2 * j + 1) * s * SD] = xr[j];
@@ -1071,171 +1086,420 @@ SZI_WINDOW_KERNEL void k_decompress(const FieldDesc* __restrict__ F,
 // Sec. V-A in one dimension: anchors every kS1 = 512 points, nine levels
 // (strides 256 .. 1), one pass per level.  A window is four chunks, 2048
 // points, plus the far anchor, as the 3D and 2D windows span four chunks
-// along x; one wave per window, its block in LDS, one target per lane at a
-// time.  The stencils, the quantiser and the histogram are those of the
-// window passes above.
-constexpr int kS1 = 512, kL1 = 9, kW1 = 4 * kS1;
-constexpr int kV1 = kW1 + 4;   // LDS floats per wave: the block of kW1 + 1
+// along x; one wave per window.
+//
+// Lane t holds points 32 t .. 32 t + 31 in registers.  The levels of stride
+// 16 and below lie inside the lanes: a lane's targets read its own points
+// and three of its neighbours' (lane moves), every index a compile-time
+// constant; those five levels hold 31 of 32 points.  The four coarse levels
+// work on the lanes' first points, one target a lane, through LDS.  Values
+// and codes cross between this layout and coalesced 16-byte global accesses
+// through a wave's LDS rows of 32 words, the 16-byte groups of a row
+// permuted by the row so that neither side meets bank conflicts.
+// Bound by instruction issue and, near it, by memory: 2^26 points, rel 1e-3:
+// compression 112 us (3.6 TB/s of values and codes), replay 96 us; one target
+// per lane at a time with its four neighbours read from LDS took 250 and
+// 217 us.
+constexpr int kS1 = 512, kW1 = 4 * kS1;
+constexpr int kP1 = kW1 / 64;   // points per lane
+static_assert(kP1 == 32, "a lane's points are one LDS row");
 
 struct Win1 {
-    uint64_t lo;   // first point
+    uint32_t lo;   // first point
     int e;         // block extent: owned points, and the far anchor where present
     int o;         // owned extent
 };
 
 __device__ __forceinline__ Win1 make_win1(const FieldDesc& f, uint32_t w) {
     Win1 wi;
-    wi.lo = (uint64_t)w * (uint64_t)kW1;
-    const uint64_t left = f.npts - 1 - wi.lo;
-    wi.e = (int)(left < (uint64_t)kW1 ? left : (uint64_t)kW1) + 1;
+    // a field has fewer than 2^32 points (the compiler drops the scalar
+    // condition of the 64-bit comparison)
+    wi.lo = w * (uint32_t)kW1;
+    const uint32_t left = (uint32_t)f.npts - 1u - wi.lo;
+    wi.e = (int)(left < (uint32_t)kW1 ? left : (uint32_t)kW1) + 1;
     wi.o = wi.e < kW1 ? wi.e : kW1;
     return wi;
 }
 
-// One level at stride s: the targets at odd multiples of s in the window.
-// Compression stores each owned target's quant-code at cb and counts it;
-// the replay takes an outlier's value from ob.
-template <int SPL, bool COMP>
-__device__ __forceinline__ void level1(float* v, uint32_t lane, int s, const Win1& wi, float el,
-                                       float ebx2, float inv, int R, SZI_G uint16_t* cb,
-                                       const SZI_G float* ob, uint32_t* hist, uint32_t& cntR) {
-    const int nt = kW1 / (2 * s);
-    const float Rf = (float)R;
-    const int last = wi.e - 1;   // the window interval ends here
-#pragma unroll 1
-    for (int t = (int)lane; t < nt; t += 64) {
-        const int p = (2 * t + 1) * s;
-        const bool act = p <= last;
-        const bool m3 = p >= 3 * s;
-        const bool p1 = p + s <= last;
-        const bool p3 = p + 3 * s <= last;
-        const float a = m3 ? v[p - 3 * s] : 0.0f;
-        const float b = v[p - s];
-        const float c = p1 ? v[p + s] : 0.0f;
-        const float d = p3 ? v[p + 3 * s] : 0.0f;
-        float num;
-        float pr = predict<SPL>(m3, p1, p3, a, b, c, d, num);
-        if (SPL == SPL_NAT) {   // numerators below the fast division's range: rare
-            const bool small = !(fabsf(num) >= 0x1p-123f);
-            if (wave_any(small) && small) pr = num / 40.0f;
+// word of point i of a window in the LDS rows
+__device__ __forceinline__ uint32_t row_word(uint32_t i) {
+    const uint32_t r = i >> 5, g = (i >> 2) & 7u;
+    return r * 32u + 4u * (g ^ (r & 7u)) + (i & 3u);
+}
+// word that holds the 16-bit codes i and i ^ 1 in the LDS rows of 16 words
+__device__ __forceinline__ uint32_t code_word(uint32_t i) {
+    const uint32_t r = i >> 5, g = (i >> 3) & 3u;
+    return r * 16u + 4u * (g ^ ((r >> 2) & 3u)) + ((i >> 1) & 3u);
+}
+// the value of the lane below / above (lanes 0 and 63 get no meaningful one)
+__device__ __forceinline__ float lane_below(float x) {
+    constexpr int kWaveShr = 0x138;
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kWaveShr, 0xF, 0xF, false));
+}
+__device__ __forceinline__ float lane_above(float x) {
+    constexpr int kWaveShl = 0x130;
+    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), kWaveShl, 0xF, 0xF, false));
+}
+
+// What the passes of a window need besides its values: codes of the lane's
+// points, two a word (written in compression, read in the replay).
+struct Lane1 {
+    float r[kP1];          // the lane's points
+    uint32_t pk[kP1 / 2];  // their codes
+    float far;             // the far anchor
+};
+
+// Finishes K targets at the lane's points o0, o0 + so, ..: quantises and
+// counts them (compression) or adds their residuals (replay).
+template <int SPL, bool COMP, bool FULL, int K>
+__device__ __forceinline__ void finish1(Lane1& L, uint32_t lane, int o0, int so, float (&pr)[K],
+                                        const float (&nm)[K], const bool (&in)[K], const Win1& wi,
+                                        float el, float ebx2, float inv, int R,
+                                        const SZI_G float* ob, uint32_t* hist) {
+    if (SPL == SPL_NAT) divide_small<K>(pr, nm);
+    if (COMP) {
+        float xv[K], xr[K];
+        uint32_t cd[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) xv[j] = L.r[o0 + j * so];
+        quantise<K>(pr, xv, in, el, ebx2, inv, R, xr, cd);
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int o = o0 + j * so;
+            L.r[o] = xr[j];
+            if (o & 1) L.pk[o >> 1] |= cd[j] << 16;
+            else L.pk[o >> 1] |= cd[j];
+            // the centre code goes to the lane's own bin
+            const uint32_t bin = cd[j] != (uint32_t)R ? cd[j] : (uint32_t)(2 * R) + lane;
+            if (FULL || kP1 * (int)lane + o < wi.o) atomicAdd(&hist[bin], 1u);
         }
-        if (COMP) {
-            const float xv = v[p];
-            const float q = rintf((xv - pr) * inv);
-            const float xr = pr + q * ebx2;
-            const bool inr = fabsf(q) < Rf;
-            const bool good = inr && fabsf(xv - xr) < el;
-            float vv = good ? xr : xv;
-            uint32_t cd = good ? (uint32_t)((int)q + R) : 0u;
-            if (wave_any(act && good != inr)) {   // the FP64 bound test where FP32 cannot decide
-                if (inr && !(fabsf(xv - xr) < el) && fabs((double)xv - (double)xr) <= (double)el) {
-                    vv = xr;
-                    cd = (uint32_t)((int)q + R);
-                }
+    } else {
+        uint32_t least = 0xFFFFu, cd[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int o = o0 + j * so;
+            cd[j] = (o & 1) ? L.pk[o >> 1] >> 16 : L.pk[o >> 1] & 0xFFFFu;
+            L.r[o] = pr[j] + (float)((int)cd[j] - R) * ebx2;
+            least = cd[j] < least ? cd[j] : least;
+        }
+        // code 0: an outlier, whose value the scatter step put in the output
+        // (points outside the field hold a code no point takes)
+        if (wave_any(least == 0u)) {
+            float v[K];
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                v[j] = L.r[o0 + j * so];
+                if (cd[j] == 0u) v[j] = *at(ob, (uint32_t)(kP1 * (int)lane + o0 + j * so));
             }
-            const bool own = act && p < wi.o;
-            if (act) {
-                v[p] = vv;
-                if (own) cb[p] = (uint16_t)cd;
-                const uint32_t bin = own && cd != (uint32_t)R ? cd : (uint32_t)(2 * R) + lane;
-                atomicAdd(&hist[bin], 1u);
-            }
-            cntR += (uint32_t)__popcll(wave_ballot(act && !own));
-        } else if (act) {
-            const uint32_t code = __float_as_uint(v[p]);
-            // code 0: an outlier, whose value the scatter step put in the output
-            v[p] = code == 0u ? ob[p] : pr + (float)((int)code - R) * ebx2;
+            settle(v);
+#pragma unroll
+            for (int j = 0; j < K; ++j) L.r[o0 + j * so] = v[j];
         }
     }
 }
 
-template <bool COMP>
-__device__ __forceinline__ void levels1(float* v, uint32_t lane, const FieldPlan& pl, const Win1& wi,
-                                        int R, SZI_G uint16_t* cb, const SZI_G float* ob,
-                                        uint32_t* hist, uint32_t& cntR) {
-#pragma unroll 1
-    for (int l = kL1; l >= 1; --l) {
-        const int s = 1 << (l - 1);
-        const float el = pl.el[l - 1], ebx2 = pl.ebx2[l - 1];
-        const float inv = el == 0.0f ? 0.0f : pl.inv[l - 1];
-        if (pl.spline[0] == SPL_LIN) level1<SPL_LIN, COMP>(v, lane, s, wi, el, ebx2, inv, R, cb, ob, hist, cntR);
-        else if (pl.spline[0] == SPL_NAK) level1<SPL_NAK, COMP>(v, lane, s, wi, el, ebx2, inv, R, cb, ob, hist, cntR);
-        else level1<SPL_NAT, COMP>(v, lane, s, wi, el, ebx2, inv, R, cb, ob, hist, cntR);
+// One level of stride S1 <= 16, inside the lanes; next0: the first point of
+// the lane above.
+template <int S1, int SPL, bool COMP, bool FULL>
+__device__ __forceinline__ void fine_level1(Lane1& L, uint32_t lane, float next0, const FieldPlan& pl,
+                                            const Win1& wi, int R, const SZI_G float* ob,
+                                            uint32_t* hist) {
+    constexpr int lvl = S1 == 1 ? 0 : S1 == 2 ? 1 : S1 == 4 ? 2 : S1 == 8 ? 3 : 4;
+    constexpr int N = kP1 / (2 * S1);        // targets per lane
+    constexpr int K = N < 4 ? N : 4;         // finished together
+    const float el = pl.el[lvl], ebx2 = pl.ebx2[lvl];
+    const float inv = el == 0.0f ? 0.0f : pl.inv[lvl];
+    // the known before the lane's first point, and the one past next0
+    const float below = lane_below(L.r[(kP1 - 2 * S1) % kP1]);
+    const float above = lane_above(S1 == 16 ? next0 : L.r[(2 * S1) % kP1]);
+    // lane 63's step past next0 would leave the window; lane 62 of stride
+    // 16 reaches the far anchor, which only next0 of lane 63 holds
+    const int last = wi.e - 1;
+    auto known = [&](int o) SZI_INLINE {
+        return o < 0 ? below : (o < kP1 ? L.r[o] : (o == kP1 ? next0 : above));
+    };
+#pragma unroll
+    for (int j0 = 0; j0 < N; j0 += K) {
+        float pr[K], nm[K];
+        bool in[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int i = j0 + j, o = (2 * i + 1) * S1;
+            const int pos = kP1 * (int)lane + o;
+            const bool m3 = i > 0 || lane > 0u;
+            const bool p1 = FULL || pos + S1 <= last;
+            const bool p3 = FULL ? (i < N - 1 || lane < 63u) : pos + 3 * S1 <= last;
+            in[j] = FULL || pos <= last;
+            pr[j] = predict<SPL>(m3, p1, p3, known(o - 3 * S1), known(o - S1), known(o + S1),
+                                 known(o + 3 * S1), nm[j]);
+        }
+        finish1<SPL, COMP, FULL, K>(L, lane, (2 * j0 + 1) * S1, 2 * S1, pr, nm, in, wi, el, ebx2, inv,
+                                    R, ob, hist);
+        // targets finished later are not predicted ahead (their registers
+        // would not fit)
+        __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// All levels of a window.  c: 66 words of the wave's LDS.
+template <int SPL, bool COMP, bool FULL>
+__device__ __forceinline__ void levels1(Lane1& L, float* c, uint32_t lane, const FieldPlan& pl,
+                                        const Win1& wi, int R, const SZI_G float* ob,
+                                        uint32_t* hist) {
+    const int last = wi.e - 1;
+    const int pos = kP1 * (int)lane;
+    if (lane == 0) c[64] = L.far;
+#pragma unroll
+    for (int m = 8; m >= 1; m >>= 1) {   // strides 32 m: 256, 128, 64, 32
+        constexpr int kLvl[9] = {0, 5, 6, 0, 7, 0, 0, 0, 8};
+        const int lvl = kLvl[m], s = kP1 * m;
+        const float el = pl.el[lvl], ebx2 = pl.ebx2[lvl];
+        const float inv = el == 0.0f ? 0.0f : pl.inv[lvl];
+        c[lane] = L.r[0];
         wave_sync();
+        const int t = (int)lane;
+        const float a = c[t >= 3 * m ? t - 3 * m : 0], b = c[t >= m ? t - m : 0];
+        const float cc = c[t + m < 64 ? t + m : 64], d = c[t + 3 * m < 64 ? t + 3 * m : 64];
+        wave_sync();
+        if ((t & (2 * m - 1)) == m) {
+            float pr[1], nm[1];
+            bool in[1] = {FULL || pos <= last};
+            pr[0] = predict<SPL>(pos >= 3 * s, pos + s <= last, pos + 3 * s <= last, a, b, cc, d, nm[0]);
+            finish1<SPL, COMP, FULL, 1>(L, lane, 0, 1, pr, nm, in, wi, el, ebx2, inv, R, ob, hist);
+        }
     }
+    const float up = lane_above(L.r[0]);
+    const float next0 = lane == 63u ? L.far : up;
+    fine_level1<16, SPL, COMP, FULL>(L, lane, next0, pl, wi, R, ob, hist);
+    fine_level1<8, SPL, COMP, FULL>(L, lane, next0, pl, wi, R, ob, hist);
+    fine_level1<4, SPL, COMP, FULL>(L, lane, next0, pl, wi, R, ob, hist);
+    fine_level1<2, SPL, COMP, FULL>(L, lane, next0, pl, wi, R, ob, hist);
+    fine_level1<1, SPL, COMP, FULL>(L, lane, next0, pl, wi, R, ob, hist);
 }
 
-__global__ __launch_bounds__(kThreads) void k_compress1d(const FieldDesc* __restrict__ F,
-                                                         const FieldPlan* __restrict__ P,
-                                                         const uint64_t* __restrict__ goff,
-                                                         uint64_t ngroups) {
-    __shared__ float vbuf[kWaves][kV1];
+template <bool COMP, bool FULL>
+__device__ __forceinline__ void levels1_spline(Lane1& L, float* c, uint32_t lane, const FieldPlan& pl,
+                                               const Win1& wi, int R, const SZI_G float* ob,
+                                               uint32_t* hist) {
+    const int spl = pl.spline[0];
+    if (spl == SPL_LIN) levels1<SPL_LIN, COMP, FULL>(L, c, lane, pl, wi, R, ob, hist);
+    else if (spl == SPL_NAK) levels1<SPL_NAK, COMP, FULL>(L, c, lane, pl, wi, R, ob, hist);
+    else levels1<SPL_NAT, COMP, FULL>(L, c, lane, pl, wi, R, ob, hist);
+}
+
+// The next window of a wave: whole windows on 16-byte boundaries are loaded
+// ahead, 16 bytes a lane, while the current one is processed; others when
+// their turn comes, value by value.
+struct Next1 {
+    Win1 wi;
+    int f;
+    bool valid, ahead;
+};
+
+// (compression holds the block, its codes and the next block: 166 registers
+// without spills; four waves a SIMD spilled the next block, 199 us)
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) void k_compress1d(
+    const FieldDesc* __restrict__ F, const FieldPlan* __restrict__ P,
+    const uint64_t* __restrict__ goff, uint64_t ngroups) {
+    __shared__ __align__(16) float vbuf[kWaves][kW1];
     extern __shared__ uint32_t hist[];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t lane = threadIdx.x & 63u;
     float* v = vbuf[wave];
+    GroupSeq gs = group_seq(ngroups);
+    if (!gs.ok()) return;
     int f = 0, hf = -1;
-    uint32_t cntR = 0;
-#pragma unroll 1
-    for (GroupSeq gs = group_seq(ngroups); gs.ok(); gs.next()) {
+    uint32_t none = 0;
+    Next1 nx;
+    vf4 pre[8];
+    float farp = 0.0f;
+    auto fetch = [&]() SZI_INLINE {
         while (gs.g >= goff[f + 1]) ++f;
-        if (f != hf) {   // uniform over the workgroup: groups never span fields
-            if (hf >= 0) flush_hist(hist, cntR, F[hf]);
-            clear_hist(hist, F[f].R);
-            __syncthreads();
-            hf = f;
-        }
         const FieldDesc& fd = F[f];
         const uint32_t w = (uint32_t)(gs.g - goff[f]) * kWaves + gs.slot(wave);
-        if (w >= (uint32_t)fd.nwin[0]) continue;
-        const Win1 wi = make_win1(fd, w);
-        const SZI_G float* in = gp(fd.in) + wi.lo;
-#pragma unroll 4
-        for (int i = (int)lane; i < wi.e; i += 64) v[i] = in[i];
-        wave_sync();
-        SZI_G uint16_t* cb = gp(fd.codes) + wi.lo;
-        levels1<true>(v, lane, P[f], wi, fd.R, cb, nullptr, hist, cntR);
-        // owned anchors: their values losslessly, quant-code R, counted
-        if (lane < (uint32_t)(kW1 / kS1) && (int)lane * kS1 < wi.o) {
-            gp(fd.anchors)[wi.lo / kS1 + lane] = v[lane * kS1];
-            cb[lane * kS1] = (uint16_t)fd.R;
-            atomicAdd(&hist[2 * fd.R + lane], 1u);
+        nx.f = f;
+        nx.valid = w < (uint32_t)fd.nwin[0];
+        nx.ahead = false;
+        if (nx.valid) {
+            nx.wi = make_win1(fd, w);
+            nx.ahead = nx.wi.o == kW1 && ((uintptr_t)fd.in & 15u) == 0u;
+            const SZI_G float* in = gp(fd.in) + nx.wi.lo;
+            if (nx.ahead) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k) pre[k] = *at((const SZI_G vf4*)in, 64u * k + lane);
+            }
+            if (nx.wi.e > kW1) farp = in[kW1];
         }
-        wave_sync();
+    };
+    fetch();
+    while (true) {
+        asm volatile("" : "+v"(lane));   // LDS addresses are formed anew, not kept in registers
+        const Next1 cu = nx;
+        Lane1 L;
+        L.far = farp;
+        if (cu.f != hf) {   // uniform over the workgroup: groups never span fields
+            if (hf >= 0) flush_hist(hist, none, F[hf]);
+            clear_hist(hist, F[cu.f].R);
+            __syncthreads();
+            hf = cu.f;
+        }
+        const FieldDesc& fd = F[cu.f];
+        if (cu.valid) {
+            if (cu.ahead) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    *reinterpret_cast<vf4*>(v + row_word(256u * k + 4u * lane)) = pre[k];
+            } else {
+                const SZI_G float* in = gp(fd.in) + cu.wi.lo;
+#pragma unroll 4
+                for (int i = (int)lane; i < kW1; i += 64) v[row_word((uint32_t)i)] = i < cu.wi.o ? in[i] : 0.0f;
+            }
+            wave_sync();
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+                const vf4 q = *reinterpret_cast<const vf4*>(v + row_word(32u * lane + 4u * g));
+                L.r[4 * g] = q.x;
+                L.r[4 * g + 1] = q.y;
+                L.r[4 * g + 2] = q.z;
+                L.r[4 * g + 3] = q.w;
+            }
+            wave_sync();
+        }
+        gs.next();
+        const bool more = gs.ok();
+        if (more) fetch();   // in flight during the passes below
+        if (cu.valid) {
+            const int R = fd.R;
+#pragma unroll
+            for (int k = 0; k < kP1 / 2; ++k) L.pk[k] = 0u;
+            // owned anchors: their values losslessly, quant-code R, counted
+            const int pos = kP1 * (int)lane;
+            if ((pos & (kS1 - 1)) == 0 && pos < cu.wi.o) {
+                gp(fd.anchors)[(cu.wi.lo + (uint32_t)pos) / (uint32_t)kS1] = L.r[0];
+                L.pk[0] = (uint32_t)R;
+                atomicAdd(&hist[2 * R + (int)lane], 1u);
+            }
+            if (cu.wi.e > kW1) levels1_spline<true, true>(L, v, lane, P[cu.f], cu.wi, R, nullptr, hist);
+            else levels1_spline<true, false>(L, v, lane, P[cu.f], cu.wi, R, nullptr, hist);
+            // the codes, two a word, through LDS to coalesced stores
+            wave_sync();
+            uint32_t* u = reinterpret_cast<uint32_t*>(v);
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *reinterpret_cast<vu4*>(u + code_word(32u * lane + 8u * g)) =
+                    vu4{L.pk[4 * g], L.pk[4 * g + 1], L.pk[4 * g + 2], L.pk[4 * g + 3]};
+            wave_sync();
+            SZI_G uint16_t* cb = gp(fd.codes) + cu.wi.lo;   // 16-byte aligned
+            if (cu.wi.o == kW1) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    *at((SZI_G vu4*)cb, 64u * k + lane) =
+                        *reinterpret_cast<const vu4*>(u + code_word(512u * k + 8u * lane));
+            } else {
+                for (int i = (int)lane; i < cu.wi.o; i += 64)
+                    cb[i] = (uint16_t)(u[code_word((uint32_t)i)] >> (16 * (i & 1)));
+            }
+            wave_sync();
+        }
+        if (!more) break;
     }
-    if (hf >= 0) flush_hist(hist, cntR, F[hf]);
+    flush_hist(hist, none, F[hf]);
 }
 
-__global__ __launch_bounds__(kThreads) void k_decompress1d(const FieldDesc* __restrict__ F,
-                                                           const FieldPlan* __restrict__ P,
-                                                           const uint64_t* __restrict__ goff,
-                                                           uint64_t ngroups) {
-    __shared__ float vbuf[kWaves][kV1];
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decompress1d(
+    const FieldDesc* __restrict__ F, const FieldPlan* __restrict__ P,
+    const uint64_t* __restrict__ goff, uint64_t ngroups) {
+    __shared__ __align__(16) float vbuf[kWaves][kW1];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t lane = threadIdx.x & 63u;
     float* v = vbuf[wave];
+    uint32_t* u = reinterpret_cast<uint32_t*>(v);
+    GroupSeq gs = group_seq(ngroups);
+    if (!gs.ok()) return;
     int f = 0;
-    uint32_t unused = 0;
-#pragma unroll 1
-    for (GroupSeq gs = group_seq(ngroups); gs.ok(); gs.next()) {
+    Next1 nx;
+    vu4 pre[4];
+    float ancp = 0.0f, farp = 0.0f;
+    auto fetch = [&]() SZI_INLINE {
         while (gs.g >= goff[f + 1]) ++f;
         const FieldDesc& fd = F[f];
         const uint32_t w = (uint32_t)(gs.g - goff[f]) * kWaves + gs.slot(wave);
-        if (w >= (uint32_t)fd.nwin[0]) continue;
-        const Win1 wi = make_win1(fd, w);
-        // every point takes its code (as float bits), the anchors their values
-        const SZI_G uint16_t* cb = gp(fd.codes) + wi.lo;
-#pragma unroll 4
-        for (int i = (int)lane; i < wi.e; i += 64) v[i] = __uint_as_float((uint32_t)cb[i]);
-        wave_sync();
-        if (lane <= (uint32_t)(kW1 / kS1) && (int)lane * kS1 < wi.e)
-            v[lane * kS1] = gp(fd.anchors)[wi.lo / kS1 + lane];
-        wave_sync();
-        SZI_G float* ob = gp(fd.out) + wi.lo;
-        levels1<false>(v, lane, P[f], wi, fd.R, nullptr, ob, nullptr, unused);
-#pragma unroll 4
-        for (int i = (int)lane; i < wi.o; i += 64) ob[i] = v[i];
-        wave_sync();
+        nx.f = f;
+        nx.valid = w < (uint32_t)fd.nwin[0];
+        nx.ahead = false;
+        if (nx.valid) {
+            nx.wi = make_win1(fd, w);
+            nx.ahead = nx.wi.o == kW1;
+            const SZI_G uint16_t* cb = gp((const uint16_t*)fd.codes) + nx.wi.lo;   // 16-byte aligned
+            if (nx.ahead) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) pre[k] = *at((const SZI_G vu4*)cb, 64u * k + lane);
+            }
+            const int pos = kP1 * (int)lane;
+            const SZI_G float* anc = gp((const float*)fd.anchors) + nx.wi.lo / (uint32_t)kS1;
+            if ((pos & (kS1 - 1)) == 0 && pos < nx.wi.o) ancp = anc[pos / kS1];
+            if (nx.wi.e > kW1) farp = anc[kW1 / kS1];
+        }
+    };
+    fetch();
+    while (true) {
+        asm volatile("" : "+v"(lane));   // LDS addresses are formed anew, not kept in registers
+        const Next1 cu = nx;
+        const FieldDesc& fd = F[cu.f];
+        Lane1 L;
+        L.far = farp;
+        L.r[0] = ancp;
+        if (cu.valid) {
+            if (cu.ahead) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    *reinterpret_cast<vu4*>(u + code_word(512u * k + 8u * lane)) = pre[k];
+            } else {
+                // points outside the field hold a code no point takes
+                const SZI_G uint16_t* cb = gp((const uint16_t*)fd.codes) + cu.wi.lo;
+                uint16_t* h = reinterpret_cast<uint16_t*>(u);
+                for (int i = (int)lane; i < kW1; i += 64)
+                    h[2u * code_word((uint32_t)i) + (uint32_t)(i & 1)] = i < cu.wi.o ? cb[i] : (uint16_t)0xFFFFu;
+            }
+            wave_sync();
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const vu4 q = *reinterpret_cast<const vu4*>(u + code_word(32u * lane + 8u * g));
+                L.pk[4 * g] = q.x;
+                L.pk[4 * g + 1] = q.y;
+                L.pk[4 * g + 2] = q.z;
+                L.pk[4 * g + 3] = q.w;
+            }
+            wave_sync();
+        }
+        gs.next();
+        const bool more = gs.ok();
+        if (more) fetch();   // in flight during the passes below
+        if (cu.valid) {
+            const int R = fd.R;
+            SZI_G float* ob = gp(fd.out) + cu.wi.lo;
+            if (cu.wi.e > kW1) levels1_spline<false, true>(L, v, lane, P[cu.f], cu.wi, R, ob, nullptr);
+            else levels1_spline<false, false>(L, v, lane, P[cu.f], cu.wi, R, ob, nullptr);
+            wave_sync();
+#pragma unroll
+            for (int g = 0; g < 8; ++g)
+                *reinterpret_cast<vf4*>(v + row_word(32u * lane + 4u * g)) =
+                    vf4{L.r[4 * g], L.r[4 * g + 1], L.r[4 * g + 2], L.r[4 * g + 3]};
+            wave_sync();
+            // the next window's codes are here by now: waited for ahead of
+            // the stores, not behind them
+            settle(pre);
+            if (cu.wi.o == kW1 && ((uintptr_t)fd.out & 15u) == 0u) {
+#pragma unroll
+                for (int k = 0; k < 8; ++k)
+                    *at((SZI_G vf4*)ob, 64u * k + lane) =
+                        *reinterpret_cast<const vf4*>(v + row_word(256u * k + 4u * lane));
+            } else {
+                for (int i = (int)lane; i < cu.wi.o; i += 64) ob[i] = v[row_word((uint32_t)i)];
+            }
+            wave_sync();
+        }
+        if (!more) break;
     }
 }
 

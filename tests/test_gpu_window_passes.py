@@ -60,3 +60,19 @@ def test_rare_branches(ctx, shape):
     # predictions that overflow
     big = np.where(rng.random(shape) < 0.5, np.float32(3e38), np.float32(-3e38)).astype(np.float32)
     check(ctx, big, eb=1e30, eb_mode=0, interp=(2,) * len(shape))
+
+
+@pytest.mark.parametrize("interp", [0, 1, 2])
+@pytest.mark.parametrize("n", [2, 31, 32, 33, 65, 511, 512, 513, 1025, 1537, 1985, 2016, 2017, 2047, 4096, 4097, 6143,
+                               10240, 8 * 2048 * 4 + 7])
+def test_line_sizes(ctx, n, interp):
+    check(ctx, synth.spectral_field((n,), seed=104), interp=(interp,), eb=1e-3)
+
+
+def test_line_rare_branches(ctx):
+    rng = np.random.default_rng(105)
+    x = synth.spectral_field((9000,), seed=105)
+    check(ctx, np.where(rng.random(9000) < 0.01, x + np.float32(1e3), x).astype(np.float32), eb=1e-3, eb_mode=0)
+    check(ctx, x + np.float32(1000.0), eb=2.0 ** -12, eb_mode=0, interp=(2,))
+    big = np.where(rng.random(9000) < 0.5, np.float32(3e38), np.float32(-3e38)).astype(np.float32)
+    check(ctx, big, eb=1e30, eb_mode=0, interp=(2,))
