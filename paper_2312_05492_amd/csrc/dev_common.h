@@ -71,9 +71,8 @@ __device__ __forceinline__ uint32_t wave_excl_scan(uint32_t v, uint32_t* total) 
     return x - v;
 }
 
-// Division by a small divisor m (< kMagicN) of dividends t < 2^16 through a
-// multiply-high by ceil(2^32 / m); exact because t * m < 2^32.  The
-// multipliers come from a constant table, so no divide runs on the GPU.
+// ceil(2^32 / m) for small divisors m: the window kernels divide by m with a
+// multiply and a shift, from a constant table, so no divide runs on the GPU.
 constexpr int kMagicN = 2048;
 struct MagicTable {
     uint32_t v[kMagicN];
@@ -82,15 +81,6 @@ struct MagicTable {
     }
 };
 static __constant__ MagicTable kMagic = MagicTable();
-
-struct FastDiv {
-    uint32_t m, mg;
-    __device__ __forceinline__ void set(uint32_t mm) {
-        m = mm;
-        mg = kMagic.v[mm];
-    }
-    __device__ __forceinline__ uint32_t div(uint32_t t) const { return m > 1 ? __umulhi(t, mg) : t; }
-};
 
 __device__ __forceinline__ bool finite_bits(float v) {
     return (__float_as_uint(v) & 0x7f800000u) != 0x7f800000u;

@@ -663,17 +663,27 @@ constexpr int kGroups = 4, kGenGroup = 3;
 inline int group_of(const Geometry& g) { return g.generic ? kGenGroup : 3 - g.ndim; }
 inline int ndim_of(int group) { return 3 - group; }   // groups 0..2
 
+// points of a window's block (the window and its far faces)
+inline uint64_t block_points(const Geometry& g) {
+    uint64_t b = 1;
+    for (int k = 0; k < g.ndim; ++k) b *= (uint64_t)g.w[k] + 1;
+    return b;
+}
+
+// block: points of the largest block of the group (generic kernels)
 hipError_t launch_compress_group(sz_ctx* c, int gi, const FieldDesc* d_fd, const FieldPlan* d_plan,
                                  const uint64_t* d_items, uint64_t nitems, LaunchShape sh, int max_R,
-                                 hipStream_t q) {
-    if (gi == kGenGroup) return launch_compress_gen(d_fd, d_plan, d_items, nitems, c->num_cus, max_R, q);
+                                 uint64_t block, hipStream_t q) {
+    if (gi == kGenGroup)
+        return launch_compress_gen(d_fd, d_plan, d_items, nitems, c->num_cus, max_R, block, q);
     return launch_compress(ndim_of(gi), d_fd, d_plan, d_items, nitems, c->num_cus, sh, max_R, q);
 }
 
 hipError_t launch_decompress_group(sz_ctx* c, int gi, const FieldDesc* d_fd, const FieldPlan* d_plan,
                                    const uint64_t* d_items, uint64_t nitems, LaunchShape sh,
-                                   hipStream_t q) {
-    if (gi == kGenGroup) return launch_decompress_gen(d_fd, d_plan, d_items, nitems, c->num_cus, q);
+                                   uint64_t block, hipStream_t q) {
+    if (gi == kGenGroup)
+        return launch_decompress_gen(d_fd, d_plan, d_items, nitems, c->num_cus, block, q);
     return launch_decompress(ndim_of(gi), d_fd, d_plan, d_items, nitems, c->num_cus, sh, q);
 }
 
@@ -1196,7 +1206,11 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
     sz_status s;
     // work lists: one per dimensionality, fields in input order
     std::vector<uint32_t> grp[kGroups];
-    for (uint32_t i = 0; i < nf; ++i) grp[group_of(geo[i])].push_back(i);
+    uint64_t gen_block = 0;
+    for (uint32_t i = 0; i < nf; ++i) {
+        grp[group_of(geo[i])].push_back(i);
+        if (geo[i].generic) gen_block = std::max(gen_block, block_points(geo[i]));
+    }
     // stage descriptors grouped: 3D fields first, then 2D, then 1D, so that each
     // group's item offsets index a contiguous slice of the descriptor array
     std::vector<uint32_t> perm;
@@ -1377,7 +1391,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
                 STAGE(c, SZ_STAGE_INTERP, q);
                 HIP_TRY(c, launch_compress_group(c, gi, d_fd + base, d_plan + base,
                                                  d_items + gi * (nf + 1), nitems[gi],
-                                                 shape_for(c, 0, ndim_of(gi), max_R), max_R, q));
+                                                 shape_for(c, 0, ndim_of(gi), max_R), max_R, gen_block, q));
             }
             base += (uint32_t)grp[gi].size();
         }
@@ -1417,7 +1431,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         const std::vector<uint64_t> sig = {nf, nitems[0], nitems[1], nitems[2], nitems[3],
                                            grp[0].size(), grp[1].size(), grp[2].size(),
                                            (uint64_t)max_R, (uint64_t)s3.per_cu, (uint64_t)s2.variant,
-                                           (uint64_t)s2.per_cu, L.off};
+                                           (uint64_t)s2.per_cu, L.off, gen_block};
         char* d = static_cast<char*>(c->arena);
         s = graph_run(c, 1, sig, o_fd, end1 - o_fd, st, [&](hipStream_t q) -> sz_status {
             sz_status r = enqueue1(q);
@@ -1481,7 +1495,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
                 if (!grp[gi].empty())
                     HIP_TRY(c, launch_compress_group(c, gi, d_fd + base, d_plan + base,
                                                      d_items + gi * (nf + 1), nitems[gi],
-                                                     shape_for(c, 0, nd, max_R), max_R, st));
+                                                     shape_for(c, 0, nd, max_R), max_R, gen_block, st));
                 base += (uint32_t)grp[gi].size();
             }
         }
@@ -1806,6 +1820,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
     std::vector<uint32_t> grp[kGroups];
     std::vector<Geometry> geo(nf);
     int max_R = 0;
+    uint64_t gen_block = 0;
     for (uint32_t i = 0; i < nf; ++i) {
         const ResultInternal* R = ri(&res[i]);
         if (!R || !d_out[i] || !res[i].words || !res[i].chunk_bits || !res[i].anchors)
@@ -1826,6 +1841,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
             res[i].n_anchors != geo[i].nanch)
             return fail(c, SZ_ERR_CORRUPT, "result %u: sizes do not match its dimensions", i);
         grp[group_of(geo[i])].push_back(i);
+        if (geo[i].generic) gen_block = std::max(gen_block, block_points(geo[i]));
         max_R = std::max(max_R, geo[i].R);
     }
     std::vector<uint32_t> perm;
@@ -1892,7 +1908,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
                 STAGE(c, SZ_STAGE_REPLAY, q);
                 HIP_TRY(c, launch_decompress_group(c, gi, d_fd + base, d_plan + base,
                                                    d_items + gi * (nf + 1), nitems[gi],
-                                                   shape_for(c, 1, ndim_of(gi), max_R), q));
+                                                   shape_for(c, 1, ndim_of(gi), max_R), gen_block, q));
             }
             base += (uint32_t)grp[gi].size();
         }
@@ -1921,7 +1937,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         const std::vector<uint64_t> sig = {nf, nblocks, nitems[0], nitems[1], nitems[2], nitems[3],
                                            grp[0].size(), grp[1].size(), grp[2].size(),
                                            (uint64_t)max_R, (uint64_t)s3.per_cu, (uint64_t)s2.variant,
-                                           (uint64_t)s2.per_cu, L.off, split ? 1u : 0u};
+                                           (uint64_t)s2.per_cu, L.off, split ? 1u : 0u, gen_block};
         if ((s = graph_run(c, 0, sig, 0, staged, st, enqueue))) return s;
         HIP_TRY(c, hipStreamSynchronize(c->gstream));
         return SZ_OK;
@@ -2055,7 +2071,7 @@ sz_status sz_decompress_noalloc(sz_ctx* c, const sz_result* res, float* d_out, v
     HIP_TRY(c, launch_huff_decode(d_fd, 1, d_dboff, nblocks, d_bsum, 2 * geo.R,
                                   R->d_sub != nullptr ? 1 : 0, st));
     HIP_TRY(c, launch_decompress_group(c, group_of(geo), d_fd, d_plan, d_items, ngroups,
-                                       shape_for(c, 1, geo.ndim, geo.R), st));
+                                       shape_for(c, 1, geo.ndim, geo.R), block_points(geo), st));
     return SZ_OK;
 }
 

@@ -24,6 +24,7 @@
 
 #include <map>
 #include <mutex>
+#include <type_traits>
 
 namespace szi {
 
@@ -898,16 +899,13 @@ __device__ __forceinline__ GroupSeq group_seq(uint64_t ngroups) {
 
 // --------------------------------------------------------------- kernels
 // LDS histogram of a workgroup: the 2R symbols, then one bin per lane that
-// collects the centre code and the targets a window does not own; nown
-// (wave-uniform) counts the latter.  The flush folds the lane bins into
-// the centre bin (modulo 2^32, so the subtraction may wrap on the way).
+// collects the centre code; the flush folds the lane bins into the centre
+// bin.
 __device__ __forceinline__ void clear_hist(uint32_t* hist, int R) {
 #pragma unroll 1
     for (int b = threadIdx.x; b < 2 * R + 64; b += kThreads) hist[b] = 0;
 }
-__device__ __forceinline__ void flush_hist(uint32_t* hist, uint32_t& nown, const FieldDesc& fd) {
-    if ((threadIdx.x & 63) == 0 && nown) atomicAdd(&hist[fd.R], 0u - nown);
-    nown = 0;
+__device__ __forceinline__ void flush_hist(uint32_t* hist, const FieldDesc& fd) {
     __syncthreads();
     if (threadIdx.x < 64) {
         const uint32_t c = wave_sum(hist[2 * fd.R + threadIdx.x]);
@@ -968,13 +966,13 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
     };
     fetch();
     int hf = -1;         // field whose histogram the workgroup accumulates
-    uint32_t cntR = 0, passes = 0;
+    uint32_t passes = 0;
     while (true) {
         const int fc = f;
         const Win wc = wn;
         const bool vc = valid, qc = quads;
         if (fc != hf) {   // uniform over the workgroup: groups never span fields
-            if (hf >= 0) flush_hist(hist, cntR, F[hf]);
+            if (hf >= 0) flush_hist(hist, F[hf]);
             clear_hist(hist, F[fc].R);
             __syncthreads();
             hf = fc;
@@ -999,7 +997,7 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
         }
         if (!more) break;
     }
-    flush_hist(hist, cntR, F[hf]);
+    flush_hist(hist, F[hf]);
 }
 
 template <int ND, int WPE>
@@ -1309,7 +1307,6 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
     GroupSeq gs = group_seq(ngroups);
     if (!gs.ok()) return;
     int f = 0, hf = -1;
-    uint32_t none = 0;
     Next1 nx;
     vf4 pre[8];
     float farp = 0.0f;
@@ -1338,7 +1335,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
         Lane1 L;
         L.far = farp;
         if (cu.f != hf) {   // uniform over the workgroup: groups never span fields
-            if (hf >= 0) flush_hist(hist, none, F[hf]);
+            if (hf >= 0) flush_hist(hist, F[hf]);
             clear_hist(hist, F[cu.f].R);
             __syncthreads();
             hf = cu.f;
@@ -1403,7 +1400,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) v
         }
         if (!more) break;
     }
-    flush_hist(hist, none, F[hf]);
+    flush_hist(hist, F[hf]);
 }
 
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) void k_decompress1d(
@@ -1508,8 +1505,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(4))) v
 // V-D leave both open: the window trades prediction accuracy at its faces
 // against parallelism) run a generic pair of kernels with the geometry read
 // from the field descriptor: one wave per window, its block (window + far
-// faces) in LDS, each pass's targets one per lane at a time.  The passes,
-// stencils, quantiser and histogram are those above.
+// faces) in LDS.  The passes work on lines as those above, K consecutive
+// targets of a line per task, with run-time strides; stencils, quantiser and
+// histogram are the same.  Bound by instruction issue: 16x16x8 windows of a
+// 256x384x384 field, rel 1e-3, compression 216 us and replay 194 us, against
+// 449 and 370 with one target a lane, its coordinates by two 32-bit
+// multiplies at a quarter of the rate, and 64 KB of LDS a workgroup whatever
+// the block.
 struct WinG {
     uint64_t gbase;
     uint32_t n0, n01;
@@ -1537,102 +1539,196 @@ __device__ __forceinline__ WinG make_wing(const FieldDesc& f, uint32_t w) {
     return wi;
 }
 
-// a point's block coordinates from its number among m0 x m1 x m2 grid
-// points with the given spacing and offset per dimension
-struct Grid3 {
-    FastDiv f0, f1;
-    int step[3], off[3];
-    __device__ __forceinline__ void at(uint32_t t, int* c) const {
-        const uint32_t t1 = f0.div(t), i0 = t - t1 * f0.m;
-        const uint32_t i2 = f1.div(t1), i1 = t1 - i2 * f1.m;
-        c[0] = off[0] + (int)i0 * step[0];
-        c[1] = off[1] + (int)i1 * step[1];
-        c[2] = off[2] + (int)i2 * step[2];
+// t / m for t <= 2^12 and m < kMagicN, from the high half of a 24-bit product:
+// (t 2^8) ceil(2^24 / m) / 2^32, exact because t m < 2^24 (24-bit multiplies
+// issue at full rate)
+struct Div24 {
+    uint32_t m, mg;
+    __device__ __forceinline__ void set(uint32_t mm) {
+        m = mm;
+        mg = (kMagic.v[mm] + 0xFFu) >> 8;
+    }
+    __device__ __forceinline__ uint32_t div(uint32_t t) const {
+        const uint32_t a = (t << 8) & 0xFFFFFFu, b = mg & 0xFFFFFFu;
+        return m > 1 ? (uint32_t)(((uint64_t)a * b) >> 32) : t;
     }
 };
+static_assert((uint64_t)kGenMaxBlock * (kGenMaxExtent + 1) < (1ull << 24) && kGenMaxBlock <= (1 << 12),
+              "block points times an extent stay below 2^24");
 
-// One pass of the generic kernels: dimension d at stride s; the other
-// dimensions at multiples of s where this level has passed them, of 2 s
-// where not (Sec. V-A).
-template <int SPL, bool COMP>
-__device__ __forceinline__ void pass_gen(float* v, uint32_t lane, const FieldDesc& fd, const WinG& wi,
-                                         int d, int s, const bool* passed, float el, float ebx2,
-                                         float inv, SZI_G uint16_t* cb, const SZI_G float* ob,
-                                         uint32_t* hist, uint32_t& cntR) {
-    const int R = fd.R;
-    Grid3 gr;
-    uint32_t m[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        const int lim = wi.e[j] - 1;
-        if (j == d) {
-            gr.step[j] = 2 * s;
-            gr.off[j] = s;
-            m[j] = lim >= s ? (uint32_t)((lim - s) / (2 * s) + 1) : 0u;
-        } else {
-            gr.step[j] = passed[j] ? s : 2 * s;
-            gr.off[j] = 0;
-            m[j] = (uint32_t)(lim / gr.step[j] + 1);
-        }
+// a point's block coordinates from its number among m0 x m1 x m2 grid
+// points with the given spacing per dimension
+struct Grid3 {
+    Div24 f0, f1;
+    int step;
+    __device__ __forceinline__ void at(uint32_t t, uint32_t* c) const {
+        const uint32_t t1 = f0.div(t), i0 = t - __umul24(t1, f0.m);
+        const uint32_t i2 = f1.div(t1), i1 = t1 - __umul24(i2, f1.m);
+        c[0] = i0 * (uint32_t)step;
+        c[1] = i1 * (uint32_t)step;
+        c[2] = i2 * (uint32_t)step;
     }
-    gr.f0.set(m[0]);
-    gr.f1.set(m[1]);
-    const uint32_t nt = m[0] * m[1] * m[2];
-    const int lim = wi.e[d] - 1;
-    const int sd = d == 0 ? 1 : (d == 1 ? wi.B0 : wi.B01);
-    const float Rf = (float)R;
+};
+// index of block coordinates in LDS and from the window origin in the field
+// (fewer than 2^32 points, so 32 bits hold it; its bytes may need more)
+__device__ __forceinline__ uint32_t lds_index(const WinG& wi, const uint32_t* c) {
+    return c[0] + __umul24(c[1], (uint32_t)wi.B0) + __umul24(c[2], (uint32_t)wi.B01);
+}
+__device__ __forceinline__ uint32_t field_index(const WinG& wi, const uint32_t* c) {
+    return c[0] + mul16x32(c[1], wi.n0) + mul16x32(c[2], wi.n01);
+}
+
+// One pass of the generic kernels along D at stride s: nseg tasks of K
+// targets per line, lines ne x ng along the other dimensions e < g, spaced
+// ste and stg (Sec. V-A: s where this level has passed the dimension, 2 s
+// where not).  FULL: the window interval along D is the whole block and K
+// divides its targets.
+template <int D, int SPL, bool COMP, bool FULL, int K>
+__device__ __forceinline__ void lines_gen(float* v, uint32_t lane, const WinG& wi, int s, uint32_t nseg,
+                                          uint32_t ne, uint32_t ng, uint32_t ste, uint32_t stg,
+                                          bool store, float el, float ebx2, float inv, int R,
+                                          SZI_G uint16_t* cb, const SZI_G float* ob, uint32_t* hist) {
+    constexpr int DE = D == 0 ? 1 : 0, DG = D == 2 ? 1 : 2;
+    const int SD = D == 0 ? 1 : (D == 1 ? wi.B0 : wi.B01);
+    const uint32_t SE = DE == 0 ? 1u : (uint32_t)wi.B0, SG = (uint32_t)(DG == 1 ? wi.B0 : wi.B01);
+    const uint32_t gsd = D == 0 ? 1u : (D == 1 ? wi.n0 : wi.n01);
+    const uint32_t gse = DE == 0 ? 1u : wi.n0, gsg = DG == 1 ? wi.n0 : wi.n01;
+    const uint32_t owne = (uint32_t)wi.o[DE], owng = (uint32_t)wi.o[DG];
+    const int lim = wi.e[D] - 1;
+    Div24 fs, fe;
+    fs.set(nseg);
+    fe.set(ne);
+    const uint32_t nt = nseg * ne * ng;
 #pragma unroll 1
     for (uint32_t t = lane; t < nt; t += 64) {
-        int c[3];
-        gr.at(t, c);
-        const int li = c[0] + c[1] * wi.B0 + c[2] * wi.B01;
-        const int cd = c[d];
-        const bool m3 = cd >= 3 * s;
-        const bool p1 = cd + s <= lim;
-        const bool p3 = cd + 3 * s <= lim;
-        const float a = m3 ? v[li - 3 * s * sd] : 0.0f;
-        const float b = v[li - s * sd];
-        const float cc = p1 ? v[li + s * sd] : 0.0f;
-        const float dd = p3 ? v[li + 3 * s * sd] : 0.0f;
-        float num;
-        float pr = predict<SPL>(m3, p1, p3, a, b, cc, dd, num);
-        if (SPL == SPL_NAT) {
-            const bool small = !(fabsf(num) >= 0x1p-123f);
-            if (wave_any(small) && small) pr = num / 40.0f;
+        const uint32_t ln = fs.div(t), seg = t - __umul24(ln, nseg);
+        const uint32_t i1 = fe.div(ln), i0 = ln - __umul24(i1, ne);
+        const uint32_t ce = __umul24(i0, ste), cg = __umul24(i1, stg);
+        const int base = (int)(__umul24(ce, SE) + __umul24(cg, SG));
+        const int p0 = (int)__umul24(seg, (uint32_t)(2 * K) * (uint32_t)s);   // segment start along D
+        // the K + 3 knowns around the targets; those outside the block are
+        // read at its ends (the flags drop them)
+        float kn[K + 3], xt[K], pr[K], nm[K];
+#pragma unroll
+        for (int i = 0; i < K + 3; ++i) {
+            int p = p0 + (2 * i - 2) * s;
+            if (!FULL || i == 0) p = p < 0 ? 0 : p;
+            if (!FULL || i == K + 2) p = p > lim ? lim : p;
+            kn[i] = v[base + __mul24(p, SD)];
         }
-        const uint64_t g = (uint64_t)c[0] + (uint64_t)c[1] * wi.n0 + (uint64_t)c[2] * wi.n01;
+        bool in[K];
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int p = p0 + (2 * j + 1) * s;
+            in[j] = FULL || p <= lim;
+            xt[j] = v[base + __mul24(FULL || p <= lim ? p : lim, SD)];
+        }
+#pragma unroll
+        for (int j = 0; j < K; ++j) {
+            const int p = p0 + (2 * j + 1) * s;
+            pr[j] = predict<SPL>(j > 0 || seg > 0u, FULL || p + s <= lim,
+                                 FULL && j < K - 1 ? true : p + 3 * s <= lim, kn[j], kn[j + 1],
+                                 kn[j + 2], kn[j + 3], nm[j]);
+        }
+        if (SPL == SPL_NAT) divide_small<K>(pr, nm);
         if (COMP) {
-            const float xv = v[li];
-            const float q = rintf((xv - pr) * inv);
-            const float xr = pr + q * ebx2;
-            const bool inr = fabsf(q) < Rf;
-            const bool good = inr && fabsf(xv - xr) < el;
-            float vv = good ? xr : xv;
-            uint32_t code = good ? (uint32_t)((int)q + R) : 0u;
-            if (wave_any(good != inr)) {   // the FP64 bound test where FP32 cannot decide
-                if (inr && !(fabsf(xv - xr) < el) && fabs((double)xv - (double)xr) <= (double)el) {
-                    vv = xr;
-                    code = (uint32_t)((int)q + R);
+            float xr[K];
+            uint32_t cd[K];
+            quantise<K>(pr, xt, in, el, ebx2, inv, R, xr, cd);
+            if (store) {
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+                    if (in[j]) v[base + __mul24(p0 + (2 * j + 1) * s, SD)] = xr[j];
+            }
+            if (ce < owne && cg < owng) {
+                const uint32_t rb = (uint32_t)(2 * R) + lane;
+                const uint32_t gl = mul16x32((uint32_t)p0, gsd) + mul16x32(ce, gse) + mul16x32(cg, gsg);
+#pragma unroll
+                for (int j = 0; j < K; ++j) {
+                    const uint32_t q = (uint32_t)((2 * j + 1) * s);
+                    if (p0 + (int)q < wi.o[D]) {
+                        cb[gl + mul16x32(q, gsd)] = (uint16_t)cd[j];
+                        atomicAdd(&hist[cd[j] != (uint32_t)R ? cd[j] : rb], 1u);
+                    }
                 }
             }
-            v[li] = vv;
-            const bool own = c[0] < wi.o[0] && c[1] < wi.o[1] && c[2] < wi.o[2];
-            if (own) cb[g] = (uint16_t)code;
-            const uint32_t bin = own && code != (uint32_t)R ? code : (uint32_t)(2 * R) + lane;
-            atomicAdd(&hist[bin], 1u);
-            cntR += (uint32_t)__popcll(wave_ballot(!own));
         } else {
-            const uint32_t code = __float_as_uint(v[li]);
-            // code 0: an outlier, whose value the scatter step put in the output
-            v[li] = code == 0u ? ob[g] : pr + (float)((int)code - R) * ebx2;
+            uint32_t least = 1u;
+#pragma unroll
+            for (int j = 0; j < K; ++j) {
+                const uint32_t code = __float_as_uint(xt[j]);
+                pr[j] = pr[j] + (float)((int)code - R) * ebx2;
+                if (in[j]) least = code < least ? code : least;
+            }
+            // code 0: an outlier, whose value the scatter step put in the
+            // output (rare)
+            if (wave_any(least == 0u)) {
+                const uint32_t gl = mul16x32((uint32_t)p0, gsd) + mul16x32(ce, gse) + mul16x32(cg, gsg);
+#pragma unroll
+                for (int j = 0; j < K; ++j)
+                    if (in[j] && __float_as_uint(xt[j]) == 0u)
+                        pr[j] = ob[gl + mul16x32((uint32_t)((2 * j + 1) * s), gsd)];
+                settle(pr);
+            }
+#pragma unroll
+            for (int j = 0; j < K; ++j)
+                if (in[j]) v[base + __mul24(p0 + (2 * j + 1) * s, SD)] = pr[j];
         }
     }
+}
+
+template <int D, int SPL, bool COMP>
+__device__ __forceinline__ void pass_gen(float* v, uint32_t lane, const FieldDesc& fd, const WinG& wi,
+                                         int s, const bool* passed, bool store, float el, float ebx2,
+                                         float inv, SZI_G uint16_t* cb, const SZI_G float* ob,
+                                         uint32_t* hist) {
+    constexpr int DE = D == 0 ? 1 : 0, DG = D == 2 ? 1 : 2;
+    const int lim = wi.e[D] - 1;
+    if (lim < s) return;   // no targets
+    const uint32_t m = (uint32_t)((lim - s) / (2 * s) + 1);   // targets per line
+    // at the finest level no later pass reads the far face of a dimension
+    // already passed
+    auto lines = [&](int j) SZI_INLINE {
+        const int last = s == 1 && passed[j] ? wi.o[j] - 1 : wi.e[j] - 1;
+        return (uint32_t)(last / (passed[j] ? s : 2 * s) + 1);
+    };
+    const uint32_t ne = lines(DE), ng = lines(DG);
+    const uint32_t ste = (uint32_t)(passed[DE] ? s : 2 * s), stg = (uint32_t)(passed[DG] ? s : 2 * s);
+    // long tasks where the pass has more than a few waves of targets: they
+    // share knowns and the task's set-up
+    const uint32_t all = m * ne * ng;
+    const bool full = wi.e[D] == fd.w[D] + 1;
+    auto go = [&](auto k) SZI_INLINE {
+        constexpr int K = decltype(k)::value;
+        if (full && m % (uint32_t)K == 0u)
+            lines_gen<D, SPL, COMP, true, K>(v, lane, wi, s, m / (uint32_t)K, ne, ng, ste, stg, store, el,
+                                             ebx2, inv, fd.R, cb, ob, hist);
+        else
+            lines_gen<D, SPL, COMP, false, K>(v, lane, wi, s, (m + (uint32_t)K - 1) / (uint32_t)K, ne, ng,
+                                              ste, stg, store, el, ebx2, inv, fd.R, cb, ob, hist);
+    };
+    if (all >= 192u && m >= 3u) go(std::integral_constant<int, 4>{});
+    else go(std::integral_constant<int, 1>{});
+}
+
+template <int D, bool COMP>
+__device__ __forceinline__ void pass_gen_spline(float* v, uint32_t lane, const FieldDesc& fd,
+                                                const WinG& wi, int spl, int s, const bool* passed,
+                                                bool store, float el, float ebx2, float inv,
+                                                SZI_G uint16_t* cb, const SZI_G float* ob,
+                                                uint32_t* hist) {
+    if (spl == SPL_LIN)
+        pass_gen<D, SPL_LIN, COMP>(v, lane, fd, wi, s, passed, store, el, ebx2, inv, cb, ob, hist);
+    else if (spl == SPL_NAK)
+        pass_gen<D, SPL_NAK, COMP>(v, lane, fd, wi, s, passed, store, el, ebx2, inv, cb, ob, hist);
+    else
+        pass_gen<D, SPL_NAT, COMP>(v, lane, fd, wi, s, passed, store, el, ebx2, inv, cb, ob, hist);
 }
 
 template <bool COMP>
 __device__ __forceinline__ void levels_gen(float* v, uint32_t lane, const FieldDesc& fd,
                                            const FieldPlan& pl, const WinG& wi, SZI_G uint16_t* cb,
-                                           const SZI_G float* ob, uint32_t* hist, uint32_t& cntR) {
+                                           const SZI_G float* ob, uint32_t* hist) {
 #pragma unroll 1
     for (int l = fd.L; l >= 1; --l) {
         const int s = 1 << (l - 1);
@@ -1643,13 +1739,17 @@ __device__ __forceinline__ void levels_gen(float* v, uint32_t lane, const FieldD
         for (int k = 0; k < fd.ndim; ++k) {
             const int d = pl.order[k];
             const int spl = pl.spline[d];
-            if (spl == SPL_LIN)
-                pass_gen<SPL_LIN, COMP>(v, lane, fd, wi, d, s, passed, el, ebx2, inv, cb, ob, hist, cntR);
-            else if (spl == SPL_NAK)
-                pass_gen<SPL_NAK, COMP>(v, lane, fd, wi, d, s, passed, el, ebx2, inv, cb, ob, hist, cntR);
-            else
-                pass_gen<SPL_NAT, COMP>(v, lane, fd, wi, d, s, passed, el, ebx2, inv, cb, ob, hist, cntR);
-            passed[d] = true;
+            const bool store = l > 1 || k + 1 < fd.ndim;   // the last pass's values are read by none
+            if (d == 0) {
+                pass_gen_spline<0, COMP>(v, lane, fd, wi, spl, s, passed, store, el, ebx2, inv, cb, ob, hist);
+                passed[0] = true;
+            } else if (d == 1) {
+                pass_gen_spline<1, COMP>(v, lane, fd, wi, spl, s, passed, store, el, ebx2, inv, cb, ob, hist);
+                passed[1] = true;
+            } else {
+                pass_gen_spline<2, COMP>(v, lane, fd, wi, spl, s, passed, store, el, ebx2, inv, cb, ob, hist);
+                passed[2] = true;
+            }
             wave_sync();
         }
     }
@@ -1660,40 +1760,38 @@ __device__ __forceinline__ void levels_gen(float* v, uint32_t lane, const FieldD
 __device__ __forceinline__ Grid3 block_grid(const int* ext, int step, uint32_t& n) {
     Grid3 gr;
     uint32_t m[3];
+    gr.step = step;
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-        gr.step[j] = step;
-        gr.off[j] = 0;
-        m[j] = (uint32_t)((ext[j] - 1) / step + 1);
-    }
+    for (int j = 0; j < 3; ++j) m[j] = (uint32_t)((ext[j] - 1) / step + 1);
     gr.f0.set(m[0]);
     gr.f1.set(m[1]);
     n = m[0] * m[1] * m[2];
     return gr;
 }
 
-__device__ __forceinline__ uint32_t anchor_index(const FieldDesc& fd, const WinG& wi, const int* c) {
-    return (uint32_t)((wi.lo[0] + c[0]) / fd.S) +
-           (uint32_t)fd.na[0] * ((uint32_t)((wi.lo[1] + c[1]) / fd.S) +
-                                 (uint32_t)fd.na[1] * (uint32_t)((wi.lo[2] + c[2]) / fd.S));
+__device__ __forceinline__ uint32_t anchor_index(const FieldDesc& fd, const WinG& wi, const uint32_t* c) {
+    return ((uint32_t)wi.lo[0] + c[0]) / (uint32_t)fd.S +
+           (uint32_t)fd.na[0] * (((uint32_t)wi.lo[1] + c[1]) / (uint32_t)fd.S +
+                                 (uint32_t)fd.na[1] * (((uint32_t)wi.lo[2] + c[2]) / (uint32_t)fd.S));
 }
 
+// BW: LDS words per wave, at least the largest block of the launch
+template <int BW>
 __global__ __launch_bounds__(kThreads) void k_compress_gen(const FieldDesc* __restrict__ F,
                                                            const FieldPlan* __restrict__ P,
                                                            const uint64_t* __restrict__ goff,
                                                            uint64_t ngroups) {
-    __shared__ float vbuf[kWaves][kGenMaxBlock];
+    __shared__ float vbuf[kWaves][BW];
     extern __shared__ uint32_t hist[];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t lane = threadIdx.x & 63u;
     float* v = vbuf[wave];
     int f = 0, hf = -1;
-    uint32_t cntR = 0;
 #pragma unroll 1
     for (GroupSeq gs = group_seq(ngroups); gs.ok(); gs.next()) {
         while (gs.g >= goff[f + 1]) ++f;
         if (f != hf) {   // uniform over the workgroup: groups never span fields
-            if (hf >= 0) flush_hist(hist, cntR, F[hf]);
+            if (hf >= 0) flush_hist(hist, F[hf]);
             clear_hist(hist, F[f].R);
             __syncthreads();
             hf = f;
@@ -1706,41 +1804,48 @@ __global__ __launch_bounds__(kThreads) void k_compress_gen(const FieldDesc* __re
         uint32_t nb;
         const Grid3 bg = block_grid(wi.e, 1, nb);
 #pragma unroll 1
-        for (uint32_t t = lane; t < nb; t += 64) {
-            int c[3];
-            bg.at(t, c);
-            v[c[0] + c[1] * wi.B0 + c[2] * wi.B01] =
-                in[(uint64_t)c[0] + (uint64_t)c[1] * wi.n0 + (uint64_t)c[2] * wi.n01];
+        for (uint32_t t = lane; t < nb; t += 512) {   // eight loads in flight
+            float x[8];
+            uint32_t li[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                uint32_t c[3];
+                bg.at(t + 64u * k < nb ? t + 64u * k : nb - 1u, c);
+                li[k] = lds_index(wi, c);
+                x[k] = in[field_index(wi, c)];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[li[k]] = x[k];   // past the end: the last point again
         }
         wave_sync();
         SZI_G uint16_t* cb = gp(fd.codes) + wi.gbase;
-        levels_gen<true>(v, lane, fd, P[f], wi, cb, nullptr, hist, cntR);
+        levels_gen<true>(v, lane, fd, P[f], wi, cb, nullptr, hist);
         // owned anchors: their values losslessly, quant-code R, counted
         uint32_t na;
         const Grid3 ag = block_grid(wi.o, fd.S, na);
 #pragma unroll 1
         for (uint32_t t = lane; t < na; t += 64) {
-            int c[3];
+            uint32_t c[3];
             ag.at(t, c);
-            gp(fd.anchors)[anchor_index(fd, wi, c)] = v[c[0] + c[1] * wi.B0 + c[2] * wi.B01];
-            cb[(uint64_t)c[0] + (uint64_t)c[1] * wi.n0 + (uint64_t)c[2] * wi.n01] = (uint16_t)fd.R;
+            gp(fd.anchors)[anchor_index(fd, wi, c)] = v[lds_index(wi, c)];
+            cb[field_index(wi, c)] = (uint16_t)fd.R;
             atomicAdd(&hist[2 * fd.R + lane], 1u);
         }
         wave_sync();
     }
-    if (hf >= 0) flush_hist(hist, cntR, F[hf]);
+    if (hf >= 0) flush_hist(hist, F[hf]);
 }
 
+template <int BW>
 __global__ __launch_bounds__(kThreads) void k_decompress_gen(const FieldDesc* __restrict__ F,
                                                              const FieldPlan* __restrict__ P,
                                                              const uint64_t* __restrict__ goff,
                                                              uint64_t ngroups) {
-    __shared__ float vbuf[kWaves][kGenMaxBlock];
+    __shared__ float vbuf[kWaves][BW];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t lane = threadIdx.x & 63u;
     float* v = vbuf[wave];
     int f = 0;
-    uint32_t unused = 0;
 #pragma unroll 1
     for (GroupSeq gs = group_seq(ngroups); gs.ok(); gs.next()) {
         while (gs.g >= goff[f + 1]) ++f;
@@ -1749,36 +1854,41 @@ __global__ __launch_bounds__(kThreads) void k_decompress_gen(const FieldDesc* __
         if (w >= (uint32_t)(fd.nwin[0] * fd.nwin[1] * fd.nwin[2])) continue;
         const WinG wi = make_wing(fd, w);
         // every point takes its code (as float bits), the anchors their values
-        const SZI_G uint16_t* cb = gp(fd.codes) + wi.gbase;
+        const SZI_G uint16_t* cb = gp((const uint16_t*)fd.codes) + wi.gbase;
         uint32_t nb;
         const Grid3 bg = block_grid(wi.e, 1, nb);
 #pragma unroll 1
-        for (uint32_t t = lane; t < nb; t += 64) {
-            int c[3];
-            bg.at(t, c);
-            v[c[0] + c[1] * wi.B0 + c[2] * wi.B01] = __uint_as_float(
-                (uint32_t)cb[(uint64_t)c[0] + (uint64_t)c[1] * wi.n0 + (uint64_t)c[2] * wi.n01]);
+        for (uint32_t t = lane; t < nb; t += 512) {   // eight loads in flight
+            uint32_t x[8], li[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                uint32_t c[3];
+                bg.at(t + 64u * k < nb ? t + 64u * k : nb - 1u, c);
+                li[k] = lds_index(wi, c);
+                x[k] = (uint32_t)cb[field_index(wi, c)];
+            }
+#pragma unroll
+            for (int k = 0; k < 8; ++k) v[li[k]] = __uint_as_float(x[k]);
         }
         wave_sync();
         uint32_t na;
         const Grid3 ag = block_grid(wi.e, fd.S, na);
 #pragma unroll 1
         for (uint32_t t = lane; t < na; t += 64) {
-            int c[3];
+            uint32_t c[3];
             ag.at(t, c);
-            v[c[0] + c[1] * wi.B0 + c[2] * wi.B01] = gp(fd.anchors)[anchor_index(fd, wi, c)];
+            v[lds_index(wi, c)] = gp((const float*)fd.anchors)[anchor_index(fd, wi, c)];
         }
         wave_sync();
         SZI_G float* ob = gp(fd.out) + wi.gbase;
-        levels_gen<false>(v, lane, fd, P[f], wi, nullptr, ob, nullptr, unused);
+        levels_gen<false>(v, lane, fd, P[f], wi, nullptr, ob, nullptr);
         uint32_t no;
         const Grid3 og = block_grid(wi.o, 1, no);
-#pragma unroll 1
+#pragma unroll 4
         for (uint32_t t = lane; t < no; t += 64) {
-            int c[3];
+            uint32_t c[3];
             og.at(t, c);
-            ob[(uint64_t)c[0] + (uint64_t)c[1] * wi.n0 + (uint64_t)c[2] * wi.n01] =
-                v[c[0] + c[1] * wi.B0 + c[2] * wi.B01];
+            ob[field_index(wi, c)] = v[lds_index(wi, c)];
         }
         wave_sync();
     }
@@ -1833,24 +1943,41 @@ hipError_t launch_compress(int ndim, const FieldDesc* d_fields, const FieldPlan*
     return hipGetLastError();
 }
 
+// The generic kernels by the LDS their blocks need: up to 1152 words a wave
+// leave seven workgroups a CU, up to 2816 three, the largest blocks two.
+template <class Fn>
+static void by_block(uint64_t block, Fn&& go) {
+    if (block <= 1152) go(std::integral_constant<int, 1152>{});
+    else if (block <= 2816) go(std::integral_constant<int, 2816>{});
+    else go(std::integral_constant<int, kGenMaxBlock>{});
+}
+
 hipError_t launch_compress_gen(const FieldDesc* d_fields, const FieldPlan* d_plans,
                                const uint64_t* d_goff, uint64_t ngroups, int num_cus, int max_R,
-                               hipStream_t st) {
+                               uint64_t block, hipStream_t st) {
     if (ngroups == 0) return hipSuccess;
+    if (block > (uint64_t)kGenMaxBlock) return hipErrorInvalidValue;
     const size_t lds = (size_t)(2 * max_R + 64) * sizeof(uint32_t);
-    const uint64_t grid = resident_grid(k_compress_gen, lds, num_cus, 0, ngroups);
-    hipLaunchKernelGGL(k_compress_gen, dim3((unsigned)grid), dim3(kThreads), lds, st, d_fields,
-                       d_plans, d_goff, ngroups);
+    by_block(block, [&](auto bw) {
+        auto k = k_compress_gen<decltype(bw)::value>;
+        const uint64_t grid = resident_grid(k, lds, num_cus, 0, ngroups);
+        hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kThreads), lds, st, d_fields, d_plans, d_goff,
+                           ngroups);
+    });
     return hipGetLastError();
 }
 
 hipError_t launch_decompress_gen(const FieldDesc* d_fields, const FieldPlan* d_plans,
                                  const uint64_t* d_goff, uint64_t ngroups, int num_cus,
-                                 hipStream_t st) {
+                                 uint64_t block, hipStream_t st) {
     if (ngroups == 0) return hipSuccess;
-    const uint64_t grid = resident_grid(k_decompress_gen, 0, num_cus, 0, ngroups);
-    hipLaunchKernelGGL(k_decompress_gen, dim3((unsigned)grid), dim3(kThreads), 0, st, d_fields,
-                       d_plans, d_goff, ngroups);
+    if (block > (uint64_t)kGenMaxBlock) return hipErrorInvalidValue;
+    by_block(block, [&](auto bw) {
+        auto k = k_decompress_gen<decltype(bw)::value>;
+        const uint64_t grid = resident_grid(k, 0, num_cus, 0, ngroups);
+        hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(kThreads), 0, st, d_fields, d_plans, d_goff,
+                           ngroups);
+    });
     return hipGetLastError();
 }
 

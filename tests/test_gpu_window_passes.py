@@ -76,3 +76,27 @@ def test_line_rare_branches(ctx):
     check(ctx, x + np.float32(1000.0), eb=2.0 ** -12, eb_mode=0, interp=(2,))
     big = np.where(rng.random(9000) < 0.5, np.float32(3e38), np.float32(-3e38)).astype(np.float32)
     check(ctx, big, eb=1e30, eb_mode=0, interp=(2,))
+
+
+# (shape, stride, window): block sizes on both sides of the kernels' LDS sizes (1152, 2816 and 4096 words), long and
+# thin windows, ragged fields whose last windows hold a single plane
+GENERAL = [((33, 34, 25), 8, (16, 16, 8)), ((17, 40, 50), 8, (8, 8, 24)), ((9, 25, 98), 8, (8, 8, 48)),
+           ((20, 33, 35), 4, (12, 16, 16)), ((13, 14, 15), 2, (2, 2, 2)), ((40, 41, 43), 4, (8, 8, 32)),
+           ((33, 65), 32, (32, 32)), ((34, 130), 16, (32, 96)), ((70, 45), 4, (60, 4)), ((2100,), 8, (1024,)),
+           ((1030,), 2, (2,)), ((5000,), 256, (768,))]
+
+
+@pytest.mark.parametrize("shape,stride,window", GENERAL)
+@pytest.mark.parametrize("interp", [0, 1, 2])
+def test_other_windows(ctx, shape, stride, window, interp):
+    x = synth.spectral_field(shape, seed=106)
+    check(ctx, x, S=stride, window=window, interp=(interp,) * len(shape), eb=1e-3)
+
+
+def test_other_window_orders_and_rare_branches(ctx):
+    x = synth.spectral_field((20, 35, 30), seed=107)
+    for order in itertools.permutations(range(3)):
+        check(ctx, x, S=8, window=(16, 16, 8), order=order, interp=(2, 1, 0), eb=1e-4)
+    rng = np.random.default_rng(108)
+    check(ctx, np.where(rng.random(x.shape) < 0.01, x + np.float32(1e3), x).astype(np.float32), S=4, eb=1e-3, eb_mode=0)
+    check(ctx, x + np.float32(1000.0), S=4, eb=2.0 ** -12, eb_mode=0, interp=(2, 2, 2))
