@@ -4,7 +4,10 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
+
+#if defined(__x86_64__)
+#include <wmmintrin.h>
+#endif
 
 namespace szi {
 
@@ -127,19 +130,106 @@ uint64_t get64(const uint8_t* h, uint64_t off) { uint64_t v; std::memcpy(&v, h +
 float getf(const uint8_t* h, uint64_t off) { float v; std::memcpy(&v, h + off, 4); return v; }
 double getd(const uint8_t* h, uint64_t off) { double v; std::memcpy(&v, h + off, 8); return v; }
 
-uint32_t crc32_update(uint32_t crc, const uint8_t* p, size_t n) {
-    static uint32_t table[256];
-    static std::once_flag once;
-    std::call_once(once, [] {
+// CRC-32 (reflected polynomial 0xEDB88320).  The register's bit 31 - i holds
+// the coefficient of x^i; a step shifts it one power up.
+namespace {
+
+constexpr uint32_t kPoly = 0xEDB88320u;
+
+uint32_t times_x(uint32_t c) { return (c & 1) ? kPoly ^ (c >> 1) : c >> 1; }
+
+struct CrcTables {
+    uint32_t t[8][256];   // t[k][b]: byte b followed by k zero bytes
+    CrcTables() {
         for (uint32_t i = 0; i < 256; ++i) {
             uint32_t c = i;
-            for (int k = 0; k < 8; ++k) c = (c & 1) ? 0xEDB88320u ^ (c >> 1) : c >> 1;
-            table[i] = c;
+            for (int k = 0; k < 8; ++k) c = times_x(c);
+            t[0][i] = c;
         }
-    });
-    crc = ~crc;
-    for (size_t i = 0; i < n; ++i) crc = table[(crc ^ p[i]) & 0xFF] ^ (crc >> 8);
-    return ~crc;
+        for (int k = 1; k < 8; ++k)
+            for (uint32_t i = 0; i < 256; ++i) t[k][i] = t[0][t[k - 1][i] & 0xFF] ^ (t[k - 1][i] >> 8);
+    }
+};
+const CrcTables& crc_tables() {
+    static const CrcTables tab;
+    return tab;
+}
+
+// the register after n bytes, eight a step
+uint32_t crc_bytes(uint32_t c, const uint8_t* p, size_t n) {
+    const CrcTables& T = crc_tables();
+    for (; n >= 8; n -= 8, p += 8) {
+        uint32_t a, b;
+        std::memcpy(&a, p, 4);
+        std::memcpy(&b, p + 4, 4);
+        a ^= c;
+        c = T.t[7][a & 0xFF] ^ T.t[6][(a >> 8) & 0xFF] ^ T.t[5][(a >> 16) & 0xFF] ^ T.t[4][a >> 24] ^
+            T.t[3][b & 0xFF] ^ T.t[2][(b >> 8) & 0xFF] ^ T.t[1][(b >> 16) & 0xFF] ^ T.t[0][b >> 24];
+    }
+    for (; n; --n, ++p) c = T.t[0][(c ^ *p) & 0xFF] ^ (c >> 8);
+    return c;
+}
+
+#if defined(__x86_64__)
+// Folding with carry-less multiplies (the method of Gopal et al., "Fast CRC
+// Computation for Generic Polynomials Using PCLMULQDQ Instruction", Intel,
+// 2009).  A 16-byte register holds 128 message bits, the first bit the
+// highest power; moving it D bits up multiplies its first half by
+// x^(64 + D) mod P and its second by x^D mod P.  In this bit order a product
+// comes out one power too high, so the factors hold one power less.
+struct CrcFold {
+    uint64_t far_hi, far_lo, near_hi, near_lo;   // D = 512 and 128 bits
+    CrcFold() {
+        auto power = [](int n) {   // x^n mod P as a 64-bit factor
+            uint32_t c = 0x80000000u;
+            while (n--) c = times_x(c);
+            return (uint64_t)c << 32;
+        };
+        far_hi = power(64 + 512 - 1);
+        far_lo = power(512 - 1);
+        near_hi = power(64 + 128 - 1);
+        near_lo = power(128 - 1);
+    }
+};
+
+__attribute__((target("pclmul,sse2"))) __m128i crc_fold(__m128i x, __m128i k, __m128i next) {
+    const __m128i a = _mm_clmulepi64_si128(x, k, 0x00), b = _mm_clmulepi64_si128(x, k, 0x11);
+    return _mm_xor_si128(_mm_xor_si128(a, b), next);
+}
+
+// the register after n >= 64 bytes
+__attribute__((target("pclmul,sse2"))) uint32_t crc_clmul(uint32_t c, const uint8_t* p, size_t n) {
+    static const CrcFold K;
+    const __m128i far = _mm_set_epi64x((long long)K.far_lo, (long long)K.far_hi);
+    const __m128i near = _mm_set_epi64x((long long)K.near_lo, (long long)K.near_hi);
+    auto at = [](const uint8_t* q) { return reinterpret_cast<const __m128i*>(q); };
+    // four registers, 64 bytes a round; the start value joins the first bits
+    __m128i x0 = _mm_xor_si128(_mm_loadu_si128(at(p)), _mm_cvtsi32_si128((int)c));
+    __m128i x1 = _mm_loadu_si128(at(p + 16)), x2 = _mm_loadu_si128(at(p + 32)), x3 = _mm_loadu_si128(at(p + 48));
+    for (p += 64, n -= 64; n >= 64; p += 64, n -= 64) {
+        x0 = crc_fold(x0, far, _mm_loadu_si128(at(p)));
+        x1 = crc_fold(x1, far, _mm_loadu_si128(at(p + 16)));
+        x2 = crc_fold(x2, far, _mm_loadu_si128(at(p + 32)));
+        x3 = crc_fold(x3, far, _mm_loadu_si128(at(p + 48)));
+    }
+    x1 = crc_fold(x0, near, x1);
+    x2 = crc_fold(x1, near, x2);
+    x3 = crc_fold(x2, near, x3);
+    for (; n >= 16; p += 16, n -= 16) x3 = crc_fold(x3, near, _mm_loadu_si128(at(p)));
+    uint8_t rest[16];
+    _mm_storeu_si128(reinterpret_cast<__m128i*>(rest), x3);
+    return crc_bytes(crc_bytes(0, rest, 16), p, n);
+}
+#endif
+
+}  // namespace
+
+uint32_t crc32_update(uint32_t crc, const uint8_t* p, size_t n) {
+#if defined(__x86_64__)
+    static const bool clmul = __builtin_cpu_supports("pclmul") != 0;
+    if (clmul && n >= 64) return ~crc_clmul(~crc, p, n);
+#endif
+    return ~crc_bytes(~crc, p, n);
 }
 
 bool kraft_ok(const uint8_t* len, int nsym) {

@@ -260,12 +260,13 @@ void pool_free(sz_ctx* c, void* p) {
 }
 
 
+constexpr size_t kPinnedLeast = (size_t)1 << 20;   // bytes of a context's pinned staging, at least
 sz_status pinned_reserve(sz_ctx* c, size_t bytes) {
     if (c->pinned_bytes >= bytes) return SZ_OK;
     if (c->pinned) (void)hipHostFree(c->pinned);
     c->pinned = nullptr;
     c->pinned_bytes = 0;
-    size_t nb = std::max(bytes, (size_t)1 << 20);
+    size_t nb = std::max(bytes, kPinnedLeast);
     HIP_TRY(c, hipHostMalloc(&c->pinned, nb, hipHostMallocDefault));
     c->pinned_bytes = nb;
     return SZ_OK;
@@ -2116,30 +2117,42 @@ sz_status sz_serialize(sz_ctx* c, const sz_result* r, void* dst, uint64_t cap, u
     if (!dst) return fail(c, SZ_ERR_INVALID_ARG, "null destination");
     HIP_TRY(c, hipSetDevice(c->device));
     uint8_t* out = static_cast<uint8_t*>(dst);
-    std::memset(out, 0, total);
-    uint8_t* h = out;
-    make_header(r, R, h);
     struct Sec {
         const void* src;
         uint64_t bytes;
     } secs[6] = {{r->anchors, r->n_anchors * 4},   {r->code_len, (uint64_t)2 * R->R},
                  {r->chunk_bits, r->n_chunks * 2}, {r->words, r->n_words * 4},
                  {r->outlier_idx, r->n_outliers * 4}, {r->outlier_val, r->n_outliers * 4}};
+    if (words_elided(r, R)) {
+        // the words without their zero words, as the compression built them
+        // on the device: bitmap, then the others
+        if (!R->d_esec) return fail(c, SZ_ERR_INVALID_ARG, "no elided words section");
+        secs[3] = {R->d_esec, elided_words(r->n_words, R->nzw) * 4};
+    }
+    // a small blob's sections cross to the pinned staging together and are
+    // waited for once (six waited copies to pageable memory: 75 us more)
+    uint8_t* to = out;
+    if (total <= kPinnedLeast) {
+        sz_status s = pinned_reserve(c, kPinnedLeast);
+        if (s) return s;
+        to = static_cast<uint8_t*>(c->pinned);
+    }
     uint64_t pos = 256;
-    for (int k = 0; k < 6; ++k) {
-        if (k == 3 && words_elided(r, R)) {
-            // the words without their zero words, as the compression built
-            // them on the device: bitmap, then the others
-            if (!R->d_esec) return fail(c, SZ_ERR_INVALID_ARG, "no elided words section");
-            const uint64_t nsec = elided_words(r->n_words, R->nzw);
-            HIP_TRY(c, hipMemcpy(out + pos, R->d_esec, nsec * 4, hipMemcpyDeviceToHost));
-            put32(h, 224 + 4 * k, crc32_update(0, out + pos, nsec * 4));
-            pos += pad8(nsec * 4);
-            continue;
-        }
-        if (secs[k].bytes) HIP_TRY(c, hipMemcpy(out + pos, secs[k].src, secs[k].bytes, hipMemcpyDeviceToHost));
+    for (int k = 0; k < 6; pos += pad8(secs[k].bytes), ++k) {
+        if (!secs[k].bytes) continue;
+        if (to != out) HIP_TRY(c, hipMemcpyAsync(to + pos, secs[k].src, secs[k].bytes, hipMemcpyDeviceToHost, nullptr));
+        else HIP_TRY(c, hipMemcpy(to + pos, secs[k].src, secs[k].bytes, hipMemcpyDeviceToHost));
+    }
+    if (to != out) {
+        HIP_TRY(c, hipStreamSynchronize(nullptr));
+        std::memcpy(out + 256, to + 256, total - 256);
+    }
+    uint8_t* h = out;
+    make_header(r, R, h);
+    pos = 256;
+    for (int k = 0; k < 6; pos += pad8(secs[k].bytes), ++k) {
+        std::memset(out + pos + secs[k].bytes, 0, pad8(secs[k].bytes) - secs[k].bytes);
         put32(h, 224 + 4 * k, crc32_update(0, out + pos, secs[k].bytes));
-        pos += pad8(secs[k].bytes);
     }
     put32(h, 252, crc32_update(0, h, 252));
     return SZ_OK;
