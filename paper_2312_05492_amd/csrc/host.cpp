@@ -584,12 +584,13 @@ void canonical(const uint8_t* len, int nsym, uint32_t* code, uint32_t* first, ui
     for (int s = 0; s < nsym; ++s) code[s] = len[s] ? next[len[s]]++ : 0;
 }
 
-// cbook entries (len << 24 | codeword) and the decode tables
+// cbook entries (the codeword from the top bit on, its length in the low five
+// bits; kLmax = 24 leaves them free) and the decode tables
 void build_tables(const uint8_t* len, int nsym, uint32_t* cbook, uint32_t* dtab) {
     std::vector<uint32_t> code(nsym);
     uint32_t first[kLmax + 2] = {0}, count[kLmax + 2] = {0};
     canonical(len, nsym, code.data(), first, count);
-    for (int s = 0; s < nsym; ++s) cbook[s] = ((uint32_t)len[s] << 24) | code[s];
+    for (int s = 0; s < nsym; ++s) cbook[s] = len[s] ? code[s] << (32 - len[s]) | (uint32_t)len[s] : 0u;
     std::memset(dtab, 0, sizeof(uint32_t) * dtab_words(nsym));
     uint16_t* lut = reinterpret_cast<uint16_t*>(dtab);   // little-endian u16 view
     for (int s = 0; s < nsym; ++s) {

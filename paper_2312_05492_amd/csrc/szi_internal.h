@@ -48,7 +48,7 @@ struct FieldDesc {
     float* anchors;
     uint32_t* hist;        // 2R bins
     // Huffman encode/decode
-    const uint32_t* cbook; // per symbol: len << 24 | codeword
+    const uint32_t* cbook; // per symbol: codeword << (32 - len) | len (0 without a code)
     uint32_t* words;
     uint16_t* chunk_bits;
     uint32_t* outlier_idx;
