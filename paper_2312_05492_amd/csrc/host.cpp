@@ -1233,15 +1233,16 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
     }
     // Huffman encode layout.  The encode kernels are specialised on the
     // chunk size, so the fields are ordered by chunk size into contiguous
-    // groups; each group runs stats -> block scan -> encode over blocks of
-    // kEncBlockChunks chunks (blocks never straddle fields).
+    // groups; each group runs stats -> encode -> elision over blocks of
+    // ec chunks (blocks never straddle fields).
     std::vector<uint32_t> hord(nf);
     for (uint32_t k = 0; k < nf; ++k) hord[k] = k;
     std::stable_sort(hord.begin(), hord.end(),
                      [&](uint32_t x, uint32_t y) { return fds[x].chunk < fds[y].chunk; });
+    const int ec = enc_block_chunks(total_chunks);
     std::vector<uint64_t> hboff(nf + 1, 0);   // global block prefix in hord order
     for (uint32_t j = 0; j < nf; ++j)
-        hboff[j + 1] = hboff[j] + (fds[hord[j]].nchunks + kEncBlockChunks - 1) / kEncBlockChunks;
+        hboff[j + 1] = hboff[j] + (fds[hord[j]].nchunks + (uint64_t)ec - 1) / (uint64_t)ec;
     struct Group {
         uint32_t fs, fe;   // field slice in hord order
     };
@@ -1252,30 +1253,29 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         else
             groups.back().fe = j + 1;
     const uint64_t total_blocks = hboff[nf];
-    // per group: block prefix (group-local) and offsets with one closing slot
-    std::vector<uint64_t> gboff;            // concatenated group-local prefixes
-    std::vector<uint64_t> gboff_at(groups.size()), goff_at(groups.size());
+    std::vector<uint64_t> gboff;            // concatenated group-local block prefixes
+    std::vector<uint64_t> gboff_at(groups.size());
     for (size_t g = 0; g < groups.size(); ++g) {
         gboff_at[g] = gboff.size();
-        goff_at[g] = hboff[groups[g].fs] + g;
         for (uint32_t j = groups[g].fs; j <= groups[g].fe; ++j)
             gboff.push_back(hboff[j] - hboff[groups[g].fs]);
     }
-    const uint64_t nbw = total_blocks + groups.size();
+    // long sums over a field's blocks (a group's start at (b0 >> shift) + fs)
+    const int shift = enc_super_shift(total_blocks);
+    const uint64_t nsup = (total_blocks >> shift) + nf + 1;
 
     // device buffers of the launches: per-call scratch, or in graph mode the
     // arena (descriptors and offsets staged from its pinned mirror)
     FieldDesc *d_fd, *d_hfd;
     FieldPlan* d_plan;
     float *d_pmin, *d_pmax;
-    uint32_t *d_pbad, *d_hist = nullptr, *d_bnz, *d_ecnt;
-    unsigned long long* d_fnz;
-    ElideField* d_ef;
-    uint64_t *d_etoff, *d_eoff;
+    uint32_t *d_pbad, *d_hist = nullptr;
+    unsigned long long* d_tot;
+    EncSums d_sums;
     char* d_scr = nullptr;   // the plain calls' scratch block
     const bool many = !graphs && nf >= 2;   // batch: gathered histograms, scattered tables
-    uint64_t *d_items, *d_gboff, *d_bwoff, *d_booff;
-    uint32_t *d_cwords, *d_couts, *d_bw, *d_bo;
+    uint64_t *d_items, *d_gboff;
+    uint32_t *d_cwords, *d_couts;
     const size_t hstride = 2 * (size_t)max_R;   // graph mode: histogram k at d_hist + k * hstride
     Layout L;
     const size_t o_fd = L.take<FieldDesc>(nf), o_items = L.take<uint64_t>(items.size());
@@ -1285,24 +1285,16 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
     const size_t o_pmax = L.take<float>((size_t)nf * kRangeBlocks);
     const size_t o_pbad = L.take<uint32_t>((size_t)nf * kRangeBlocks);
     const size_t o_hfd = L.take<FieldDesc>(nf), o_gboff = L.take<uint64_t>(gboff.size());
-    const size_t o_ef = L.take<ElideField>(nf), o_etoff = L.take<uint64_t>(nf + 1);
     const size_t end2 = L.off;
     const size_t o_cwords = L.take<uint32_t>(std::max<uint64_t>(total_chunks, 1));
     const size_t o_couts = L.take<uint32_t>(std::max<uint64_t>(total_chunks, 1));
-    const size_t o_bw = L.take<uint32_t>(std::max<uint64_t>(total_blocks, 1));
-    const size_t o_bo = L.take<uint32_t>(std::max<uint64_t>(total_blocks, 1));
-    const size_t o_bwoff = L.take<uint64_t>(nbw), o_booff = L.take<uint64_t>(nbw);
-    const size_t o_bnz = L.take<uint32_t>(std::max<uint64_t>(total_blocks, 1));
-    const size_t o_fnz = L.take<unsigned long long>(nf);
-    // zero-word elision: tiles of every field's words at their largest, of
-    // a size chosen from that bound
-    uint64_t ewords_max = 0;
-    for (uint32_t k = 0; k < nf; ++k) ewords_max += fds[k].npts * kLmax / 32 + fds[k].nchunks + 1;
-    const uint64_t etw = elide_tile_words(ewords_max);
-    uint64_t etiles_max = 0;
-    for (uint32_t k = 0; k < nf; ++k)
-        etiles_max += (fds[k].npts * kLmax / 32 + fds[k].nchunks + 1) / etw + 1;
-    const size_t o_ecnt = L.take<uint32_t>(etiles_max), o_eoff = L.take<uint64_t>(etiles_max + 1);
+    const size_t nblk = std::max<uint64_t>(total_blocks, 1);
+    const size_t o_bw = L.take<uint32_t>(nblk), o_bo = L.take<uint32_t>(nblk);
+    const size_t o_bnz = L.take<uint32_t>(nblk), o_woff = L.take<uint32_t>(nblk);
+    const size_t o_tot = L.take<unsigned long long>(2 * (size_t)nf);
+    // cleared by the plan kernel: the long sums
+    const size_t o_sup = L.take<uint32_t>(2 * (size_t)kSuperLine * nsup);
+    const uint64_t nzero = 2 * (uint64_t)kSuperLine * nsup;
     // host staging in pinned memory (copies from it are asynchronous): the
     // arena's layout, then each field's code lengths, codebook and decode
     // tables
@@ -1312,6 +1304,12 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         const size_t nsym = 2 * (size_t)fds[k].R;
         o_cb[k + 1] = o_cb[k] + ((tables_bytes((int)nsym) + 255) & ~(size_t)255);
     }
+    auto set_sums = [&](char* d) {
+        auto at = [&](size_t o) { return reinterpret_cast<uint32_t*>(d + o); };
+        d_tot = reinterpret_cast<unsigned long long*>(d + o_tot);
+        d_sums = EncSums{at(o_bw), at(o_bo), at(o_bnz), at(o_woff), at(o_sup),
+                         at(o_sup) + (size_t)kSuperLine * nsup, shift};
+    };
     char* hs;   // the staging base
     if (graphs) {
         if ((s = arena_reserve(c, o_cb[nf]))) return s;
@@ -1333,16 +1331,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         d_gboff = reinterpret_cast<uint64_t*>(d + o_gboff);
         d_cwords = reinterpret_cast<uint32_t*>(d + o_cwords);
         d_couts = reinterpret_cast<uint32_t*>(d + o_couts);
-        d_bw = reinterpret_cast<uint32_t*>(d + o_bw);
-        d_bo = reinterpret_cast<uint32_t*>(d + o_bo);
-        d_bwoff = reinterpret_cast<uint64_t*>(d + o_bwoff);
-        d_booff = reinterpret_cast<uint64_t*>(d + o_booff);
-        d_bnz = reinterpret_cast<uint32_t*>(d + o_bnz);
-        d_ef = reinterpret_cast<ElideField*>(d + o_ef);
-        d_etoff = reinterpret_cast<uint64_t*>(d + o_etoff);
-        d_ecnt = reinterpret_cast<uint32_t*>(d + o_ecnt);
-        d_eoff = reinterpret_cast<uint64_t*>(d + o_eoff);
-        d_fnz = reinterpret_cast<unsigned long long*>(d + o_fnz);
+        set_sums(d);
         for (uint32_t k = 0; k < nf; ++k) fds[k].hist = d_hist + k * hstride;
     } else {
         // one scratch block in the arena's layout, so that the staged
@@ -1362,19 +1351,9 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         d_gboff = reinterpret_cast<uint64_t*>(d + o_gboff);
         d_cwords = reinterpret_cast<uint32_t*>(d + o_cwords);
         d_couts = reinterpret_cast<uint32_t*>(d + o_couts);
-        d_bw = reinterpret_cast<uint32_t*>(d + o_bw);
-        d_bo = reinterpret_cast<uint32_t*>(d + o_bo);
-        d_bwoff = reinterpret_cast<uint64_t*>(d + o_bwoff);
-        d_booff = reinterpret_cast<uint64_t*>(d + o_booff);
-        d_bnz = reinterpret_cast<uint32_t*>(d + o_bnz);
-        d_ef = reinterpret_cast<ElideField*>(d + o_ef);
-        d_etoff = reinterpret_cast<uint64_t*>(d + o_etoff);
-        d_ecnt = reinterpret_cast<uint32_t*>(d + o_ecnt);
-        d_eoff = reinterpret_cast<uint64_t*>(d + o_eoff);
-        d_fnz = reinterpret_cast<unsigned long long*>(d + o_fnz);
+        set_sums(d);
     }
-    // the offsets and per-block counts read back at the end, one region
-    const size_t o_back = o_bwoff, n_back = o_bnz + sizeof(uint32_t) * total_blocks - o_bwoff;
+    const size_t n_tot = sizeof(unsigned long long) * 2 * nf;   // read back at the end
 
     // part 1: range, profile, plan (which also zeroes the histograms),
     // interpolation (with histogram)
@@ -1385,7 +1364,8 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         }
         {
             STAGE(c, SZ_STAGE_PLAN, q);
-            HIP_TRY(c, launch_plan(d_fd, d_plan, (int)nf, d_pmin, d_pmax, d_pbad, q));
+            HIP_TRY(c, launch_plan(d_fd, d_plan, (int)nf, d_pmin, d_pmax, d_pbad,
+                                   d_sums.sup, nzero, q));
         }
         uint32_t base = 0;
         for (int gi = 0; gi < kGroups; ++gi) {
@@ -1433,7 +1413,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         const std::vector<uint64_t> sig = {nf, nitems[0], nitems[1], nitems[2], nitems[3],
                                            grp[0].size(), grp[1].size(), grp[2].size(),
                                            (uint64_t)max_R, (uint64_t)s3.per_cu, (uint64_t)s2.variant,
-                                           (uint64_t)s2.per_cu, L.off, gen_block};
+                                           (uint64_t)s2.per_cu, L.off, gen_block, o_sup, nzero};
         char* d = static_cast<char*>(c->arena);
         s = graph_run(c, 1, sig, o_fd, end1 - o_fd, st, [&](hipStream_t q) -> sz_status {
             sz_status r = enqueue1(q);
@@ -1582,62 +1562,38 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         for (uint32_t j = 0; j < nf; ++j) {
             hfd[j] = fds[hord[j]];
             hfd[j].chunk_base = cb;
-            hfd[j].nzw = d_fnz + j;
+            hfd[j].tot = d_tot + 2 * j;
+            hfd[j].esec = ri(&res[perm[hord[j]]])->d_esec;
             cb += hfd[j].nchunks;
         }
     }
-    // the elision's fields (encode order): words, section, the device word
-    // offsets that bound them; tiles of each field's word capacity
-    std::vector<ElideField> ef(nf);
-    std::vector<uint64_t> etoff(nf + 1, 0);
-    for (size_t g = 0; g < groups.size(); ++g)
-        for (uint32_t j = groups[g].fs; j < groups[g].fe; ++j) {
-            const uint64_t lo = gboff[gboff_at[g] + (j - groups[g].fs)];
-            const uint64_t hi = gboff[gboff_at[g] + (j - groups[g].fs) + 1];
-            ef[j].words = hfd[j].words;
-            ef[j].sec = ri(&res[perm[hord[j]]])->d_esec;
-            ef[j].wbeg = d_bwoff + goff_at[g] + lo;
-            ef[j].wend = d_bwoff + goff_at[g] + hi;
-            ef[j].nzw = d_fnz + j;
-            ef[j].nw = 0;
-        }
-    for (uint32_t j = 0; j < nf; ++j)
-        etoff[j + 1] = etoff[j] + (hfd[j].words_cap + etw - 1) / etw;
-    const uint64_t etiles = etoff[nf];
-    if (etiles > etiles_max) return fail(c, SZ_ERR_DEVICE, "elision tiles exceed their bound");
-    // part 2: Huffman stats, block scans, encode with outlier compaction,
+    // part 2: Huffman stats, encode with outlier compaction,
     // zero-word elision
     auto enqueue2 = [&](hipStream_t q) -> sz_status {
         for (size_t g = 0; g < groups.size(); ++g) {
             const uint32_t fs = groups[g].fs, nfg = groups[g].fe - groups[g].fs;
             const uint64_t b0 = hboff[fs], nb = hboff[groups[g].fe] - b0;
+            const uint64_t s0 = (b0 >> shift) + fs;
             const int chunk = hfd[fs].chunk;
+            const EncSums es{d_sums.words + b0, d_sums.outs + b0, d_sums.nz + b0, d_sums.woff + b0,
+                             d_sums.sup + s0 * kSuperLine, d_sums.supnz + s0 * kSuperLine, shift};
             {
                 STAGE(c, SZ_STAGE_HUFF_STATS, q);
-                HIP_TRY(c, launch_huff_stats(d_hfd + fs, (int)nfg, d_gboff + gboff_at[g], nb, chunk,
-                                             d_cwords, d_couts, d_bw + b0, d_bo + b0, 2 * max_R, q));
-            }
-            {
-                STAGE(c, SZ_STAGE_SCAN, q);
-                HIP_TRY(c, launch_scan_blocks(d_bw + b0, d_bo + b0, nb, d_bwoff + goff_at[g],
-                                              d_booff + goff_at[g], q));
+                HIP_TRY(c, launch_huff_stats(d_hfd + fs, (int)nfg, d_gboff + gboff_at[g], nb, chunk, ec,
+                                             d_cwords, d_couts, es, 2 * max_R, q));
             }
             {
                 STAGE(c, SZ_STAGE_ENCODE, q);
-                HIP_TRY(c, launch_huff_encode(d_hfd + fs, (int)nfg, d_gboff + gboff_at[g], nb, chunk,
-                                              d_cwords, d_couts, d_bwoff + goff_at[g],
-                                              d_booff + goff_at[g], d_bnz + b0, 2 * max_R, q));
+                HIP_TRY(c, launch_huff_encode(d_hfd + fs, (int)nfg, d_gboff + gboff_at[g], nb, chunk, ec,
+                                              d_cwords, d_couts, es, 2 * max_R, q));
             }
-        }
-        {
             STAGE(c, SZ_STAGE_ELIDE, q);
-            HIP_TRY(c, launch_elide(d_ef, (int)nf, d_etoff, etiles, etw, d_ecnt, d_eoff, 0, q));
+            HIP_TRY(c, launch_elide(d_hfd + fs, (int)nfg, d_gboff + gboff_at[g], nb, es, q));
         }
         return SZ_OK;
     };
-    // sync 2: block word offsets and non-zero word counts (small) to the host
-    std::vector<uint64_t> bwoff(nbw);
-    std::vector<uint32_t> bnz(std::max<uint64_t>(total_blocks, 1));
+    // sync 2: the fields' words and non-zero words to the host
+    std::vector<unsigned long long> tot(2 * (size_t)nf);
     // with given code books, after the end: the plans and, where a field has
     // more outliers than its guessed lists hold, exact lists and the encode
     // again (eagerly, on the caller's stream)
@@ -1667,12 +1623,12 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         if (again) {
             std::memcpy(hs + o_hfd, hfd.data(), sizeof(FieldDesc) * nf);
             HIP_TRY(c, hipMemcpyAsync(d_hfd, hs + o_hfd, sizeof(FieldDesc) * nf, hipMemcpyHostToDevice, q));
+            HIP_TRY(c, launch_fill_u32(d_sums.sup, nzero, 0u, q));
             sz_status r = enqueue2(q);
             if (r) return r;
-            HIP_TRY(c, hipMemcpyAsync(hs + o_back, d_bwoff, n_back, hipMemcpyDeviceToHost, q));
+            HIP_TRY(c, hipMemcpyAsync(hs + o_tot, d_tot, n_tot, hipMemcpyDeviceToHost, q));
             HIP_TRY(c, hipStreamSynchronize(q));
-            std::memcpy(bwoff.data(), hs + o_bwoff, sizeof(uint64_t) * nbw);
-            std::memcpy(bnz.data(), hs + o_bnz, sizeof(uint32_t) * total_blocks);
+            std::memcpy(tot.data(), hs + o_tot, n_tot);
         }
         return SZ_OK;
     };
@@ -1681,10 +1637,8 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         char* d = static_cast<char*>(c->arena);
         std::memcpy(h + o_hfd, hfd.data(), sizeof(FieldDesc) * nf);
         std::memcpy(h + o_gboff, gboff.data(), sizeof(uint64_t) * gboff.size());
-        std::memcpy(h + o_ef, ef.data(), sizeof(ElideField) * nf);
-        std::memcpy(h + o_etoff, etoff.data(), sizeof(uint64_t) * (nf + 1));
         std::vector<uint64_t> sig = {nf, groups.size(), total_blocks, total_chunks, (uint64_t)max_R, L.off,
-                                     etiles};
+                                     o_tot, o_sup, nsup};
         for (size_t g = 0; g < groups.size(); ++g) {
             sig.push_back(groups[g].fs);
             sig.push_back(groups[g].fe);
@@ -1695,17 +1649,13 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         s = graph_run(c, 2, sig, o_hfd, end2 - o_hfd, st, [&](hipStream_t q) -> sz_status {
             sz_status r = enqueue2(q);
             if (r) return r;
-            HIP_TRY(c, hipMemcpyAsync(h + o_bwoff, d + o_bwoff, sizeof(uint64_t) * nbw,
-                                      hipMemcpyDeviceToHost, q));
-            HIP_TRY(c, hipMemcpyAsync(h + o_bnz, d + o_bnz, sizeof(uint32_t) * total_blocks,
-                                      hipMemcpyDeviceToHost, q));
+            HIP_TRY(c, hipMemcpyAsync(h + o_tot, d + o_tot, n_tot, hipMemcpyDeviceToHost, q));
             return SZ_OK;
         });
         if (s) return s;
         HIP_TRY(c, hipStreamSynchronize(c->gstream));
         HIP_TRY(c, hipStreamSynchronize(st));
-        std::memcpy(bwoff.data(), h + o_bwoff, sizeof(uint64_t) * nbw);
-        std::memcpy(bnz.data(), h + o_bnz, sizeof(uint32_t) * total_blocks);
+        std::memcpy(tot.data(), h + o_tot, n_tot);
         if (given) {
             std::memcpy(plans.data(), h + o_plan, sizeof(FieldPlan) * nf);
             for (uint32_t k = 0; k < nf; ++k)
@@ -1716,17 +1666,14 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
     } else {
         std::memcpy(hs + o_hfd, hfd.data(), sizeof(FieldDesc) * nf);
         std::memcpy(hs + o_gboff, gboff.data(), sizeof(uint64_t) * gboff.size());
-        std::memcpy(hs + o_ef, ef.data(), sizeof(ElideField) * nf);
-        std::memcpy(hs + o_etoff, etoff.data(), sizeof(uint64_t) * (nf + 1));
         HIP_TRY(c, hipMemcpyAsync(d_hfd, hs + o_hfd, end2 - o_hfd, hipMemcpyHostToDevice, st));
         if (many) HIP_TRY(c, launch_scatter_tables(d_hfd, (int)nf, reinterpret_cast<const uint8_t*>(d_scr + o_cb[0]), st));
         cb_mark.reset();
         if ((s = enqueue2(st))) return s;
-        HIP_TRY(c, hipMemcpyAsync(hs + o_back, d_bwoff, n_back, hipMemcpyDeviceToHost, st));
+        HIP_TRY(c, hipMemcpyAsync(hs + o_tot, d_tot, n_tot, hipMemcpyDeviceToHost, st));
         if (given && (s = read_plans_hists(st))) return s;
         HIP_TRY(c, hipStreamSynchronize(st));
-        std::memcpy(bwoff.data(), hs + o_bwoff, sizeof(uint64_t) * nbw);
-        std::memcpy(bnz.data(), hs + o_bnz, sizeof(uint32_t) * total_blocks);
+        std::memcpy(tot.data(), hs + o_tot, n_tot);
         if (given) {
             std::memcpy(plans.data(), hs + o_plan, sizeof(FieldPlan) * nf);
             for (uint32_t k = 0; k < nf; ++k)
@@ -1738,18 +1685,14 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
     resolve_marks(c);
     for (size_t g = 0; g < groups.size(); ++g) {
         for (uint32_t j = groups[g].fs; j < groups[g].fe; ++j) {
-            const uint64_t lo = gboff[gboff_at[g] + (j - groups[g].fs)];
-            const uint64_t hi = gboff[gboff_at[g] + (j - groups[g].fs) + 1];
             const uint32_t k = hord[j];
             const uint32_t i = perm[k];
-            res[i].n_words = bwoff[goff_at[g] + hi] - bwoff[goff_at[g] + lo];
+            res[i].n_words = tot[2 * j];
             if (res[i].n_words > fds[k].words_cap)   // sized from the histogram or the largest
                 return fail(c, SZ_ERR_DEVICE, "field %u: %llu Huffman words exceed the %llu sized "
                             "from the histogram", i, (unsigned long long)res[i].n_words,
                             (unsigned long long)fds[k].words_cap);
-            uint64_t nz = 0;   // non-zero words of the field's encode blocks
-            for (uint64_t b = hboff[j]; b < hboff[j + 1]; ++b) nz += bnz[b];
-            ri(&res[i])->nzw = nz;
+            ri(&res[i])->nzw = tot[2 * j + 1];
             if (!words_elided(&res[i], ri(&res[i]))) {   // the section buffer is not needed
                 res_release(c, ri(&res[i]), ri(&res[i])->d_esec);
                 ri(&res[i])->d_esec = nullptr;
@@ -2239,8 +2182,6 @@ sz_status sz_upload(sz_ctx* c, const void* blob, uint64_t bytes, void* stream, s
         ElideField e;
         e.words = r.words;
         e.sec = R->d_esec;
-        e.wbeg = e.wend = nullptr;
-        e.nzw = nullptr;
         e.nw = r.n_words;
         const uint64_t tw = elide_tile_words(r.n_words);
         const uint64_t tiles = (r.n_words + tw - 1) / tw;
@@ -2258,10 +2199,10 @@ sz_status sz_upload(sz_ctx* c, const void* blob, uint64_t bytes, void* stream, s
         hipError_t e3 = hipSuccess;
         if (e1 == hipSuccess && e2 == hipSuccess) {
             STAGE(c, SZ_STAGE_ELIDE, st);
-            e3 = launch_elide(reinterpret_cast<ElideField*>(d + o_e), 1,
-                              reinterpret_cast<uint64_t*>(d + o_t), tiles, tw,
-                              reinterpret_cast<uint32_t*>(d + o_c), reinterpret_cast<uint64_t*>(d + o_o),
-                              1, st);
+            e3 = launch_restore(reinterpret_cast<ElideField*>(d + o_e), 1,
+                                reinterpret_cast<uint64_t*>(d + o_t), tiles, tw,
+                                reinterpret_cast<uint32_t*>(d + o_c), reinterpret_cast<uint64_t*>(d + o_o),
+                                st);
         }
         if (e1 != hipSuccess || e2 != hipSuccess || e3 != hipSuccess) {
             release_result(c, &r);

@@ -1,14 +1,15 @@
 // k_huff.hip -- chunked Huffman encode/decode with fused outlier compaction
 // (Sec. VI-A) on gfx950.
 //
-// Encode: kEncChunks consecutive chunks of one field per workgroup (4 wave64,
+// Encode: up to 32 consecutive chunks of one field per workgroup (4 wave64,
 // one chunk per wave at a time, C/64 consecutive symbols per lane).
 //   k_huff_stats   bit count and outlier count of every chunk; sums per
-//                  workgroup block
-//   k_scan_blocks  exclusive scan of the block sums (one workgroup)
-//   k_huff_encode  chunk offsets = block offset + in-block prefix; packs the
-//                  codewords MSB-first through LDS and writes the outliers
-//                  (index, original value) in ascending index order
+//                  workgroup block and per 64 blocks
+//   k_huff_encode  chunk offsets = sums of the field's earlier blocks +
+//                  in-block prefix; packs the codewords MSB-first through
+//                  LDS and writes the outliers (index, original value) in
+//                  ascending index order; sums of the non-zero words
+//   k_elide        zero-word elision of the words, block by block
 // Decode: kDecChunks chunks per decode block, kSubParts lanes per chunk from
 // the bit offsets of its parts that the encoder records (one lane per chunk
 // without them).
@@ -21,10 +22,45 @@
 
 namespace szi {
 
-constexpr int kEncChunks = 32;
 constexpr int kDecChunks = 256;
-static_assert(kEncChunks == kEncBlockChunks && kDecChunks == kDecBlockChunks,
-              "the host sizes the Huffman grids with the same chunk counts");
+static_assert(kDecChunks == kDecBlockChunks,
+              "the host sizes the decode grid with the same chunk count");
+
+// Sum over the blocks [first, blk) of field f of one number a block or two
+// (b, the second of a line of sup), by the 256 threads of a workgroup; red:
+// 8 words of LDS, with a barrier inside.
+__device__ __forceinline__ void sum_before(const uint32_t* __restrict__ a, const uint32_t* __restrict__ b,
+                                           const uint32_t* __restrict__ sup, int shift, int f,
+                                           uint64_t first, uint64_t blk, uint32_t* red, uint32_t& ra,
+                                           uint32_t& rb) {
+    const uint32_t nsup = (uint32_t)((blk - first) >> shift);
+    const uint64_t sb0 = (first >> shift) + (uint32_t)f;
+    uint32_t xa = 0, xb = 0;
+    for (uint32_t i = threadIdx.x; i < nsup; i += 256) {
+        xa += gp(sup)[(sb0 + i) * kSuperLine];
+        if (b) xb += gp(sup)[(sb0 + i) * kSuperLine + 1];
+    }
+    const uint64_t i = first + ((uint64_t)nsup << shift) + threadIdx.x;   // fewer than 256 left
+    if (i < blk) {
+        xa += gp(a)[i];
+        if (b) xb += gp(b)[i];
+    }
+    xa = wave_sum(xa);
+    if (b) xb = wave_sum(xb);
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = xa;
+        red[4 + (threadIdx.x >> 6)] = xb;
+    }
+    __syncthreads();
+    ra = red[0] + red[1] + red[2] + red[3];
+    rb = red[4] + red[5] + red[6] + red[7];
+}
+// the word of the long sum that block blk of field f, [first, end), belongs
+// to, or -1 where the field ends before it is complete
+__device__ __forceinline__ int64_t super_of(int shift, int f, uint64_t first, uint64_t end, uint64_t blk) {
+    const uint64_t k = (blk - first) >> shift;
+    return k < ((end - first) >> shift) ? (int64_t)(((first >> shift) + (uint32_t)f + k) * kSuperLine) : -1;
+}
 
 // symbols [s0, s0 + per) of the code array (all inside the field)
 template <int PER>
@@ -67,28 +103,26 @@ __device__ __forceinline__ void lane_syms(const FieldDesc& fd, uint64_t ch, int 
 
 template <int PER>
 __global__ __launch_bounds__(256) void k_huff_stats(const FieldDesc* __restrict__ F, int nfields,
-                                                    const uint64_t* __restrict__ boff,
+                                                    const uint64_t* __restrict__ boff, int ec,
                                                     uint32_t* cwords, uint32_t* couts,
-                                                    uint32_t* bw, uint32_t* bo) {
+                                                    EncSums sums) {
     // the last blocks first: the codes written last may still lie in the
     // memory-side cache, and the encode then starts on those read last here
     // (512^3: 58 -> 56 us, encode 95 -> 91)
     const uint32_t blk = gridDim.x - 1u - blockIdx.x;
     extern __shared__ uint32_t cb[];
-    __shared__ uint32_t sw[kEncChunks], so[kEncChunks];
+    __shared__ uint32_t sw[kEncBlockMax], so[kEncBlockMax];
     const int f = block_field(boff, nfields, blk);
     const FieldDesc& fd = F[f];
     const int nsym = 2 * fd.R;
-    // the field's non-zero word count, which its encode blocks add to
-    if (threadIdx.x == 0 && blk == boff[f] && fd.nzw) *gp(fd.nzw) = 0ull;
     // per symbol its length, with 2^16 added for an outlier (code 0): the sum
     // over a chunk then holds its bits (< 2^16) and outliers (<= 2048)
     for (int s = threadIdx.x; s < nsym; s += blockDim.x)
         cb[s] = (gp(fd.cbook)[s] & 31u) + (s == 0 ? 0x10000u : 0u);
     __syncthreads();
-    const uint64_t first = (blk - boff[f]) * kEncChunks;
+    const uint64_t first = (blk - boff[f]) * (uint32_t)ec;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int j = wave; j < kEncChunks; j += 4) {
+    for (int j = wave; j < ec; j += 4) {
         const uint64_t ch = first + j;
         uint32_t words = 0, zeros = 0;
         if (ch < fd.nchunks) {   // uniform across the wave
@@ -123,25 +157,29 @@ __global__ __launch_bounds__(256) void k_huff_stats(const FieldDesc* __restrict_
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t a = 0, b = 0;
-        for (int j = 0; j < kEncChunks; ++j) {
+        for (int j = 0; j < ec; ++j) {
             a += sw[j];
             b += so[j];
         }
-        bw[blk] = a;
-        bo[blk] = b;
+        sums.words[blk] = a;
+        sums.outs[blk] = b;
+        const int64_t sb = super_of(sums.shift, f, boff[f], boff[f + 1], blk);
+        if (sb >= 0)   // words and outliers in one 64-bit addition (neither sum reaches 2^32)
+            __hip_atomic_fetch_add(reinterpret_cast<SZI_G unsigned long long*>(gp(sums.sup) + sb),
+                                   (unsigned long long)a | (unsigned long long)b << 32, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
     }
 }
 
-// Exclusive scan of up to two u32 arrays of length n into u64 offsets; one
+// Exclusive scan of a u32 array of length n into u64 offsets; one
 // workgroup of 1024 threads, a contiguous run per thread: run sums, wave
 // scans, the 16 wave totals through LDS (one barrier), then the run's
 // offsets.  off[n] receives the total.  LONG = false takes runs of at
 // most kRun (n <= 16384) in registers; LONG = true, longer runs kRun
 // elements a round (the launchers choose by n).
 template <bool LONG>
-__global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict__ a,
-                                                      const uint32_t* __restrict__ b, uint64_t n,
-                                                      uint64_t* aoff, uint64_t* boff) {
+__global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict__ a, uint64_t n,
+                                                      uint64_t* aoff) {
     const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
     const uint64_t per = (n + 1023) / 1024;
     const uint64_t beg = (uint64_t)t * per < n ? (uint64_t)t * per : n;
@@ -149,19 +187,17 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict
     // runs of up to kRun elements sit in registers, all loads issued at once
     constexpr int kRun = 16;
     const bool regs = !LONG && per <= (uint64_t)kRun;   // LONG: runs of more than kRun
-    uint32_t va[kRun], vb[kRun];
-    uint64_t sa = 0, sb = 0;
+    uint32_t va[kRun];
+    uint64_t sa = 0;
     if (regs) {
 #pragma unroll
         for (int k = 0; k < kRun; ++k) {
             const uint64_t i = beg + k;
             va[k] = i < end ? a[i] : 0u;
-            vb[k] = (b && i < end) ? b[i] : 0u;
         }
 #pragma unroll
         for (int k = 0; k < kRun; ++k) {
             sa += va[k];
-            sb += vb[k];
         }
     } else if (LONG) {
         // longer runs (the LONG instance): kRun elements a round, their
@@ -171,44 +207,37 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict
             for (int k = 0; k < kRun; ++k) {
                 const uint64_t i = i0 + k;
                 va[k] = i < end ? a[i] : 0u;
-                vb[k] = (b && i < end) ? b[i] : 0u;
-            }
+                }
 #pragma unroll
             for (int k = 0; k < kRun; ++k) {
                 sa += va[k];
-                sb += vb[k];
-            }
+                }
         }
     }
-    uint64_t xa = sa, xb = sb;   // inclusive scans over the wave's lanes
+    uint64_t xa = sa;   // inclusive scans over the wave's lanes
     for (int o = 1; o < 64; o <<= 1) {
-        const uint64_t ya = __shfl_up(xa, o), yb = __shfl_up(xb, o);
+        const uint64_t ya = __shfl_up(xa, o);
         if (lane >= o) {
             xa += ya;
-            xb += yb;
         }
     }
-    __shared__ uint64_t wa[16], wb[16];
+    __shared__ uint64_t wa[16];
     if (lane == 63) {
         wa[wave] = xa;
-        wb[wave] = xb;
     }
     __syncthreads();
     for (int k = 0; k < wave; ++k) {
         xa += wa[k];
-        xb += wb[k];
     }
-    uint64_t ra = xa - sa, rb = xb - sb;
+    uint64_t ra = xa - sa;
     if (regs) {
 #pragma unroll
         for (int k = 0; k < kRun; ++k) {
             const uint64_t i = beg + k;
             if (i < end) {
                 aoff[i] = ra;
-                if (b) boff[i] = rb;
             }
             ra += va[k];
-            rb += vb[k];
         }
     } else if (LONG) {
         for (uint64_t i0 = beg; i0 < end; i0 += kRun) {
@@ -216,23 +245,19 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict
             for (int k = 0; k < kRun; ++k) {
                 const uint64_t i = i0 + k;
                 va[k] = i < end ? a[i] : 0u;
-                vb[k] = (b && i < end) ? b[i] : 0u;
-            }
+                }
 #pragma unroll
             for (int k = 0; k < kRun; ++k) {
                 const uint64_t i = i0 + k;
                 if (i < end) {
                     aoff[i] = ra;
-                    if (b) boff[i] = rb;
-                }
+                    }
                 ra += va[k];
-                rb += vb[k];
-            }
+                }
         }
     }
     if (t == 1023) {
         aoff[n] = xa;
-        if (b) boff[n] = xb;
     }
 }
 
@@ -257,14 +282,12 @@ __host__ __device__ constexpr int enc_chunk_words(int chunk) { return (chunk * k
 // loading the next chunk ahead, were both slower.)
 template <int PER>
 __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict__ F, int nfields,
-                                                     const uint64_t* __restrict__ boff,
+                                                     const uint64_t* __restrict__ boff, int ec,
                                                      const uint32_t* __restrict__ cwords,
                                                      const uint32_t* __restrict__ couts,
-                                                     const uint64_t* __restrict__ bwoff,
-                                                     const uint64_t* __restrict__ booff,
-                                                     uint32_t* __restrict__ bnz) {
+                                                     EncSums sums) {
     extern __shared__ uint32_t smem[];
-    __shared__ uint32_t wnz[4];
+    __shared__ uint32_t wnz[4], red[8];
     constexpr int C = PER * 64;
     constexpr int MCW = enc_chunk_words(C);
     const int f = block_field(boff, nfields, blockIdx.x);
@@ -275,22 +298,23 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
     uint32_t* wbuf = smem + nsym + wave * MCW;
     for (int s = threadIdx.x; s < nsym; s += blockDim.x) cb[s] = gp(fd.cbook)[s];
     const uint64_t blk_local = blockIdx.x - boff[f];
-    const uint64_t first = blk_local * kEncChunks;
-    // this field's sections start at 0: subtract the offsets of its first block
-    const uint64_t wbase = bwoff[boff[f]], obase = booff[boff[f]];
-    const uint64_t bw0 = bwoff[blockIdx.x] - wbase, bo0 = booff[blockIdx.x] - obase;
+    const uint64_t first = blk_local * (uint32_t)ec;
     // in-block exclusive prefix of the chunk word and outlier counts
     uint32_t cw = 0, co = 0;
-    if (lane < kEncChunks && first + lane < fd.nchunks) {
+    if (lane < ec && first + lane < fd.nchunks) {
         cw = cwords[fd.chunk_base + first + lane];
         co = couts[fd.chunk_base + first + lane];
     }
     uint32_t tw, to;
     const uint32_t pw = wave_excl_scan(cw, &tw);
     const uint32_t po = wave_excl_scan(co, &to);
-    __syncthreads();   // the code book is in LDS
+    // words and outliers of the field's earlier blocks; the barrier inside
+    // also completes the code book in LDS
+    uint32_t bw0, bo0;
+    sum_before(sums.words, sums.outs, sums.sup, sums.shift, f, boff[f], blockIdx.x, red, bw0, bo0);
+    if (threadIdx.x == 0) sums.woff[blockIdx.x] = bw0;
     uint32_t nz = 0;   // non-zero words written, for the zero-word elision of the blob
-    for (int j = wave; j < kEncChunks; j += 4) {
+    for (int j = wave; j < ec; j += 4) {
         const uint64_t ch = first + j;
         if (ch >= fd.nchunks) break;   // uniform across the wave
         uint32_t sym[PER], e[PER];
@@ -344,7 +368,7 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
         }
         if (tbz >> 16) {   // uniform: outliers in this chunk
             uint32_t zo = pbz >> 16;
-            const uint64_t oo = bo0 + (uint32_t)__builtin_amdgcn_readlane((int)po, j);
+            const uint64_t oo = (uint64_t)bo0 + (uint32_t)__builtin_amdgcn_readlane((int)po, j);
             const uint64_t s0 = ch * (uint64_t)C + (uint64_t)lane * PER;
 #pragma unroll
             for (int k = 0; k < PER; ++k) {
@@ -358,7 +382,7 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
             }
         }
         wave_lds_sync();
-        const uint64_t ow = bw0 + (uint32_t)__builtin_amdgcn_readlane((int)pw, j);   // j is uniform
+        const uint64_t ow = (uint64_t)bw0 + (uint32_t)__builtin_amdgcn_readlane((int)pw, j);   // j is uniform
         for (uint32_t k = lane; k < nw; k += 64) {
             const uint32_t w = wbuf[k];
             nz += w != 0u;
@@ -378,14 +402,15 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
         }
         wave_lds_sync();
     }
-    // one count per block, and one atomic per block for the field's total
+    // one count per block, and one atomic for the long sum it belongs to
     nz = wave_sum(nz);
     if (lane == 0) wnz[wave] = nz;
     __syncthreads();
     if (threadIdx.x == 0) {
         const uint32_t t = wnz[0] + wnz[1] + wnz[2] + wnz[3];
-        bnz[blockIdx.x] = t;
-        if (fd.nzw) atomicAdd(fd.nzw, (unsigned long long)t);
+        sums.nz[blockIdx.x] = t;
+        const int64_t sb = super_of(sums.shift, f, boff[f], boff[f + 1], blockIdx.x);
+        if (sb >= 0) gatomic_add(gp(sums.supnz) + sb, t);
     }
 }
 
@@ -646,119 +671,118 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __r
     }
 }
 
-// ------------------------------------------------------- zero-word elision
-// The de-redundancy step after Huffman coding (taking the place of the
-// closed pass of Sec. VI-B): the words section becomes a bitmap of the
-// non-zero words (bit k % 32 of bitmap word k / 32 for word k) followed by
-// those words in order.  Work is split into tiles of tw words (8192, or 2048
-// for calls with few words), one wave per tile: a count pass, an exclusive
-// scan of the tile counts over all fields (k_scan_blocks), and a write pass.  The restore (upload of an
-// elided blob) runs the same tiling backwards: counts of set bits, scan,
-// then each tile's words in place.
-static_assert(kElideTileWords % 2048 == 0 && kElideTileSmall % 2048 == 0,
-              "a tile is whole rounds of 32 ballots of 64 words");
-
-__device__ __forceinline__ uint64_t elide_words(const ElideField& e) {
-    return e.wbeg ? *e.wend - *e.wbeg : e.nw;
-}
-
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
 // restore = 0: non-zero words per tile of the words; 1: set bits per tile
 // of the bitmap (the tile's 64 bitmap words)
-template <int RESTORE>
-__global__ __launch_bounds__(256) void k_elide_count(const ElideField* __restrict__ E, int nf,
-                                                     const uint64_t* __restrict__ toff,
-                                                     uint64_t ntiles, uint64_t tw, uint32_t* cnt) {
-    // the wave's tile, uniform (so the field record and its pointers sit in
-    // scalar registers, loaded once, not again before every word)
-    const uint64_t tile = (uint64_t)blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+// ------------------------------------------------------- zero-word elision
+// The de-redundancy step after Huffman coding (taking the place of the
+// closed pass of Sec. VI-B): the words section becomes a bitmap of the
+// non-zero words (bit k % 32 of bitmap word k / 32 for word k) followed by
+// those words in order.
+//
+// One workgroup per encode block, whose words it elides: the non-zero words
+// before it follow from the encode's sums, each wave counts a quarter of the
+// block's words and then writes them.  Rounds of 64 words start at multiples
+// of 64; the bitmap word of 32 words is written by the block that holds the
+// first of them.  A field that would not get shorter is left alone from its
+// totals.  (One launch in place of a count, a scan and a write over tiles:
+// 64^3 13 -> 6 us, 512^3 14 -> 7, 24 climate fields 37 -> 24.)
+__global__ __launch_bounds__(256) void k_elide(const FieldDesc* __restrict__ F, int nfields,
+                                               const uint64_t* __restrict__ boff, EncSums sums) {
+    __shared__ uint32_t red[8], cnt[4];
+    const int f = block_field(boff, nfields, blockIdx.x);
+    const FieldDesc& fd = F[f];
+    const uint64_t bf = boff[f], be = boff[f + 1];
+    uint32_t nz, before, none;
+    sum_before(sums.nz, nullptr, sums.supnz, sums.shift, f, bf, be, red, nz, none);
+    const uint64_t nw = (uint64_t)sums.woff[be - 1] + sums.words[be - 1], nbm = (nw + 31) / 32;
+    if (blockIdx.x == be - 1 && threadIdx.x == 0) {
+        fd.tot[0] = nw;
+        fd.tot[1] = nz;
+    }
+    if (nbm + nz >= nw) return;   // uniform: the field keeps its words
+    __syncthreads();
+    sum_before(sums.nz, nullptr, sums.supnz, sums.shift, f, bf, blockIdx.x, red, before, none);
+    const uint64_t w0 = sums.woff[blockIdx.x], w1 = w0 + sums.words[blockIdx.x];
+    const uint64_t base = w0 & ~(uint64_t)63;
+    const uint32_t rounds = (uint32_t)((w1 - base + 63) / 64), each = (rounds + 3) / 4;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const uint32_t lane = threadIdx.x & 63u;
-    if (tile >= ntiles) return;
-    const int f = block_field(toff, nf, tile);
-    const ElideField& e = E[f];
-    const uint64_t nw = elide_words(e);
-    const uint64_t w0 = (tile - toff[f]) * tw;
-    const int rounds = (int)(tw / 2048);
+    const uint32_t r0 = wave * each < rounds ? wave * each : rounds;
+    const uint32_t r1 = r0 + each < rounds ? r0 + each : rounds;
+    const SZI_G uint32_t* words = gp((const uint32_t*)fd.words);
+    constexpr int kIn = 8;   // rounds of loads in flight
     uint32_t n = 0;
-    if (!RESTORE && e.nzw && (nw + 31) / 32 + *gp(e.nzw) >= nw) {
-        // the field keeps its words: nothing to count
-    } else if (RESTORE) {
-        const uint64_t nbm = (nw + 31) / 32;
-        const SZI_G uint32_t* sec = gp(e.sec);
-        for (int j = 0; j < rounds; ++j) {
-            const uint64_t b = w0 / 32 + (uint64_t)j * 64 + lane;
-            n += (uint32_t)__popc(b < nbm ? sec[b] : 0u);
+    for (uint32_t r = r0; r < r1; r += kIn) {
+        uint32_t w[kIn];
+#pragma unroll
+        for (int k = 0; k < kIn; ++k) {   // unconditional loads, held inside the block's words
+            const uint64_t i = base + (uint64_t)(r + k) * 64 + lane;
+            w[k] = words[i < w1 ? i : w1 - 1];
         }
-        for (int o = 32; o > 0; o >>= 1) n += __shfl_xor(n, o);
-    } else {
-        // 32 loads in flight a round: unconditional loads at indices held
-        // inside the words (a predicated load would be waited for at once),
-        // the words past the end then taken as zero
-        const SZI_G uint32_t* words = gp(e.words);
-        const uint64_t last = nw > 0 ? nw - 1 : 0;
-        for (int r = 0; r < rounds && nw > 0; ++r) {
-            uint32_t w[32];
 #pragma unroll
-            for (int it = 0; it < 32; ++it) {
-                const uint64_t i = w0 + (uint64_t)(r * 32 + it) * 64 + lane;
-                w[it] = words[i < nw ? i : last];
-            }
-#pragma unroll
-            for (int it = 0; it < 32; ++it) {
-                const uint64_t i = w0 + (uint64_t)(r * 32 + it) * 64 + lane;
-                w[it] = i < nw ? w[it] : 0u;
-            }
-#pragma unroll
-            for (int it = 0; it < 32; ++it)
-                n += (uint32_t)__popcll(__builtin_amdgcn_ballot_w64(w[it] != 0u));
+        for (int k = 0; k < kIn; ++k) {
+            const uint64_t i = base + (uint64_t)(r + k) * 64 + lane;
+            n += (uint32_t)__popcll(wave_ballot(r + k < r1 && i >= w0 && i < w1 && w[k] != 0u));
         }
     }
-    if (lane == 0) cnt[tile] = n;
-}
-
-// elision: bitmap words and non-zero words of a tile into e.sec, if the
-// field's section is shorter than its words (else nothing is written)
-__global__ __launch_bounds__(256) void k_elide_write(const ElideField* __restrict__ E, int nf,
-                                                     const uint64_t* __restrict__ toff,
-                                                     uint64_t ntiles, uint64_t tw,
-                                                     const uint64_t* __restrict__ off) {
-    // the wave's tile, uniform (so the field record and its pointers sit in
-    // scalar registers, loaded once, not again before every word)
-    const uint64_t tile = (uint64_t)blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const uint32_t lane = threadIdx.x & 63u;
-    if (tile >= ntiles) return;
-    const int f = block_field(toff, nf, tile);
-    const ElideField& e = E[f];
-    const uint64_t nw = elide_words(e), nbm = (nw + 31) / 32;
-    const uint64_t first = off[toff[f]];
-    const uint64_t nz = e.nzw ? (uint64_t)*gp(e.nzw) : off[toff[f + 1]] - first;
-    if (nbm + nz >= nw) return;
-    const uint64_t w0 = (tile - toff[f]) * tw;
-    if (w0 >= nw) return;
-    uint64_t at = nbm + (off[tile] - first);
-    SZI_G uint32_t* sec = gp(e.sec);
-    const SZI_G uint32_t* words = gp(e.words);
-    // rounds of 32 rows of 64 words, each round's loads in flight together
-    for (int r = 0; r < (int)(tw / 2048); ++r) {
-        uint32_t wv[32];
+    if (lane == 0) cnt[wave] = n;
+    __syncthreads();
+    uint64_t at = nbm + before;
+    for (uint32_t k = 0; k < wave; ++k) at += cnt[k];
+    SZI_G uint32_t* sec = gp(fd.esec);
+    for (uint32_t r = r0; r < r1; r += kIn) {
+        uint32_t w[kIn];
 #pragma unroll
-        for (int it = 0; it < 32; ++it) {
-            const uint64_t i = w0 + (uint64_t)(r * 32 + it) * 64 + lane;
-            wv[it] = i < nw ? words[i] : 0u;
+        for (int k = 0; k < kIn; ++k) {   // past the block too, for its last bitmap word
+            const uint64_t i = base + (uint64_t)(r + k) * 64 + lane;
+            w[k] = words[i < nw ? i : nw - 1];
         }
 #pragma unroll
-        for (int it = 0; it < 32; ++it) {
-            const uint64_t i0 = w0 + (uint64_t)(r * 32 + it) * 64;
-            const uint32_t w = wv[it];
-            const uint64_t m = __builtin_amdgcn_ballot_w64(w != 0u);
-            if (lane < 2 && i0 + 32 * lane < nw) sec[i0 / 32 + lane] = (uint32_t)(m >> (32 * lane));
-            if (w) sec[at + lanes_below(m)] = w;
+        for (int k = 0; k < kIn; ++k) {
+            const uint64_t i0 = base + (uint64_t)(r + k) * 64, i = i0 + lane;
+            const bool live = r + k < r1;   // uniform
+            const uint64_t all = wave_ballot(i < nw && w[k] != 0u);
+            const bool mine = live && i >= w0 && i < w1 && w[k] != 0u;
+            const uint64_t m = wave_ballot(mine);
+            const uint64_t b = i0 + 32u * lane;   // lanes 0 and 1: the round's bitmap words
+            if (live && lane < 2u && b >= w0 && b < w1) sec[b / 32] = (uint32_t)(all >> (32u * lane));
+            if (mine) sec[at + lanes_below(m)] = w[k];
             at += (uint64_t)__popcll(m);
         }
     }
+}
+
+// The restore (upload of an elided blob) splits the words into tiles of tw
+// words (8192, or 2048 where there are few), one wave per tile: counts of
+// set bits, an exclusive scan of the tile counts (k_scan_blocks), then each
+// tile's words in place.
+static_assert(kElideTileWords % 2048 == 0 && kElideTileSmall % 2048 == 0,
+              "a tile is whole rounds of 64 bitmap words");
+
+__global__ __launch_bounds__(256) void k_restore_count(const ElideField* __restrict__ E, int nf,
+                                                       const uint64_t* __restrict__ toff,
+                                                       uint64_t ntiles, uint64_t tw, uint32_t* cnt) {
+    // the wave's tile, uniform (so the field record and its pointers sit in
+    // scalar registers, loaded once, not again before every word)
+    const uint64_t tile = (uint64_t)blockIdx.x * 4 + (uint32_t)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const uint32_t lane = threadIdx.x & 63u;
+    if (tile >= ntiles) return;
+    const int f = block_field(toff, nf, tile);
+    const ElideField& e = E[f];
+    const uint64_t nbm = (e.nw + 31) / 32;
+    const uint64_t w0 = (tile - toff[f]) * tw;
+    const SZI_G uint32_t* sec = gp((const uint32_t*)e.sec);
+    uint32_t n = 0;
+    for (int j = 0; j < (int)(tw / 2048); ++j) {
+        const uint64_t b = w0 / 32 + (uint64_t)j * 64 + lane;
+        n += (uint32_t)__popc(b < nbm ? sec[b] : 0u);
+    }
+    n = wave_sum(n);
+    if (lane == 0) cnt[tile] = n;
 }
 
 // restore: the words of a tile from the bitmap and the non-zero words
@@ -773,7 +797,7 @@ __global__ __launch_bounds__(256) void k_restore_write(const ElideField* __restr
     if (tile >= ntiles) return;
     const int f = block_field(toff, nf, tile);
     const ElideField& e = E[f];
-    const uint64_t nw = elide_words(e), nbm = (nw + 31) / 32;
+    const uint64_t nw = e.nw, nbm = (nw + 31) / 32;
     const uint64_t w0 = (tile - toff[f]) * tw;
     if (w0 >= nw) return;
     uint64_t at = nbm + (off[tile] - off[toff[f]]);
@@ -791,63 +815,57 @@ __global__ __launch_bounds__(256) void k_restore_write(const ElideField* __restr
 }
 
 // ------------------------------------------------------- launchers
-hipError_t launch_elide(const ElideField* d_e, int nf, const uint64_t* d_toff, uint64_t ntiles,
-                        uint64_t tw, uint32_t* d_cnt, uint64_t* d_off, int restore, hipStream_t st) {
+hipError_t launch_elide(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
+                        uint64_t nblocks, EncSums sums, hipStream_t st) {
+    if (nblocks == 0) return hipSuccess;
+    hipLaunchKernelGGL(k_elide, dim3((unsigned)nblocks), dim3(256), 0, st, d_fields, nfields, d_boff, sums);
+    return hipGetLastError();
+}
+
+hipError_t launch_restore(const ElideField* d_e, int nf, const uint64_t* d_toff, uint64_t ntiles,
+                          uint64_t tw, uint32_t* d_cnt, uint64_t* d_off, hipStream_t st) {
     if (ntiles == 0) return hipSuccess;
     if (tw == 0 || tw % 2048 != 0) return hipErrorInvalidValue;
     const dim3 g((unsigned)((ntiles + 3) / 4)), b(256);
-    if (restore) hipLaunchKernelGGL(k_elide_count<1>, g, b, 0, st, d_e, nf, d_toff, ntiles, tw, d_cnt);
-    else hipLaunchKernelGGL(k_elide_count<0>, g, b, 0, st, d_e, nf, d_toff, ntiles, tw, d_cnt);
+    hipLaunchKernelGGL(k_restore_count, g, b, 0, st, d_e, nf, d_toff, ntiles, tw, d_cnt);
     if (ntiles > 16 * 1024)
-        hipLaunchKernelGGL(k_scan_blocks<true>, dim3(1), dim3(1024), 0, st, d_cnt,
-                           (const uint32_t*)nullptr, ntiles, d_off, (uint64_t*)nullptr);
+        hipLaunchKernelGGL(k_scan_blocks<true>, dim3(1), dim3(1024), 0, st, d_cnt, ntiles, d_off);
     else
-        hipLaunchKernelGGL(k_scan_blocks<false>, dim3(1), dim3(1024), 0, st, d_cnt,
-                           (const uint32_t*)nullptr, ntiles, d_off, (uint64_t*)nullptr);
-    if (restore) hipLaunchKernelGGL(k_restore_write, g, b, 0, st, d_e, nf, d_toff, ntiles, tw, d_off);
-    else hipLaunchKernelGGL(k_elide_write, g, b, 0, st, d_e, nf, d_toff, ntiles, tw, d_off);
+        hipLaunchKernelGGL(k_scan_blocks<false>, dim3(1), dim3(1024), 0, st, d_cnt, ntiles, d_off);
+    hipLaunchKernelGGL(k_restore_write, g, b, 0, st, d_e, nf, d_toff, ntiles, tw, d_off);
     return hipGetLastError();
 }
 
 hipError_t launch_huff_stats(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
-                             uint64_t nblocks, int chunk, uint32_t* d_cwords, uint32_t* d_couts,
-                             uint32_t* d_bw, uint32_t* d_bo, int max_nsym, hipStream_t st) {
+                             uint64_t nblocks, int chunk, int ec, uint32_t* d_cwords,
+                             uint32_t* d_couts, EncSums sums, int max_nsym, hipStream_t st) {
     if (nblocks == 0) return hipSuccess;
+    if (ec < 4 || ec > kEncBlockMax || ec % 4 != 0) return hipErrorInvalidValue;
     const size_t lds = (size_t)max_nsym * sizeof(uint32_t);
     const dim3 g((unsigned)nblocks), b(256);
     switch (chunk) {
-    case 256: hipLaunchKernelGGL(k_huff_stats<4>, g, b, lds, st, d_fields, nfields, d_boff, d_cwords, d_couts, d_bw, d_bo); break;
-    case 512: hipLaunchKernelGGL(k_huff_stats<8>, g, b, lds, st, d_fields, nfields, d_boff, d_cwords, d_couts, d_bw, d_bo); break;
-    case 1024: hipLaunchKernelGGL(k_huff_stats<16>, g, b, lds, st, d_fields, nfields, d_boff, d_cwords, d_couts, d_bw, d_bo); break;
-    case 2048: hipLaunchKernelGGL(k_huff_stats<32>, g, b, lds, st, d_fields, nfields, d_boff, d_cwords, d_couts, d_bw, d_bo); break;
+    case 256: hipLaunchKernelGGL(k_huff_stats<4>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
+    case 512: hipLaunchKernelGGL(k_huff_stats<8>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
+    case 1024: hipLaunchKernelGGL(k_huff_stats<16>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
+    case 2048: hipLaunchKernelGGL(k_huff_stats<32>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_scan_blocks(const uint32_t* d_a, const uint32_t* d_b, uint64_t n,
-                              uint64_t* d_aoff, uint64_t* d_boff, hipStream_t st) {
-    if (n > 16 * 1024)
-        hipLaunchKernelGGL(k_scan_blocks<true>, dim3(1), dim3(1024), 0, st, d_a, d_b, n, d_aoff, d_boff);
-    else
-        hipLaunchKernelGGL(k_scan_blocks<false>, dim3(1), dim3(1024), 0, st, d_a, d_b, n, d_aoff, d_boff);
-    return hipGetLastError();
-}
-
 hipError_t launch_huff_encode(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
-                              uint64_t nblocks, int chunk, const uint32_t* d_cwords,
-                              const uint32_t* d_couts, const uint64_t* d_bwoff,
-                              const uint64_t* d_booff, uint32_t* d_bnz, int max_nsym,
-                              hipStream_t st) {
+                              uint64_t nblocks, int chunk, int ec, const uint32_t* d_cwords,
+                              const uint32_t* d_couts, EncSums sums, int max_nsym, hipStream_t st) {
     if (nblocks == 0) return hipSuccess;
+    if (ec < 4 || ec > kEncBlockMax || ec % 4 != 0) return hipErrorInvalidValue;
     const int mcw = enc_chunk_words(chunk);
     const size_t lds = ((size_t)max_nsym + 4 * (size_t)mcw) * sizeof(uint32_t);
     const dim3 g((unsigned)nblocks), b(256);
     switch (chunk) {
-    case 256: hipLaunchKernelGGL(k_huff_encode<4>, g, b, lds, st, d_fields, nfields, d_boff, d_cwords, d_couts, d_bwoff, d_booff, d_bnz); break;
-    case 512: hipLaunchKernelGGL(k_huff_encode<8>, g, b, lds, st, d_fields, nfields, d_boff, d_cwords, d_couts, d_bwoff, d_booff, d_bnz); break;
-    case 1024: hipLaunchKernelGGL(k_huff_encode<16>, g, b, lds, st, d_fields, nfields, d_boff, d_cwords, d_couts, d_bwoff, d_booff, d_bnz); break;
-    case 2048: hipLaunchKernelGGL(k_huff_encode<32>, g, b, lds, st, d_fields, nfields, d_boff, d_cwords, d_couts, d_bwoff, d_booff, d_bnz); break;
+    case 256: hipLaunchKernelGGL(k_huff_encode<4>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
+    case 512: hipLaunchKernelGGL(k_huff_encode<8>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
+    case 1024: hipLaunchKernelGGL(k_huff_encode<16>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
+    case 2048: hipLaunchKernelGGL(k_huff_encode<32>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

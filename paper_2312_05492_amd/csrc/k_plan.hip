@@ -284,7 +284,12 @@ __global__ __launch_bounds__(kDecBlockChunks) void k_dec_prep(const FieldDesc* _
 
 __global__ __launch_bounds__(256) void k_plan(const FieldDesc* __restrict__ F, FieldPlan* P,
                                               const float* pmin, const float* pmax,
-                                              const uint32_t* pbad) {
+                                              const uint32_t* pbad, uint32_t* zero,
+                                              uint64_t nzero) {
+    // sums that the kernels after the interpolation add to
+    for (uint64_t i = (uint64_t)blockIdx.x * blockDim.x + threadIdx.x; i < nzero;
+         i += (uint64_t)gridDim.x * blockDim.x)
+        gp(zero)[i] = 0u;
     // a copy of the field record: the plan's stores below then cannot make
     // the compiler load its members again (one wait each)
     const FieldDesc f = F[blockIdx.x];
@@ -448,9 +453,9 @@ hipError_t launch_range(const FieldDesc* d_fields, FieldPlan* d_plans, int nfiel
 
 hipError_t launch_plan(const FieldDesc* d_fields, FieldPlan* d_plans, int nfields,
                        const float* d_part_min, const float* d_part_max,
-                       const uint32_t* d_part_bad, hipStream_t st) {
+                       const uint32_t* d_part_bad, uint32_t* zero, uint64_t nzero, hipStream_t st) {
     hipLaunchKernelGGL(k_plan, dim3(nfields), dim3(256), 0, st, d_fields, d_plans, d_part_min,
-                       d_part_max, d_part_bad);
+                       d_part_max, d_part_bad, zero, nzero);
     return hipGetLastError();
 }
 

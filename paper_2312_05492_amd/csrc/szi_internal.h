@@ -12,7 +12,7 @@ namespace szi {
 constexpr int kLutBits = 13;       // decode look-up table width (bits)
 constexpr int kRangeBlocks = 2048; // partial min/max blocks per field
 constexpr int kThreads = 256;      // threads per interpolation workgroup
-constexpr int kEncBlockChunks = 32;   // Huffman chunks per encode workgroup
+constexpr int kEncBlockMax = 32;      // Huffman chunks per encode workgroup, at most
 constexpr int kDecBlockChunks = 256;  // Huffman chunks per decode workgroup
 constexpr int kWordPad = 8;        // allocated u32 past the end of every Huffman word array
 
@@ -54,7 +54,8 @@ struct FieldDesc {
     uint32_t* outlier_idx;
     float* outlier_val;
     const uint32_t* dtab;  // decode tables (see DecodeTables layout)
-    unsigned long long* nzw;  // compress: the field's non-zero words (stats clears, encode adds)
+    unsigned long long* tot;  // compress: receives the field's words and non-zero words
+    uint32_t* esec;        // compress: its words section with the zero words elided
     uint16_t* sub;         // per chunk kSubParts bit offsets: 0, then where its 2nd .. last eighth starts (or null)
 };
 
@@ -120,9 +121,10 @@ __host__ __device__ inline int dtab_words(int nsym) { return kDtSorted + nsym; }
 hipError_t launch_range(const FieldDesc* d_fields, FieldPlan* d_plans, int nfields,
                         float* d_part_min, float* d_part_max, uint32_t* d_part_bad,
                         hipStream_t st);
+// zero: nzero words to clear (the encode's sums)
 hipError_t launch_plan(const FieldDesc* d_fields, FieldPlan* d_plans, int nfields,
                        const float* d_part_min, const float* d_part_max,
-                       const uint32_t* d_part_bad, hipStream_t st);
+                       const uint32_t* d_part_bad, uint32_t* zero, uint64_t nzero, hipStream_t st);
 hipError_t launch_zero_hist(const FieldDesc* d_fields, int nfields, hipStream_t st);
 // decompression prologue: block word counts, outlier scatter, pass descriptors
 hipError_t launch_dec_prep(const FieldDesc* d_fields, FieldPlan* d_plans, int nfields,
@@ -160,45 +162,64 @@ hipError_t launch_decompress_gen(const FieldDesc* d_fields, const FieldPlan* d_p
 hipError_t launch_decompress(int ndim, const FieldDesc* d_fields, const FieldPlan* d_plans,
                              const uint64_t* d_goff, uint64_t ngroups, int num_cus,
                              LaunchShape shape, hipStream_t st);
+// Chunks per encode workgroup (a multiple of its four waves): 32 where that
+// leaves eight workgroups a CU, fewer on smaller calls, where a workgroup's
+// chunks follow each other with nothing beside them (64^3, 256 chunks: stats
+// 10 -> 7 us and encode 18 -> 8 us with 4 instead of 32).
+inline int enc_block_chunks(uint64_t chunks) {
+    int ec = kEncBlockMax;
+    while (ec > 4 && chunks < 2048ull * (uint64_t)ec) ec /= 2;
+    return ec;
+}
+// Sums over the encode blocks of a group: per block, and over every 2^shift
+// of a field's blocks (its last ones, fewer than that, are not summed), so
+// that a block finds what lies before it from a few hundred numbers even in
+// the largest field, without a scan between the kernels.  The long sums are
+// added to by atomics and start at zero (launch_plan clears them), each in a
+// 128-byte line of its own: atomics on one line take 25 ns each, one after
+// another (one counter per field had bounded the encode of 512^3, 4096
+// blocks, at 91 us; sums over 256 blocks cost 6 us at 100x500x500).  Those
+// of field f of the group start at (boff[f] >> shift) + f.
+inline int enc_super_shift(uint64_t blocks) { return blocks <= 16384 ? 6 : 8; }
+constexpr int kSuperLine = 32;   // words
+struct EncSums {
+    uint32_t* words;    // per block: Huffman words, outliers, non-zero words
+    uint32_t* outs;
+    uint32_t* nz;
+    uint32_t* woff;     // per block: words of the field's earlier blocks
+    uint32_t* sup;      // per 2^shift blocks: words, outliers
+    uint32_t* supnz;    // per 2^shift blocks: non-zero words
+    int shift;          // 6, or 8 where the sums would be more than a few hundred
+};
 hipError_t launch_huff_stats(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
-                             uint64_t nblocks, int chunk, uint32_t* d_cwords, uint32_t* d_couts,
-                             uint32_t* d_bw, uint32_t* d_bo, int max_nsym, hipStream_t st);
-hipError_t launch_scan_blocks(const uint32_t* d_a, const uint32_t* d_b, uint64_t n,
-                              uint64_t* d_aoff, uint64_t* d_boff, hipStream_t st);
-// d_bnz: per encode block, the number of non-zero words it wrote (each
-// block also adds it to its field's *nzw, where nzw is set)
+                             uint64_t nblocks, int chunk, int ec, uint32_t* d_cwords,
+                             uint32_t* d_couts, EncSums sums, int max_nsym, hipStream_t st);
 hipError_t launch_huff_encode(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
-                              uint64_t nblocks, int chunk, const uint32_t* d_cwords,
-                              const uint32_t* d_couts, const uint64_t* d_bwoff,
-                              const uint64_t* d_booff, uint32_t* d_bnz, int max_nsym,
-                              hipStream_t st);
-// Zero-word elision of one field's Huffman words: words (the field's word
-// array), sec (the elided section: bitmap words, then the non-zero words;
-// capacity (n_words + 31) / 32 + n_words), and the word count, either n or
-// read on the device as *wend - *wbeg (the field's block word offsets).
-// nzw, when set, is the field's count of non-zero words from the encoder:
-// a field that does not elide is then skipped without reading its words.
+                              uint64_t nblocks, int chunk, int ec, const uint32_t* d_cwords,
+                              const uint32_t* d_couts, EncSums sums, int max_nsym, hipStream_t st);
+// Zero-word elision of the words that the encode left: into each field's
+// esec (bitmap words, then the non-zero words; capacity (n_words + 31) / 32 +
+// n_words) where that is shorter.
+hipError_t launch_elide(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
+                        uint64_t nblocks, EncSums sums, hipStream_t st);
+// The restore of an uploaded field's nw words from its elided section.
 struct ElideField {
     uint32_t* words;
     uint32_t* sec;
-    const uint64_t* wbeg;
-    const uint64_t* wend;
-    const unsigned long long* nzw;
     uint64_t nw;
 };
-// Elision tiles: 8192 words, or 2048 where the call has few words (then
-// four times the waves share them, each with one round of loads instead of
-// four); the tile size only splits the work, the section is the same.
+// Restore tiles: 8192 words, or 2048 where there are few words (then four
+// times the waves share them, each with one round of loads instead of four);
+// the tile size only splits the work.
 constexpr uint64_t kElideTileWords = 8192;
 constexpr uint64_t kElideTileSmall = 2048;
 inline uint64_t elide_tile_words(uint64_t words) {
     return words < (uint64_t)1024 * kElideTileSmall ? kElideTileSmall : kElideTileWords;
 }
-// restore = 0: elide words into sec where that is shorter; 1: restore words
-// from sec.  Fields own the tiles [toff[f], toff[f + 1]) of tw words (a
-// multiple of 2048); cnt and off (u32[ntiles], u64[ntiles + 1]) are scratch.
-hipError_t launch_elide(const ElideField* d_e, int nf, const uint64_t* d_toff, uint64_t ntiles,
-                        uint64_t tw, uint32_t* d_cnt, uint64_t* d_off, int restore, hipStream_t st);
+// Fields own the tiles [toff[f], toff[f + 1]) of tw words (a multiple of
+// 2048); cnt and off (u32[ntiles], u64[ntiles + 1]) are scratch.
+hipError_t launch_restore(const ElideField* d_e, int nf, const uint64_t* d_toff, uint64_t ntiles,
+                          uint64_t tw, uint32_t* d_cnt, uint64_t* d_off, hipStream_t st);
 // d_bsum: the word count of every decode block (launch_dec_prep)
 // split: every field has sub-chunk offsets (kSubParts lanes per chunk)
 hipError_t launch_huff_decode(const FieldDesc* d_fields, int nfields, const uint64_t* d_dboff,

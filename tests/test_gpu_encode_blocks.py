@@ -1,0 +1,96 @@
+"""The Huffman encode's block sizes and sums against the CPU oracle: chunk counts on both sides of each number of
+chunks per workgroup (4, 8, 16, 32), fields that end inside a block and inside a long sum, fields whose zero words
+are elided and ones that keep them, batches whose fields' sums lie side by side, and more blocks than the short
+sums serve."""
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_2312_05492_amd as szi
+from paper_2312_05492_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    O.build(force=False)
+    c = szi.Context(0)
+    yield c
+    c.close()
+
+
+def smooth(n):
+    """A slow wave with a quiet stretch: most Huffman words are zero."""
+    t = np.arange(n, dtype=np.float64)
+    return (np.sin(t * 1e-4) * (1.0 + 0.5 * np.sin(t * 3e-7))).astype(np.float32)
+
+
+def rough(n):
+    return np.random.default_rng(n).normal(size=n).astype(np.float32)
+
+
+def check(ctx, x, **kw):
+    import torch
+    print("\n[encode] %s %s" % (x.shape, kw), flush=True)
+    ref = O.compress(x, O.Params(shape=x.shape, **kw))
+    res = ctx.compress(torch.from_numpy(x).cuda(), **kw)
+    try:
+        assert np.array_equal(res.read(szi.SEC_WORDS), ref.words)
+        assert np.array_equal(res.read(szi.SEC_OUTLIER_IDX), ref.outlier_idx)
+        blob = res.blob()
+        assert blob == ref.blob()
+        y = ctx.decompress(res).cpu().numpy()
+        assert np.array_equal(y.view(np.uint32), ref.recon.view(np.uint32))
+        # the elided words are restored from the blob
+        up = ctx.upload(blob)
+        assert np.array_equal(up.read(szi.SEC_WORDS), ref.words)
+        up.free()
+        return blob
+    finally:
+        res.free()
+
+
+@pytest.mark.parametrize("chunks", [4, 5, 64 * 4, 64 * 4 + 1, 16383, 16385, 32769, 65535, 65537])
+@pytest.mark.parametrize("gen", [smooth, rough])
+def test_block_sizes(ctx, chunks, gen):
+    check(ctx, gen(chunks * 256 - 77), chunk=256, eb=1e-2 if gen is rough else 1e-3)
+
+
+def test_batch_of_block_counts(ctx):
+    # fields of one to a few hundred blocks, elided and not, two chunk sizes
+    import torch
+    sizes = [(300, smooth, 256), (70000, rough, 256), (65536 * 4, smooth, 256), (1, rough, 256), (200000, smooth, 1024),
+             (65536 * 16 + 5, rough, 1024), (900000, smooth, 256), (5000, smooth, 1024)]
+    xs = [g(n) for n, g, _ in sizes]
+    params = [dict(chunk=c, eb=1e-3) for _, _, c in sizes]
+    refs = [O.compress(x, O.Params(shape=x.shape, **p)) for x, p in zip(xs, params)]
+    for rep in range(2):
+        print("\n[encode] batch, pass %d" % rep, flush=True)
+        outs = ctx.compress_batch([torch.from_numpy(x).cuda() for x in xs], params)
+        for r, ref in zip(outs, refs):
+            assert r.blob() == ref.blob()
+            r.free()
+
+
+def test_given_code_with_many_outliers_runs_the_encode_again(ctx):
+    import torch
+    x = rough(300000)
+    kw = dict(eb=1e-30, eb_mode=0)
+    ref = O.compress(x, O.Params(shape=x.shape, **kw))
+    book = szi.code_lengths(ref.hist)
+    want = O.compress(x, O.Params(shape=x.shape, **kw), lengths=book)
+    print("\n[encode] again", flush=True)
+    res = ctx.compress_with_code(torch.from_numpy(x).cuda(), book, **kw)
+    assert res.blob() == want.blob()
+    res.free()
+
+
+def test_more_blocks_than_short_sums(ctx):
+    # 2^27 points in chunks of 256: more than 16384 blocks of 32 chunks
+    x = smooth(2 ** 27 + 12345)
+    blob = check(ctx, x, chunk=256, eb=1e-4)
+    assert blob[124] & 1   # elided
