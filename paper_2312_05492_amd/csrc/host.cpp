@@ -659,6 +659,11 @@ void release_result(sz_ctx* c, sz_result* r) {
     std::memset(r, 0, sizeof(*r));
 }
 
+// the chunks' first words, behind their parts' bit offsets
+inline uint32_t* chunk_words(uint16_t* sub, uint64_t nchunks) {
+    return sub ? reinterpret_cast<uint32_t*>(sub + (size_t)kSubParts * nchunks) : nullptr;
+}
+
 // the window kernels run per group of fields: 3D, 2D and 1D with the
 // default stride and window, then every other geometry (the generic kernels)
 constexpr int kGroups = 4, kGenGroup = 3;
@@ -1188,7 +1193,8 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         R->d_cbook = reinterpret_cast<uint32_t*>(tabs + tables_len_bytes(nsym));
         R->d_dtab = R->d_cbook + nsym;
         if ((s = res_alloc(c, R, geo[i].nchunks, &res[i].chunk_bits))) return s;
-        if ((s = res_alloc(c, R, (size_t)kSubParts * geo[i].nchunks, &R->d_sub))) return s;
+        // bit offsets of the chunks' parts and, behind them, their first words
+        if ((s = res_alloc(c, R, (size_t)(kSubParts + 2) * geo[i].nchunks, &R->d_sub))) return s;
         res[i].n = geo[i].npts;
         res[i].n_anchors = geo[i].nanch;
         res[i].n_chunks = geo[i].nchunks;
@@ -1197,6 +1203,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         fd[i].hist = res[i].hist;
         fd[i].chunk_bits = res[i].chunk_bits;
         fd[i].sub = R->d_sub;
+        fd[i].choff = chunk_words(R->d_sub, geo[i].nchunks);
         fd[i].cbook = R->d_cbook;
         fd[i].chunk_base = chunk_base;
         chunk_base += geo[i].nchunks;
@@ -1806,6 +1813,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         f.words = res[i].words;
         f.chunk_bits = res[i].chunk_bits;
         f.sub = R->d_sub;
+        f.choff = chunk_words(R->d_sub, geo[i].nchunks);
         split = split && R->d_sub != nullptr;
         f.outlier_idx = res[i].outlier_idx;
         f.outlier_val = res[i].outlier_val;
@@ -1990,6 +1998,7 @@ sz_status sz_decompress_noalloc(sz_ctx* c, const sz_result* res, float* d_out, v
     f.words = res->words;
     f.chunk_bits = res->chunk_bits;
     f.sub = R->d_sub;
+    f.choff = chunk_words(R->d_sub, geo.nchunks);
     f.outlier_idx = res->outlier_idx;
     f.outlier_val = res->outlier_val;
     f.n_outliers = res->n_outliers;

@@ -396,6 +396,7 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
             b[0] = 0u;
 #pragma unroll
             for (int k = 1; k < 8; ++k) b[k] = (uint32_t)__builtin_amdgcn_readlane((int)pos, 8 * k);
+            if (lane == 0) gp(fd.choff)[ch] = (uint32_t)ow;   // and the chunk's first word
             if (lane == 0)
                 *reinterpret_cast<SZI_G vu4*>(gp(fd.sub) + (uint64_t)kSubParts * ch) =
                     vu4{b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16)};
@@ -432,14 +433,52 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
 // stores.
 //
 // With Q = kSubParts (8) lanes per chunk, each lane decodes an eighth of
-// the chunk's symbols from the bit offset the encoder recorded for it
-// (fd.sub: eight per chunk, the first 0, kept with a compressed result):
-// eight times the independent chains, each an eighth as long (against four
-// lanes a chunk, 1 % faster at rel 1e-3, 5 % at 1e-4 and 38 % on a 64^3
-// field).  A workgroup then covers an eighth of a decode block (kDecChunks
-// chunks, whose word counts the prologue summed).  A field without offsets
-// (an uploaded blob) is decoded by the first lane of each chunk.
+// the chunk's symbols from the word and bit that the encoder recorded for it
+// (fd.choff: the chunk's first word; fd.sub: the eighths' bit offsets, the
+// first 0; both kept with a compressed result): eight times the independent
+// chains, each an eighth as long (against four lanes a chunk, 1 % faster at
+// rel 1e-3, 5 % at 1e-4 and 38 % on a 64^3 field), and no sums over the
+// field's earlier words ahead of them.  A workgroup then covers an eighth of
+// a decode block (kDecChunks chunks).  A field without offsets (an uploaded
+// blob) is decoded by one lane a chunk, which finds its words from the word
+// counts that the prologue summed.
+//
+// What a workgroup of eight lanes a chunk takes at 512^3, rel 1e-3 (164 us
+// for 5.3 rounds of workgroups, before; timed with parts of the kernel left
+// out): 61 us ahead of the first symbol (table, sums, offsets, words, one
+// after another), 34 us for stores of 64 different lines an instruction, the
+// rest the symbols.  So the words are requested before the table is filled,
+// and eight lanes of a chunk exchange their 16-byte pieces, after which each
+// store instruction writes eight whole lines (DECT us now).
 constexpr int kRing = 32;   // ring words per lane (power of 2)
+
+// Exchange among the eight lanes c, c + 8, .., c + 56 of a wave (all lanes
+// active): lane c + 8 q's piece j becomes lane c + 8 j's piece q.
+__device__ __forceinline__ void exchange8(vu4 (&p)[8]) {
+#pragma unroll
+    for (int d = 0; d < 4; ++d) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {   // lane bit 5 with piece bit 2
+            const auto r = __builtin_amdgcn_permlane32_swap(p[i][d], p[i + 4][d], false, false);
+            p[i][d] = r[0];
+            p[i + 4][d] = r[1];
+        }
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {   // lane bit 4 with piece bit 1
+            if (i & 2) continue;
+            const auto r = __builtin_amdgcn_permlane16_swap(p[i][d], p[i + 2][d], false, false);
+            p[i][d] = r[0];
+            p[i + 2][d] = r[1];
+        }
+#pragma unroll
+        for (int i = 0; i < 8; i += 2) {   // lane bit 3 with piece bit 0: rows rotated by 8, half of each kept
+            constexpr int kRowRor8 = 0x128;
+            const int a = (int)p[i][d], b = (int)p[i + 1][d];
+            p[i][d] = (uint32_t)__builtin_amdgcn_update_dpp(a, b, kRowRor8, 0xF, 0xC, false);
+            p[i + 1][d] = (uint32_t)__builtin_amdgcn_update_dpp(b, a, kRowRor8, 0xF, 0x3, false);
+        }
+    }
+}
 
 template <int Q>
 __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __restrict__ F,
@@ -464,7 +503,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __r
     const int ntab = dtab_words(nsym);
     const uint16_t* lut = reinterpret_cast<const uint16_t*>(lut32);
     const int tid = threadIdx.x;
-    {
+    auto fill_tables = [&]() SZI_INLINE {
         // the look-up table 16 bytes at a time, its four loads per lane in
         // flight together (word by word where the tables do not start on 16
         // bytes: odd radius), then the rest word by word
@@ -482,49 +521,52 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __r
             for (int k = tid; k < kDtLimit; k += kDecChunks) lut32[k] = src[k];
         }
         for (int k = kDtLimit + tid; k < ntab; k += kDecChunks) tab_hi[k - kDtLimit] = src[k];
-    }
+    };
     // length limits of the codes longer than the LUT, in scalar registers
     uint32_t lim[kLmax - kLutBits - 1];
 #pragma unroll
     for (int l = kLutBits + 1; l < kLmax; ++l)
         lim[l - kLutBits - 1] = __builtin_amdgcn_readfirstlane(gp(fd.dtab)[kDtLimit + l]);
-    const uint32_t q = (uint32_t)tid % Q;   // the lane's part of its chunk
+    // the lane's part of its chunk: eight lanes of a chunk lie 8 apart (exchange8)
+    const uint32_t q = Q > 1 ? ((uint32_t)tid >> 3) & 7u : 0u;
     const uint64_t bfirst = (pblk - boff[f]) * kDecChunks;   // the decode block's first chunk
-    const uint64_t ch = bfirst + part * CPW + (uint64_t)tid / Q;
+    const uint64_t ch = Q > 1 ? bfirst + part * CPW + (uint32_t)(8 * (tid >> 6) + (tid & 7)) : bfirst + (uint32_t)tid;
     const bool live = ch < fd.nchunks;
     const uint32_t cbits = live ? (uint32_t)gp(fd.chunk_bits)[ch] : 0u;
-    const uint32_t nw = (cbits + 31) >> 5;
-    // words of the field's earlier blocks (the sum of their word counts),
-    // of this block's chunks before the workgroup's, and the workgroup's
-    // exclusive scan of its chunks' word counts (each chunk counted once,
-    // by its first lane)
-    uint64_t pb = 0;
-    for (uint64_t i = boff[f] + (uint64_t)tid; i < pblk; i += kDecChunks) pb += bsum[i];
-    if (Q > 1)
-        for (uint32_t k = (uint32_t)tid; k < part * CPW; k += kDecChunks)
-            if (bfirst + k < fd.nchunks) pb += ((uint32_t)gp(fd.chunk_bits)[bfirst + k] + 31u) >> 5;
-    for (int o = 32; o > 0; o >>= 1) pb += __shfl_xor(pb, o);
-    uint32_t tot;
-    const uint32_t wx = wave_excl_scan(q == 0 ? nw : 0u, &tot) - (q == 0 ? 0u : nw);
-    if ((tid & 63) == 0) {
-        scan[tid >> 6] = tot;
-        pre[tid >> 6] = pb;
-    }
-    __syncthreads();
-    uint64_t before = 0;
-    for (int k = 0; k < kDecChunks / 64; ++k) before += pre[k];
-    for (int k = 0; k < (tid >> 6); ++k) before += scan[k];
     const int C = fd.chunk;
-    const bool split = Q > 1 && fd.sub != nullptr;   // the field has sub-chunk offsets
-    const int SC = split ? C / Q : C;                // symbols per lane
-    const uint64_t s0 = ch * (uint64_t)C + (uint64_t)(split ? q * (uint32_t)SC : 0u);
-    int cnt = !live || (!split && q != 0) || s0 >= fd.npts ? 0
-              : (s0 + SC <= fd.npts ? SC : (int)(fd.npts - s0));
-    const uint32_t bo = split ? (uint32_t)gp(fd.sub)[(uint64_t)Q * ch + q] : 0u;   // entry 0 is 0
-    if (bo > cbits) cnt = 0;   // a corrupt offset: nothing to decode from it
-    if (cnt == 0) return;
-    const uint64_t w0abs = before + wx + (bo >> 5);   // the lane's first word
-    const uint32_t b0 = bo & 31u;                     // and bit in it
+    const int SC = C / Q;   // symbols per lane
+    const uint64_t s0 = ch * (uint64_t)C + (uint64_t)(q * (uint32_t)SC);
+    int cnt = !live || s0 >= fd.npts ? 0 : (s0 + SC <= fd.npts ? SC : (int)(fd.npts - s0));
+    uint64_t wfirst = 0;               // the chunk's first word
+    uint32_t bo = 0, be0 = cbits;      // the lane's bits of it
+    if constexpr (Q > 1) {
+        if (live) {
+            wfirst = gp(fd.choff)[ch];
+            if (q > 0u) bo = (uint32_t)gp(fd.sub)[(uint64_t)Q * ch + q];
+            if (q + 1u < (uint32_t)Q) be0 = (uint32_t)gp(fd.sub)[(uint64_t)Q * ch + q + 1];
+        }
+        if (bo > cbits) cnt = 0;   // a corrupt offset: nothing to decode from it
+    } else {
+        // words of the field's earlier blocks (the sum of their word counts)
+        // and the workgroup's exclusive scan of its chunks' word counts
+        fill_tables();
+        const uint32_t nw = (cbits + 31) >> 5;
+        uint64_t pb = 0;
+        for (uint64_t i = boff[f] + (uint64_t)tid; i < pblk; i += kDecChunks) pb += bsum[i];
+        for (int o = 32; o > 0; o >>= 1) pb += __shfl_xor(pb, o);
+        uint32_t tot;
+        const uint32_t wx = wave_excl_scan(nw, &tot);
+        if ((tid & 63) == 0) {
+            scan[tid >> 6] = tot;
+            pre[tid >> 6] = pb;
+        }
+        __syncthreads();
+        for (int k = 0; k < kDecChunks / 64; ++k) wfirst += pre[k];
+        for (int k = 0; k < (tid >> 6); ++k) wfirst += scan[k];
+        wfirst += wx;
+    }
+    const uint64_t w0abs = wfirst + (bo >> 5);   // the lane's first word
+    const uint32_t b0 = bo & 31u;                // and bit in it
     // word indices count from the 4-aligned word at or below the lane's
     // first; requests stop after the word that holds the lane's last bit
     // (where the next part starts, else the chunk's end; the ring may
@@ -534,12 +576,11 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __r
     // it).  Stopping at the lane's own end saves a twentieth of decode time.
     const uint64_t wbase = w0abs & ~(uint64_t)3;
     const SZI_G uint32_t* words = gp(fd.words) + wbase;
-    const uint32_t be0 = split && q + 1 < (uint32_t)Q ? (uint32_t)gp(fd.sub)[(uint64_t)Q * ch + q + 1] : cbits;
     const uint32_t be = be0 < bo || be0 > cbits ? cbits : be0;   // a corrupt offset: the chunk's end
-    const uint64_t wlim0 = before + wx + ((be + 31u) >> 5);
+    const uint64_t wlim0 = wfirst + ((be + 31u) >> 5);
     const uint64_t wlim = wlim0 < fd.words_cap ? wlim0 : fd.words_cap;
     const uint64_t wleft = wlim > wbase ? wlim - wbase : 0;
-    const uint32_t wcap = wleft < (1u << 30) ? (uint32_t)wleft : (1u << 30);
+    const uint32_t wcap = cnt == 0 ? 0u : (wleft < (1u << 30) ? (uint32_t)wleft : (1u << 30));
     // the lane's ring: word i at ring[(i ^ sw) % kRing], the 16-byte groups
     // permuted per lane so that lanes at the same position hit different banks
     uint32_t* ring = rings + tid * kRing;
@@ -562,6 +603,11 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __r
             c = *reinterpret_cast<const SZI_G vu4*>(words + 8);
             d = *reinterpret_cast<const SZI_G vu4*>(words + 12);
         }
+        if (Q > 1) {   // the words are on their way; then the table
+            fill_tables();
+            __syncthreads();
+        }
+        if (!wave_any(cnt > 0)) return;   // uniform: a wave past the field's chunks
         put(0u, a, b);
         put(8u, c, d);
         wr = 16;
@@ -648,10 +694,26 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __r
         return pk;
     };
     int k = 0;
-    // 64 symbols of a lane leave as eight back-to-back 16-byte stores, so
-    // that a lane writes a whole 128-byte cache line at once (half lines
-    // written far apart in time cost 15 % more decode time)
-    if (vec) {
+    // Symbols leave 64 at a time.  Where every lane of the wave has them (all
+    // but a field's last chunks) the eight lanes of a chunk exchange their
+    // pieces: store j then writes the whole 128-byte line of part j.
+    if (Q > 1 && vec) {
+        SZI_G uint16_t* cout = gp(fd.codes) + ch * (uint64_t)C + 8u * q;
+#pragma unroll 1
+        for (; !wave_any(k + 64 > cnt); k += 64) {
+            vu4 p[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) p[j] = group8();
+            exchange8(p);
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                *reinterpret_cast<SZI_G vu4*>(cout + (uint32_t)(j * SC + k)) = p[j];
+        }
+    }
+    // One lane a chunk: a lane's 64 symbols as eight back-to-back 16-byte
+    // stores, so that it writes a whole line at once (half lines written far
+    // apart in time cost 15 % more decode time).
+    if (Q == 1 && vec) {
 #pragma unroll 1
         for (; k + 64 <= cnt; k += 64) {
             vu4 p[8];

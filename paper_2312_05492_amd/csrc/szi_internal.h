@@ -57,6 +57,7 @@ struct FieldDesc {
     unsigned long long* tot;  // compress: receives the field's words and non-zero words
     uint32_t* esec;        // compress: its words section with the zero words elided
     uint16_t* sub;         // per chunk kSubParts bit offsets: 0, then where its 2nd .. last eighth starts (or null)
+    uint32_t* choff;       // per chunk its first word (with sub)
 };
 
 // One pass of the interpolation (Sec. V-A: levels from stride S/2 to 1, one
