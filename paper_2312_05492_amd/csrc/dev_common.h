@@ -4,6 +4,9 @@
 #include <float.h>
 #include <math.h>
 
+#include <map>
+#include <mutex>
+
 #include "szi_internal.h"
 
 namespace szi {
@@ -122,6 +125,25 @@ __device__ __forceinline__ int block_field(const uint64_t* __restrict__ boff, in
         if (boff[mid] <= b) lo = mid; else hi = mid - 1;
     }
     return lo;
+}
+
+// occupancy of a kernel at an LDS size, asked of the runtime once per process
+template <class K>
+static int resident_per_cu(K kernel, size_t lds) {
+    static std::mutex mu;
+    static std::map<std::pair<const void*, size_t>, int> known;
+    std::lock_guard<std::mutex> lock(mu);
+    const auto key = std::make_pair(reinterpret_cast<const void*>(kernel), lds);
+    auto it = known.find(key);
+    if (it != known.end()) return it->second;
+    int occ = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, kernel, kThreads, lds) != hipSuccess ||
+        occ < 1) {
+        (void)hipGetLastError();
+        occ = 2;
+    }
+    known[key] = occ;
+    return occ;
 }
 
 }  // namespace szi

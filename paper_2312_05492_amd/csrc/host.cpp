@@ -1853,7 +1853,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         {
             STAGE(c, SZ_STAGE_DECODE, q);
             HIP_TRY(c, launch_huff_decode(d_fd, (int)nf, d_dboff, nblocks, d_bsum, 2 * max_R,
-                                          split ? 1 : 0, q));
+                                          split ? 1 : 0, c->num_cus, q));
         }
         uint32_t base = 0;
         for (int gi = 0; gi < kGroups; ++gi) {
@@ -2023,7 +2023,7 @@ sz_status sz_decompress_noalloc(sz_ctx* c, const sz_result* res, float* d_out, v
     HIP_TRY(c, launch_stage_words(reinterpret_cast<uint32_t*>(ws), sw, st));
     HIP_TRY(c, launch_dec_prep(d_fd, d_plan, 1, d_dboff, nblocks, d_bsum, st));
     HIP_TRY(c, launch_huff_decode(d_fd, 1, d_dboff, nblocks, d_bsum, 2 * geo.R,
-                                  R->d_sub != nullptr ? 1 : 0, st));
+                                  R->d_sub != nullptr ? 1 : 0, c->num_cus, st));
     HIP_TRY(c, launch_decompress_group(c, group_of(geo), d_fd, d_plan, d_items, ngroups,
                                        shape_for(c, 1, geo.ndim, geo.R), block_points(geo), st));
     return SZ_OK;

@@ -443,13 +443,15 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
 // blob) is decoded by one lane a chunk, which finds its words from the word
 // counts that the prologue summed.
 //
-// What a workgroup of eight lanes a chunk takes at 512^3, rel 1e-3 (164 us
-// for 5.3 rounds of workgroups, before; timed with parts of the kernel left
+// Where the time of eight lanes a chunk went at 512^3, rel 1e-3 (164 us, one
+// workgroup per eighth of a decode block; timed with parts of the kernel left
 // out): 61 us ahead of the first symbol (table, sums, offsets, words, one
 // after another), 34 us for stores of 64 different lines an instruction, the
-// rest the symbols.  So the words are requested before the table is filled,
-// and eight lanes of a chunk exchange their 16-byte pieces, after which each
-// store instruction writes eight whole lines (DECT us now).
+// rest the symbols.  So the eight lanes of a chunk exchange their 16-byte
+// pieces, after which each store instruction writes eight whole lines, and
+// the kernel is persistent: a workgroup fills its table once and its waves
+// go through their chunks on their own, a chunk's offsets requested two ahead
+// and its first words one ahead (142 us).
 constexpr int kRing = 32;   // ring words per lane (power of 2)
 
 // Exchange among the eight lanes c, c + 8, .., c + 56 of a wave (all lanes
@@ -480,154 +482,120 @@ __device__ __forceinline__ void exchange8(vu4 (&p)[8]) {
     }
 }
 
-template <int Q>
-__global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __restrict__ F,
-                                                            int nfields,
-                                                            const uint64_t* __restrict__ boff,
-                                                            const uint32_t* __restrict__ bsum) {
-    // the rings and the look-up table at fixed LDS addresses (a look-up's
-    // address is then its index and an offset, with no base to add); the
-    // limits, bases and sorted symbols, sized by the radius, after them
-    __shared__ __align__(16) uint32_t rings[kDecChunks * kRing];
-    __shared__ __align__(16) uint32_t lut32[kDtLimit];   // 2^kLutBits u16 entries
-    __shared__ uint32_t scan[kDecChunks / 64];
-    __shared__ uint64_t pre[kDecChunks / 64];
-    extern __shared__ uint32_t tab_hi[];   // decode-table words kDtLimit .. dtab_words(nsym)
-    static_assert(Q == 1 || Q == kSubParts, "one lane or kSubParts per chunk");
-    constexpr int CPW = kDecChunks / Q;   // chunks per workgroup
-    const uint64_t pblk = blockIdx.x / Q;   // the decode block
-    const uint32_t part = blockIdx.x % Q;   // the workgroup's share of it
-    const int f = block_field(boff, nfields, pblk);
-    const FieldDesc& fd = F[f];
-    const int nsym = 2 * fd.R;
-    const int ntab = dtab_words(nsym);
-    const uint16_t* lut = reinterpret_cast<const uint16_t*>(lut32);
-    const int tid = threadIdx.x;
-    auto fill_tables = [&]() SZI_INLINE {
-        // the look-up table 16 bytes at a time, its four loads per lane in
-        // flight together (word by word where the tables do not start on 16
-        // bytes: odd radius), then the rest word by word
-        const SZI_G uint32_t* src = gp(fd.dtab);
-        static_assert(kDtLimit % (4 * kDecChunks) == 0, "whole rounds of 16-byte copies");
-        if (((uintptr_t)fd.dtab & 15u) == 0u) {
-            const SZI_G vu4* s4 = reinterpret_cast<const SZI_G vu4*>(src);
-            vu4* d4 = reinterpret_cast<vu4*>(lut32);
-            vu4 v[kDtLimit / (4 * kDecChunks)];
+// The tables of a field in LDS: the look-up table at a fixed address (a
+// look-up's address is then its index and an offset, with no base to add),
+// the limits, bases and sorted symbols, sized by the radius, after it.
+__device__ __forceinline__ void fill_tables(const FieldDesc& fd, uint32_t* lut32, uint32_t* tab_hi) {
+    // the look-up table 16 bytes at a time, its four loads per lane in
+    // flight together (word by word where the tables do not start on 16
+    // bytes: odd radius), then the rest word by word
+    const int tid = threadIdx.x, ntab = dtab_words(2 * fd.R);
+    const SZI_G uint32_t* src = gp(fd.dtab);
+    static_assert(kDtLimit % (4 * kDecChunks) == 0, "whole rounds of 16-byte copies");
+    if (((uintptr_t)fd.dtab & 15u) == 0u) {
+        const SZI_G vu4* s4 = reinterpret_cast<const SZI_G vu4*>(src);
+        vu4* d4 = reinterpret_cast<vu4*>(lut32);
+        vu4 v[kDtLimit / (4 * kDecChunks)];
 #pragma unroll
-            for (int j = 0; j < kDtLimit / (4 * kDecChunks); ++j) v[j] = s4[tid + j * kDecChunks];
+        for (int j = 0; j < kDtLimit / (4 * kDecChunks); ++j) v[j] = s4[tid + j * kDecChunks];
 #pragma unroll
-            for (int j = 0; j < kDtLimit / (4 * kDecChunks); ++j) d4[tid + j * kDecChunks] = v[j];
-        } else {
-            for (int k = tid; k < kDtLimit; k += kDecChunks) lut32[k] = src[k];
-        }
-        for (int k = kDtLimit + tid; k < ntab; k += kDecChunks) tab_hi[k - kDtLimit] = src[k];
-    };
-    // length limits of the codes longer than the LUT, in scalar registers
-    uint32_t lim[kLmax - kLutBits - 1];
-#pragma unroll
-    for (int l = kLutBits + 1; l < kLmax; ++l)
-        lim[l - kLutBits - 1] = __builtin_amdgcn_readfirstlane(gp(fd.dtab)[kDtLimit + l]);
-    // the lane's part of its chunk: eight lanes of a chunk lie 8 apart (exchange8)
-    const uint32_t q = Q > 1 ? ((uint32_t)tid >> 3) & 7u : 0u;
-    const uint64_t bfirst = (pblk - boff[f]) * kDecChunks;   // the decode block's first chunk
-    const uint64_t ch = Q > 1 ? bfirst + part * CPW + (uint32_t)(8 * (tid >> 6) + (tid & 7)) : bfirst + (uint32_t)tid;
-    const bool live = ch < fd.nchunks;
-    const uint32_t cbits = live ? (uint32_t)gp(fd.chunk_bits)[ch] : 0u;
-    const int C = fd.chunk;
-    const int SC = C / Q;   // symbols per lane
-    const uint64_t s0 = ch * (uint64_t)C + (uint64_t)(q * (uint32_t)SC);
-    int cnt = !live || s0 >= fd.npts ? 0 : (s0 + SC <= fd.npts ? SC : (int)(fd.npts - s0));
-    uint64_t wfirst = 0;               // the chunk's first word
-    uint32_t bo = 0, be0 = cbits;      // the lane's bits of it
-    if constexpr (Q > 1) {
-        if (live) {
-            wfirst = gp(fd.choff)[ch];
-            if (q > 0u) bo = (uint32_t)gp(fd.sub)[(uint64_t)Q * ch + q];
-            if (q + 1u < (uint32_t)Q) be0 = (uint32_t)gp(fd.sub)[(uint64_t)Q * ch + q + 1];
-        }
-        if (bo > cbits) cnt = 0;   // a corrupt offset: nothing to decode from it
+        for (int j = 0; j < kDtLimit / (4 * kDecChunks); ++j) d4[tid + j * kDecChunks] = v[j];
     } else {
-        // words of the field's earlier blocks (the sum of their word counts)
-        // and the workgroup's exclusive scan of its chunks' word counts
-        fill_tables();
-        const uint32_t nw = (cbits + 31) >> 5;
-        uint64_t pb = 0;
-        for (uint64_t i = boff[f] + (uint64_t)tid; i < pblk; i += kDecChunks) pb += bsum[i];
-        for (int o = 32; o > 0; o >>= 1) pb += __shfl_xor(pb, o);
-        uint32_t tot;
-        const uint32_t wx = wave_excl_scan(nw, &tot);
-        if ((tid & 63) == 0) {
-            scan[tid >> 6] = tot;
-            pre[tid >> 6] = pb;
-        }
-        __syncthreads();
-        for (int k = 0; k < kDecChunks / 64; ++k) wfirst += pre[k];
-        for (int k = 0; k < (tid >> 6); ++k) wfirst += scan[k];
-        wfirst += wx;
+        for (int k = tid; k < kDtLimit; k += kDecChunks) lut32[k] = src[k];
     }
-    const uint64_t w0abs = wfirst + (bo >> 5);   // the lane's first word
-    const uint32_t b0 = bo & 31u;                // and bit in it
-    // word indices count from the 4-aligned word at or below the lane's
-    // first; requests stop after the word that holds the lane's last bit
-    // (where the next part starts, else the chunk's end; the ring may
-    // then hold stale words past it, which only fill a look-up's unused
-    // low bits) and never pass the field's words (the array has kWordPad
-    // words of slack, so the 8-word loads of the last request stay inside
-    // it).  Stopping at the lane's own end saves a twentieth of decode time.
+    for (int k = kDtLimit + tid; k < ntab; k += kDecChunks) tab_hi[k - kDtLimit] = src[k];
+}
+
+// Where a lane's symbols start in its field's words, and how far it may read.
+struct LaneWords {
+    const SZI_G uint32_t* words;   // from the 4-aligned word at or below the lane's first
+    uint32_t first;                // the lane's first word, counted from there
+    uint32_t b0;                   // and bit in it
+    uint32_t cap;                  // words to request (0: none)
+};
+// wfirst: the chunk's first word; bits [bo, be0) of the chunk's cbits are
+// the lane's.  Requests stop after the word that holds the lane's last bit
+// (the ring may then hold stale words past it, which only fill a look-up's
+// unused low bits) and never pass the field's words (the array has kWordPad
+// words of slack, so the 8-word loads of the last request stay inside it).
+// Stopping at the lane's own end saves a twentieth of decode time.
+__device__ __forceinline__ LaneWords lane_words(const FieldDesc& fd, bool any, uint64_t wfirst, uint32_t bo,
+                                                uint32_t be0, uint32_t cbits) {
+    const uint64_t w0abs = wfirst + (bo >> 5);
     const uint64_t wbase = w0abs & ~(uint64_t)3;
-    const SZI_G uint32_t* words = gp(fd.words) + wbase;
     const uint32_t be = be0 < bo || be0 > cbits ? cbits : be0;   // a corrupt offset: the chunk's end
     const uint64_t wlim0 = wfirst + ((be + 31u) >> 5);
     const uint64_t wlim = wlim0 < fd.words_cap ? wlim0 : fd.words_cap;
-    const uint64_t wleft = wlim > wbase ? wlim - wbase : 0;
-    const uint32_t wcap = cnt == 0 ? 0u : (wleft < (1u << 30) ? (uint32_t)wleft : (1u << 30));
-    // the lane's ring: word i at ring[(i ^ sw) % kRing], the 16-byte groups
-    // permuted per lane so that lanes at the same position hit different banks
-    uint32_t* ring = rings + tid * kRing;
-    const uint32_t sw = ((uint32_t)tid & (kRing / 4 - 1)) << 2;
-    auto slot = [&](uint32_t i) SZI_INLINE { return (i ^ sw) & (uint32_t)(kRing - 1); };
-    auto put = [&](uint32_t at, vu4 a, vu4 b) SZI_INLINE {   // words [at, at + 8) into the ring
+    const uint64_t wleft = any && wlim > wbase ? wlim - wbase : 0;
+    return LaneWords{gp((const uint32_t*)fd.words) + wbase, (uint32_t)(w0abs - wbase), bo & 31u,
+                     wleft < (1u << 30) ? (uint32_t)wleft : (1u << 30)};
+}
+// the first 16 words of a lane
+__device__ __forceinline__ void first_words(const LaneWords& l, vu4 (&w)[4]) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) w[k] = vu4{0u, 0u, 0u, 0u};
+    if (l.cap > 0) {
+        w[0] = *reinterpret_cast<const SZI_G vu4*>(l.words);
+        w[1] = *reinterpret_cast<const SZI_G vu4*>(l.words + 4);
+    }
+    if (l.cap > 8) {
+        w[2] = *reinterpret_cast<const SZI_G vu4*>(l.words + 8);
+        w[3] = *reinterpret_cast<const SZI_G vu4*>(l.words + 12);
+    }
+}
+
+// A lane's decoder.
+struct LaneDec {
+    const uint16_t* lut;
+    const uint32_t* tab_hi;
+    uint32_t* ring;      // the lane's ring: word i at ring[(i ^ sw) % kRing], the 16-byte groups
+    uint32_t sw;         // permuted per lane so that lanes at the same position hit different banks
+    uint32_t nsym;
+    uint32_t lim[kLmax - kLutBits - 1];   // limits of the codes longer than the table (scalar registers)
+    LaneWords l;
+    uint32_t wr, rd;     // next word to request, next word to read from the ring
+    uint32_t w0, w1, nxw;   // the window's words, and the one the next move takes
+    int32_t nego;        // minus the window's first bit o of w0:w1 (1 <= o <= 32)
+    bool pend;           // words [pat, pat + 8) requested, in la and lb
+    uint32_t pat;
+    vu4 la, lb;
+
+    __device__ __forceinline__ void tables(const FieldDesc& fd) {
+        nsym = 2u * (uint32_t)fd.R;
+#pragma unroll
+        for (int k = kLutBits + 1; k < kLmax; ++k)
+            lim[k - kLutBits - 1] = __builtin_amdgcn_readfirstlane(gp(fd.dtab)[kDtLimit + k]);
+    }
+    __device__ __forceinline__ uint32_t slot(uint32_t i) const { return (i ^ sw) & (uint32_t)(kRing - 1); }
+    __device__ __forceinline__ void put(uint32_t at, vu4 a, vu4 b) {   // words [at, at + 8) into the ring
         *reinterpret_cast<vu4*>(ring + slot(at)) = a;
         *reinterpret_cast<vu4*>(ring + slot(at + 4u)) = b;
-    };
-    uint32_t wr = 0;                              // next word to request
-    uint32_t rd = (uint32_t)(w0abs - wbase);      // next word to read from the ring
-    // prime the ring with 16 words
-    {
-        vu4 a = {0u, 0u, 0u, 0u}, b = a, c = a, d = a;
-        if (wcap > 0) {
-            a = *reinterpret_cast<const SZI_G vu4*>(words);
-            b = *reinterpret_cast<const SZI_G vu4*>(words + 4);
-        }
-        if (wcap > 8) {
-            c = *reinterpret_cast<const SZI_G vu4*>(words + 8);
-            d = *reinterpret_cast<const SZI_G vu4*>(words + 12);
-        }
-        if (Q > 1) {   // the words are on their way; then the table
-            fill_tables();
-            __syncthreads();
-        }
-        if (!wave_any(cnt > 0)) return;   // uniform: a wave past the field's chunks
-        put(0u, a, b);
-        put(8u, c, d);
+    }
+    // starts on a lane's words: 16 into the ring, the window at bit b0 of
+    // the first: the top of w1 (o = 32) or bit b0 of w0
+    __device__ __forceinline__ void start(const LaneWords& lw, const vu4 (&w)[4]) {
+        l = lw;
+        put(0u, w[0], w[1]);
+        put(8u, w[2], w[3]);
         wr = 16;
+        rd = l.first;
+        w0 = 0u;
+        if (l.b0 == 0u) {
+            w1 = ring[slot(rd)];
+            ++rd;
+            nego = -32;
+        } else {
+            w0 = ring[slot(rd)];
+            w1 = ring[slot(rd + 1u)];
+            rd += 2;
+            nego = -(int32_t)l.b0;
+        }
+        nxw = ring[slot(rd)];
+        pend = false;
+        pat = 0;
+        la = lb = vu4{0u, 0u, 0u, 0u};
     }
-    // the window starts at bit b0 of the first word: the top of w1 (o = 32,
-    // held as nego = -o) or bit b0 of w0
-    uint32_t w0 = 0u, w1;
-    int32_t nego;
-    if (b0 == 0u) {
-        w1 = ring[slot(rd)];
-        ++rd;
-        nego = -32;
-    } else {
-        w0 = ring[slot(rd)];
-        w1 = ring[slot(rd + 1u)];
-        rd += 2;
-        nego = -(int32_t)b0;
-    }
-    uint32_t nxw = ring[slot(rd)];   // the ring word the next move takes
-    auto decode_one = [&]() SZI_INLINE -> uint32_t {
+    __device__ __forceinline__ uint32_t one() {
         // bits [o, o + 32) of w0:w1 (the shift amount is 32 - o, taken mod 32)
         const uint32_t x = __builtin_amdgcn_alignbit(w0, w1, (uint32_t)nego);
         const uint32_t e = lut[x >> (32 - kLutBits)];
@@ -639,9 +607,9 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __r
             const uint32_t w = x >> (32 - kLmax);
             uint32_t ln = kLutBits + 1;
 #pragma unroll
-            for (int l = kLutBits + 1; l < kLmax; ++l) ln += w >= lim[l - kLutBits - 1] ? 1u : 0u;
+            for (int k = kLutBits + 1; k < kLmax; ++k) ln += w >= lim[k - kLutBits - 1] ? 1u : 0u;
             const uint32_t i = tab_hi[kDtBase - kDtLimit + ln] + (w >> (kLmax - ln));
-            const uint32_t sl = tab_hi[kDtSorted - kDtLimit + (i < (uint32_t)nsym ? i : 0u)];   // a corrupt stream stays inside
+            const uint32_t sl = tab_hi[kDtSorted - kDtLimit + (i < nsym ? i : 0u)];   // a corrupt stream stays inside
             const bool lng = len == 0;
             sym = lng ? sl : sym;
             len = lng ? ln : len;
@@ -655,81 +623,209 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode(const FieldDesc* __r
         rd += t ? 1u : 0u;
         nxw = ring[slot(rd)];
         return sym;
-    };
-    SZI_G uint16_t* out = gp(fd.codes) + s0;   // s0: a multiple of 64 symbols
-    const bool vec = ((uintptr_t)fd.codes & 15u) == 0u;   // s0 and k are multiples of 8
-    // a group: commit the previous request, maybe request 8 more words,
-    // then decode up to 8 symbols
-    bool pend = false;
-    uint32_t pat = 0;
-    vu4 la = {0u, 0u, 0u, 0u}, lb = la;
-    auto refill = [&]() SZI_INLINE {
+    }
+    // ahead of a group of up to 8 symbols: commit the previous request,
+    // maybe request 8 more words
+    __device__ __forceinline__ void refill() {
         if (pend) put(pat, la, lb);
         // the ring holds [rd, wr) and a request adds 8; the prefetched word
         // at rd is not overwritten because the ring keeps kRing - 8 >= 7
-        pend = wr < wcap && wr + 8 - rd <= (uint32_t)kRing;
+        pend = wr < l.cap && wr + 8 - rd <= (uint32_t)kRing;
         if (pend) {
             pat = wr;
-            la = *reinterpret_cast<const SZI_G vu4*>(words + wr);
-            lb = *reinterpret_cast<const SZI_G vu4*>(words + wr + 4);
+            la = *reinterpret_cast<const SZI_G vu4*>(l.words + wr);
+            lb = *reinterpret_cast<const SZI_G vu4*>(l.words + wr + 4);
             wr += 8;
         }
-    };
-    auto group8 = [&]() SZI_INLINE -> vu4 {
+    }
+    __device__ __forceinline__ uint32_t two() {
+        const uint32_t lo = one(), hi = one();
+        return lo | (hi << 16);
+    }
+    __device__ __forceinline__ vu4 group8() {
         refill();
         vu4 pk;
-        uint32_t lo, hi;
-        lo = decode_one();
-        hi = decode_one();
-        pk.x = lo | (hi << 16);
-        lo = decode_one();
-        hi = decode_one();
-        pk.y = lo | (hi << 16);
-        lo = decode_one();
-        hi = decode_one();
-        pk.z = lo | (hi << 16);
-        lo = decode_one();
-        hi = decode_one();
-        pk.w = lo | (hi << 16);
+        pk.x = two();
+        pk.y = two();
+        pk.z = two();
+        pk.w = two();
         return pk;
-    };
-    int k = 0;
-    // Symbols leave 64 at a time.  Where every lane of the wave has them (all
-    // but a field's last chunks) the eight lanes of a chunk exchange their
-    // pieces: store j then writes the whole 128-byte line of part j.
-    if (Q > 1 && vec) {
-        SZI_G uint16_t* cout = gp(fd.codes) + ch * (uint64_t)C + 8u * q;
+    }
+    // symbols [k, cnt) one store each
+    __device__ __forceinline__ void tail(SZI_G uint16_t* out, int k, int cnt) {
 #pragma unroll 1
-        for (; !wave_any(k + 64 > cnt); k += 64) {
-            vu4 p[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) p[j] = group8();
-            exchange8(p);
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                *reinterpret_cast<SZI_G vu4*>(cout + (uint32_t)(j * SC + k)) = p[j];
+        while (k < cnt) {
+            refill();
+            const int e = k + 8 < cnt ? k + 8 : cnt;
+#pragma unroll 1
+            for (; k < e; ++k) out[k] = (uint16_t)one();
         }
     }
-    // One lane a chunk: a lane's 64 symbols as eight back-to-back 16-byte
-    // stores, so that it writes a whole line at once (half lines written far
-    // apart in time cost 15 % more decode time).
-    if (Q == 1 && vec) {
+};
+
+// One lane a chunk, kDecChunks chunks a workgroup.
+__global__ __launch_bounds__(kDecChunks) void k_huff_decode1(const FieldDesc* __restrict__ F, int nfields,
+                                                             const uint64_t* __restrict__ boff,
+                                                             const uint32_t* __restrict__ bsum) {
+    __shared__ __align__(16) uint32_t rings[kDecChunks * kRing];
+    __shared__ __align__(16) uint32_t lut32[kDtLimit];   // 2^kLutBits u16 entries
+    __shared__ uint32_t scan[kDecChunks / 64];
+    __shared__ uint64_t pre[kDecChunks / 64];
+    extern __shared__ uint32_t tab_hi[];   // decode-table words kDtLimit .. dtab_words(nsym)
+    const uint64_t pblk = blockIdx.x;
+    const int f = block_field(boff, nfields, pblk);
+    const FieldDesc& fd = F[f];
+    const int tid = threadIdx.x;
+    fill_tables(fd, lut32, tab_hi);
+    LaneDec dec;
+    dec.lut = reinterpret_cast<const uint16_t*>(lut32);
+    dec.tab_hi = tab_hi;
+    dec.ring = rings + tid * kRing;
+    dec.sw = ((uint32_t)tid & (kRing / 4 - 1)) << 2;
+    dec.tables(fd);
+    const uint64_t ch = (pblk - boff[f]) * kDecChunks + (uint32_t)tid;
+    const uint32_t cbits = ch < fd.nchunks ? (uint32_t)gp(fd.chunk_bits)[ch] : 0u;
+    // words of the field's earlier blocks (the sum of their word counts) and
+    // the workgroup's exclusive scan of its chunks' word counts
+    uint64_t pb = 0;
+    for (uint64_t i = boff[f] + (uint64_t)tid; i < pblk; i += kDecChunks) pb += bsum[i];
+    for (int o = 32; o > 0; o >>= 1) pb += __shfl_xor(pb, o);
+    uint32_t tot;
+    const uint32_t wx = wave_excl_scan((cbits + 31) >> 5, &tot);
+    if ((tid & 63) == 0) {
+        scan[tid >> 6] = tot;
+        pre[tid >> 6] = pb;
+    }
+    __syncthreads();
+    uint64_t wfirst = wx;
+    for (int k = 0; k < kDecChunks / 64; ++k) wfirst += pre[k];
+    for (int k = 0; k < (tid >> 6); ++k) wfirst += scan[k];
+    const uint64_t s0 = ch * (uint64_t)fd.chunk;
+    const int cnt = s0 >= fd.npts ? 0 : (s0 + fd.chunk <= fd.npts ? fd.chunk : (int)(fd.npts - s0));
+    if (cnt == 0) return;
+    const LaneWords lw = lane_words(fd, true, wfirst, 0u, cbits, cbits);
+    vu4 w[4];
+    first_words(lw, w);
+    dec.start(lw, w);
+    SZI_G uint16_t* out = gp(fd.codes) + s0;
+    int k = 0;
+    // 64 symbols of a lane leave as eight back-to-back 16-byte stores, so
+    // that a lane writes a whole 128-byte cache line at once (half lines
+    // written far apart in time cost 15 % more decode time)
+    if (((uintptr_t)fd.codes & 15u) == 0u) {   // s0 and k are multiples of 8
 #pragma unroll 1
         for (; k + 64 <= cnt; k += 64) {
             vu4 p[8];
 #pragma unroll
-            for (int j = 0; j < 8; ++j) p[j] = group8();
+            for (int j = 0; j < 8; ++j) p[j] = dec.group8();
             SZI_G vu4* o = reinterpret_cast<SZI_G vu4*>(out + k);
 #pragma unroll
             for (int j = 0; j < 8; ++j) o[j] = p[j];
         }
     }
+    dec.tail(out, k, cnt);
+}
+
+// Eight lanes a chunk.  A decode block is kUnits units of 32 chunks, eight a
+// wave; workgroup b takes the units [b n / G, (b + 1) n / G) of all fields'
+// n, its table filled again where the field changes.
+constexpr int kUnits = kSubParts;
+static_assert(kUnits * 32 == kDecChunks, "32 chunks a unit, eight lanes each");
+
+__global__ __launch_bounds__(kDecChunks) void k_huff_decode8(const FieldDesc* __restrict__ F, int nfields,
+                                                             const uint64_t* __restrict__ boff,
+                                                             uint64_t units) {
+    __shared__ __align__(16) uint32_t rings[kDecChunks * kRing];
+    __shared__ __align__(16) uint32_t lut32[kDtLimit];   // 2^kLutBits u16 entries
+    extern __shared__ uint32_t tab_hi[];   // decode-table words kDtLimit .. dtab_words(nsym)
+    const int tid = threadIdx.x;
+    const uint32_t q = ((uint32_t)tid >> 3) & 7u;   // the lane's part: eight lanes of a chunk lie 8 apart
+    LaneDec dec;
+    dec.lut = reinterpret_cast<const uint16_t*>(lut32);
+    dec.tab_hi = tab_hi;
+    dec.ring = rings + tid * kRing;
+    dec.sw = ((uint32_t)tid & (kRing / 4 - 1)) << 2;
+    // a unit as this lane sees it: its chunk's record
+    struct Unit {
+        int f;
+        uint32_t ch;         // chunk of the field (fields have fewer than 2^32)
+        uint32_t cbits, wfirst, bo, be;
+    };
+    auto request = [&](uint64_t u, Unit& n) SZI_INLINE {   // n.f: the field of the unit before
+        while (u / kUnits >= boff[n.f + 1]) ++n.f;
+        const FieldDesc& fd = F[n.f];
+        n.ch = (uint32_t)(u - boff[n.f] * kUnits) * 32u + (uint32_t)(8 * (tid >> 6) + (tid & 7));
+        n.cbits = n.wfirst = n.bo = n.be = 0u;
+        if (n.ch < fd.nchunks) {
+            n.cbits = (uint32_t)gp(fd.chunk_bits)[n.ch];
+            n.wfirst = gp(fd.choff)[n.ch];
+            const SZI_G uint16_t* sub = gp((const uint16_t*)fd.sub) + (uint64_t)kSubParts * n.ch;
+            if (q > 0u) n.bo = (uint32_t)sub[q];
+            n.be = q + 1u < (uint32_t)kSubParts ? (uint32_t)sub[q + 1] : 0xFFFFu;   // the last part: to the end
+        }
+    };
+    // symbols of the lane in a unit (none from a corrupt offset)
+    auto symbols = [&](const FieldDesc& fd, const Unit& n, uint64_t& s0) SZI_INLINE {
+        const int SC = fd.chunk / kSubParts;
+        s0 = (uint64_t)n.ch * (uint32_t)fd.chunk + q * (uint32_t)SC;
+        if (n.ch >= fd.nchunks || s0 >= fd.npts || n.bo > n.cbits) return 0;
+        return s0 + SC <= fd.npts ? SC : (int)(fd.npts - s0);
+    };
+    uint64_t u = (uint64_t)blockIdx.x * units / gridDim.x;
+    const uint64_t ue = ((uint64_t)blockIdx.x + 1) * units / gridDim.x;
+    if (u >= ue) return;
+    // the current unit's words and the next one's record are on their way
+    Unit cu, nx;
+    cu.f = block_field(boff, nfields, u / kUnits);
+    request(u, cu);
+    uint64_t s0;
+    int cnt = symbols(F[cu.f], cu, s0);
+    LaneWords lw = lane_words(F[cu.f], cnt > 0, cu.wfirst, cu.bo, cu.be, cu.cbits);
+    vu4 w[4];
+    first_words(lw, w);
+    nx = cu;
+    if (u + 1 < ue) request(u + 1, nx);
+    int tf = -1;   // the field whose tables are in LDS
+    while (true) {
+        const FieldDesc& fd = F[cu.f];
+        if (cu.f != tf) {   // uniform over the workgroup
+            if (tf >= 0) __syncthreads();
+            fill_tables(fd, lut32, tab_hi);
+            dec.tables(fd);
+            __syncthreads();
+            tf = cu.f;
+        }
+        dec.start(lw, w);
+        const int n = cnt;
+        const uint64_t first = s0;
+        const uint32_t ch = cu.ch;
+        if (u + 1 < ue) {
+            cu = nx;
+            cnt = symbols(F[cu.f], cu, s0);
+            lw = lane_words(F[cu.f], cnt > 0, cu.wfirst, cu.bo, cu.be, cu.cbits);
+            first_words(lw, w);
+            if (u + 2 < ue) request(u + 2, nx);
+        }
+        int k = 0;
+        // Symbols leave 64 at a time where every lane of the wave has them
+        // (all but a field's last chunks): the eight lanes of a chunk
+        // exchange their pieces, and store j writes the whole 128-byte line
+        // of part j.
+        if (((uintptr_t)fd.codes & 15u) == 0u) {
+            const uint32_t SC = (uint32_t)fd.chunk / kSubParts;
+            SZI_G uint16_t* cout = gp(fd.codes) + (uint64_t)ch * (uint32_t)fd.chunk + 8u * q;
 #pragma unroll 1
-    while (k < cnt) {
-        refill();
-        const int e = k + 8 < cnt ? k + 8 : cnt;
-#pragma unroll 1
-        for (; k < e; ++k) out[k] = (uint16_t)decode_one();
+            for (; !wave_any(k + 64 > n); k += 64) {
+                vu4 p[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) p[j] = dec.group8();
+                exchange8(p);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) *reinterpret_cast<SZI_G vu4*>(cout + (uint32_t)j * SC + (uint32_t)k) = p[j];
+            }
+        }
+        dec.tail(gp(fd.codes) + first, k, n);
+        if (++u >= ue) break;
     }
 }
 
@@ -936,16 +1032,20 @@ hipError_t launch_huff_encode(const FieldDesc* d_fields, int nfields, const uint
 
 hipError_t launch_huff_decode(const FieldDesc* d_fields, int nfields, const uint64_t* d_dboff,
                               uint64_t nblocks, const uint32_t* d_bsum, int max_nsym, int split,
-                              hipStream_t st) {
+                              int num_cus, hipStream_t st) {
     if (nblocks == 0) return hipSuccess;
     const size_t lds = (size_t)(dtab_words(max_nsym) - kDtLimit) *
                        sizeof(uint32_t);
-    if (split)
-        hipLaunchKernelGGL(k_huff_decode<kSubParts>, dim3((unsigned)(kSubParts * nblocks)), dim3(kDecChunks), lds, st,
-                           d_fields, nfields, d_dboff, d_bsum);
-    else
-        hipLaunchKernelGGL(k_huff_decode<1>, dim3((unsigned)nblocks), dim3(kDecChunks), lds, st,
-                           d_fields, nfields, d_dboff, d_bsum);
+    if (split) {
+        // as many workgroups as are resident at once, but no more than units
+        uint64_t grid = (uint64_t)num_cus * (uint64_t)resident_per_cu(k_huff_decode8, lds);
+        if (grid > kUnits * nblocks) grid = kUnits * nblocks;
+        hipLaunchKernelGGL(k_huff_decode8, dim3((unsigned)grid), dim3(kDecChunks), lds, st, d_fields, nfields,
+                           d_dboff, kUnits * nblocks);
+    } else {
+        hipLaunchKernelGGL(k_huff_decode1, dim3((unsigned)nblocks), dim3(kDecChunks), lds, st, d_fields, nfields,
+                           d_dboff, d_bsum);
+    }
     return hipGetLastError();
 }
 

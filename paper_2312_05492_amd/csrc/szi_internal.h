@@ -225,7 +225,7 @@ hipError_t launch_restore(const ElideField* d_e, int nf, const uint64_t* d_toff,
 // split: every field has sub-chunk offsets (kSubParts lanes per chunk)
 hipError_t launch_huff_decode(const FieldDesc* d_fields, int nfields, const uint64_t* d_dboff,
                               uint64_t nblocks, const uint32_t* d_bsum, int max_nsym, int split,
-                              hipStream_t st);
+                              int num_cus, hipStream_t st);
 
 // ---- the entry point that allocates nothing (noalloc.hip) ----
 // Workspace of sz_decompress_noalloc: a static device array of this many
