@@ -29,6 +29,9 @@ __device__ __forceinline__ const SZI_G T* gp(const T* p) {
 // builtin vectors for wide global loads (no constructors, so they load
 // through address-space-qualified pointers)
 typedef float vf4 __attribute__((ext_vector_type(4)));
+// four floats at any float's address: global memory takes 16-byte accesses
+// at 4-byte alignment
+typedef float vf4a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t vu4 __attribute__((ext_vector_type(4)));
 typedef uint32_t vu2 __attribute__((ext_vector_type(2)));
 

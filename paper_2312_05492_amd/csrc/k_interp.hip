@@ -253,7 +253,7 @@ __device__ __forceinline__ void load_quads(float* pre, const SZI_G float* wb, co
         uint32_t g;
         int l;
         vf4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (qm.quad(k, lane, n01, g, l)) t = *at((const SZI_G vf4*)wb, g >> 2);
+        if (qm.quad(k, lane, n01, g, l)) t = *(const SZI_G vf4a4*)at(wb, g);
         pre[4 * k] = t.x;
         pre[4 * k + 1] = t.y;
         pre[4 * k + 2] = t.z;
@@ -802,7 +802,7 @@ __device__ __forceinline__ void write_values(const float* v, uint32_t lane, cons
     const int x = 4 * (int)(lane % (uint32_t)(G::W0 / 4));
     const int lq = x + (int)sub * G::SY;
     const uint32_t gq = (uint32_t)x + sub * wi.n0;
-    if (FULL && (wi.n0 & 3u) == 0u && ((uintptr_t)f.out & 15u) == 0u) {
+    if (FULL) {
 #pragma unroll
         for (int k = 0; k < M::NS; ++k) {
             const int l = lq + M::y0(k) * G::SY + M::z0(k) * G::SZ;
@@ -812,7 +812,7 @@ __device__ __forceinline__ void write_values(const float* v, uint32_t lane, cons
             o.z = v[l + 2];
             o.w = v[l + 3];
             const uint32_t g = gq + (uint32_t)M::y0(k) * wi.n0 + (uint32_t)M::z0(k) * wi.n01;
-            *at((SZI_G vf4*)ob, g >> 2) = o;
+            *(SZI_G vf4a4*)at(ob, g) = o;
         }
     } else {
 #pragma unroll 1
@@ -951,14 +951,13 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
         if (valid) {
             wn = make_win<ND>(F[f], w);
             const SZI_G float* wb = gp(F[f].in) + wn.gbase;
-            quads = wn.full && (wn.n0 & 3u) == 0u && ((uintptr_t)F[f].in & 15u) == 0u;
+            quads = wn.full;
             if (quads) {
                 qm.init(lane, wn.n0, wn.n01);
                 load_quads<ND>(pre, wb, qm, lane, wn.n01);
             } else {
                 lm.init(lane, wn.n0, wn.n01);
-                if (wn.full) load_block<ND, true>(pre, wb, lm, wn, 0.0f);
-                else load_block<ND, false>(pre, wb, lm, wn, 0.0f);
+                load_block<ND, false>(pre, wb, lm, wn, 0.0f);
             }
         }
     };
@@ -978,7 +977,6 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
         }
         if (vc) {
             if (qc) commit_quads<ND>(v, pre, qm, lane, wc.n01);
-            else if (wc.full) commit_block<ND, true>(v, pre, lm, wc);
             else commit_block<ND, false>(v, pre, lm, wc);
         }
         gs.next();
