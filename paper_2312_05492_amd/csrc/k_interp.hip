@@ -96,7 +96,7 @@ __device__ __forceinline__ SZI_G T* at(SZI_G T* base, uint32_t off) {
 }
 
 // ------------------------------------------------------------ block staging
-// Slots of the block load, NPRE per lane; slot k of a lane is a (global
+// Slots of the replay's code load, NPRE per lane; slot k of a lane is a (global
 // offset from the window origin, LDS index) pair and whether the lane holds
 // a point of the block there (of its in-extent part, for partial windows).
 // 3D: slots 0-35 hold rows (y, z) and (y, z + 4) of planes 0-7 (lanes 0-31
@@ -168,12 +168,12 @@ struct LaneMap<2> {
     }
 };
 
-// 16-byte staging of a whole FP32 block whose rows are 16-byte aligned
-// (n[0] a multiple of 4): lane = (quad q of x, row).  3D: slots 0-8 hold
-// planes z = 0-8 at rows y = lane / 8, slot 9 rows y = 8 of planes lane / 8,
-// slot 10 row (8, 8); then the x = 32 column in two scalar slots.  2D: slots
-// 0-4 rows 4k + lane / 16, then the x = 64 column.  NQ quads and NC column
-// values per lane, the quads first in the register array.
+// 16-byte staging of the FP32 block (rows at any float's address): lane =
+// (quad q of x, row).  3D: slots 0-8 hold planes z = 0-8 at rows y = lane /
+// 8, slot 9 rows y = 8 of planes lane / 8, slot 10 row (8, 8); then the x =
+// 32 column in two scalar slots.  2D: slots 0-4 rows 4k + lane / 16, then
+// the x = 64 column.  NQ quads and NC column values per lane, the quads
+// first in the register array.
 template <int ND>
 struct QuadMap;
 
@@ -210,10 +210,20 @@ struct QuadMap<3> {
         l = 4 * (int)(lane & 7u) + 8 * 33 + 8 * 297;
         return lane < 8u;
     }
+    // values of quad slot k inside a partial window's block
+    __device__ __forceinline__ int inside(int k, uint32_t lane, const Win& wi) const {
+        const int r = (int)(lane >> 3);
+        const int y = k < 9 ? r : 8, z = k < 9 ? k : (k == 9 ? r : 8);
+        return y < wi.e1 && z < wi.e2 ? wi.e0 - 4 * (int)(lane & 7u) : 0;
+    }
     __device__ __forceinline__ bool col(int k, uint32_t lane, uint32_t& g, int& l) const {
         g = k == 0 ? gc0 : gc1;
         l = 32 + 33 * ((int)lane + 64 * k);
         return k == 0 || c1v;
+    }
+    __device__ __forceinline__ bool col_inside(int k, uint32_t lane, const Win& wi) const {
+        const uint32_t r = lane + 64u * (uint32_t)k;
+        return 32 < wi.e0 && (int)(r % 9u) < wi.e1 && (int)(r / 9u) < wi.e2;
     }
 };
 
@@ -237,23 +247,38 @@ struct QuadMap<2> {
         l = lq + 65 * 4 * k;
         return 4 * k + (int)r < 17;
     }
+    __device__ __forceinline__ int inside(int k, uint32_t lane, const Win& wi) const {
+        return 4 * k + (int)r < wi.e1 ? wi.e0 - 4 * (int)(lane & 15u) : 0;
+    }
     __device__ __forceinline__ bool col(int, uint32_t lane, uint32_t& g, int& l) const {
         g = gc0;
         l = 64 + 65 * (int)lane;
         return lane < 17u;
     }
+    __device__ __forceinline__ bool col_inside(int, uint32_t lane, const Win& wi) const {
+        return 64 < wi.e0 && (int)lane < wi.e1;
+    }
 };
 
-template <int ND>
+// FULL: the whole block lies in the field; else quads that cross its end
+// load the values inside it one by one, the others hold zeros
+template <int ND, bool FULL>
 __device__ __forceinline__ void load_quads(float* pre, const SZI_G float* wb, const QuadMap<ND>& qm,
-                                           uint32_t lane, uint32_t n01) {
+                                           uint32_t lane, const Win& wi) {
     using Q = QuadMap<ND>;
 #pragma unroll
     for (int k = 0; k < Q::NQ; ++k) {
         uint32_t g;
         int l;
         vf4 t = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (qm.quad(k, lane, n01, g, l)) t = *(const SZI_G vf4a4*)at(wb, g);
+        const bool slot = qm.quad(k, lane, wi.n01, g, l);
+        const int in = FULL ? 4 : (slot ? qm.inside(k, lane, wi) : 0);
+        if (FULL ? slot : in >= 4) t = *(const SZI_G vf4a4*)at(wb, g);
+        if (!FULL && in > 0 && in < 4) {
+            t.x = *at(wb, g);
+            if (in > 1) t.y = *at(wb, g + 1u);
+            if (in > 2) t.z = *at(wb, g + 2u);
+        }
         pre[4 * k] = t.x;
         pre[4 * k + 1] = t.y;
         pre[4 * k + 2] = t.z;
@@ -264,7 +289,7 @@ __device__ __forceinline__ void load_quads(float* pre, const SZI_G float* wb, co
         uint32_t g;
         int l;
         float t = 0.0f;
-        if (qm.col(k, lane, g, l)) t = *at(wb, g);
+        if (qm.col(k, lane, g, l) && (FULL || qm.col_inside(k, lane, wi))) t = *at(wb, g);
         pre[4 * Q::NQ + k] = t;
     }
 }
@@ -303,17 +328,6 @@ __device__ __forceinline__ void load_block(U* pre, const SZI_G T* wb, const Lane
         U t = fill;
         if (lm.template slot<FULL>(k, wi, g, l)) t = (U)*at(wb, g);
         pre[k] = t;
-    }
-}
-
-template <int ND, bool FULL, class T, class U>
-__device__ __forceinline__ void commit_block(T* dst, const U* pre, const LaneMap<ND>& lm,
-                                             const Win& wi) {
-#pragma unroll
-    for (int k = 0; k < Geo<ND>::NPRE; ++k) {
-        uint32_t g;
-        int l;
-        if (lm.template slot<FULL>(k, wi, g, l)) dst[l] = (T)pre[k];
     }
 }
 
@@ -821,9 +835,13 @@ __device__ __forceinline__ void write_values(const float* v, uint32_t lane, cons
             if (y >= wi.own(1) || z >= wi.own(2)) continue;
             const int l = x + y * G::SY + z * G::SZ;
             const uint32_t g = (uint32_t)x + (uint32_t)y * wi.n0 + (uint32_t)z * wi.n01;
+            if (x + 4 <= wi.own(0)) {
+                *(SZI_G vf4a4*)at(ob, g) = vf4{v[l], v[l + 1], v[l + 2], v[l + 3]};
+            } else {
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if (x + i < wi.own(0)) *at(ob, g + (uint32_t)i) = v[l + i];
+                for (int i = 0; i < 3; ++i)
+                    if (x + i < wi.own(0)) *at(ob, g + (uint32_t)i) = v[l + i];
+            }
         }
     }
 }
@@ -935,14 +953,10 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
     GroupSeq gs = group_seq(ngroups);
     if (!gs.ok()) return;
     int f = 0;
-    // block of the next window: 16-byte quads where the window lies in the
-    // field and its rows are aligned, else one value per slot
-    constexpr int NPQ = QuadMap<ND>::N > G::NPRE ? QuadMap<ND>::N : G::NPRE;
-    float pre[NPQ];
-    LaneMap<ND> lm;
+    float pre[QuadMap<ND>::N];   // block of the next window
     QuadMap<ND> qm;
     Win wn;
-    bool valid, quads = false;
+    bool valid;
     // window of group g for this wave, and the start of its block load
     auto fetch = [&]() {
         while (gs.g >= goff[f + 1]) ++f;
@@ -951,14 +965,9 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
         if (valid) {
             wn = make_win<ND>(F[f], w);
             const SZI_G float* wb = gp(F[f].in) + wn.gbase;
-            quads = wn.full;
-            if (quads) {
-                qm.init(lane, wn.n0, wn.n01);
-                load_quads<ND>(pre, wb, qm, lane, wn.n01);
-            } else {
-                lm.init(lane, wn.n0, wn.n01);
-                load_block<ND, false>(pre, wb, lm, wn, 0.0f);
-            }
+            qm.init(lane, wn.n0, wn.n01);
+            if (wn.full) load_quads<ND, true>(pre, wb, qm, lane, wn);
+            else load_quads<ND, false>(pre, wb, qm, lane, wn);
         }
     };
     fetch();
@@ -967,7 +976,7 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
     while (true) {
         const int fc = f;
         const Win wc = wn;
-        const bool vc = valid, qc = quads;
+        const bool vc = valid;
         if (fc != hf) {   // uniform over the workgroup: groups never span fields
             if (hf >= 0) flush_hist(hist, F[hf]);
             clear_hist(hist, F[fc].R);
@@ -975,10 +984,7 @@ SZI_WINDOW_KERNEL void k_compress(const FieldDesc* __restrict__ F, const FieldPl
             hf = fc;
             passes = load_passes(P[fc], lane);
         }
-        if (vc) {
-            if (qc) commit_quads<ND>(v, pre, qm, lane, wc.n01);
-            else commit_block<ND, false>(v, pre, lm, wc);
-        }
+        if (vc) commit_quads<ND>(v, pre, qm, lane, wc.n01);
         gs.next();
         gs.set_priority();
         const bool more = gs.ok();
