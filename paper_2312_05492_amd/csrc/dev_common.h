@@ -34,6 +34,7 @@ typedef float vf4 __attribute__((ext_vector_type(4)));
 typedef float vf4a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t vu4 __attribute__((ext_vector_type(4)));
 typedef uint32_t vu2 __attribute__((ext_vector_type(2)));
+typedef uint32_t vu2a2 __attribute__((ext_vector_type(2), aligned(2)));   // at any u16's address
 
 __device__ __forceinline__ void gatomic_add(SZI_G uint32_t* p, uint32_t v) {
     __hip_atomic_fetch_add(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

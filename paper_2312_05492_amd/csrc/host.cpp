@@ -1800,6 +1800,8 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
     for (int gi = 0; gi < kGroups; ++gi) perm.insert(perm.end(), grp[gi].begin(), grp[gi].end());
     uint64_t cb = 0;
     bool split = true;   // every field has sub-chunk offsets: kSubParts decode lanes per chunk
+    uint64_t words = 0, npts = 0;
+    int min_chunk = INT32_MAX;
     std::vector<uint64_t> dboff(nf + 1, 0);
     for (uint32_t k = 0; k < nf; ++k) {
         const uint32_t i = perm[k];
@@ -1815,6 +1817,9 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         f.sub = R->d_sub;
         f.choff = chunk_words(R->d_sub, geo[i].nchunks);
         split = split && R->d_sub != nullptr;
+        words += res[i].n_words;
+        npts += geo[i].npts;
+        min_chunk = std::min(min_chunk, (int)geo[i].chunk);
         f.outlier_idx = res[i].outlier_idx;
         f.outlier_val = res[i].outlier_val;
         f.n_outliers = res[i].n_outliers;
@@ -1838,6 +1843,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         nitems[gi] = grp[gi].empty() ? 0 : io[grp[gi].size()];
     }
     const uint64_t nblocks = dboff[nf];
+    const DecodeKind kind = decode_kind(split, nblocks, words, npts, min_chunk, c->num_cus);
     FieldDesc* d_fd;
     FieldPlan* d_plan;
     uint64_t *d_items, *d_dboff;
@@ -1853,7 +1859,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         {
             STAGE(c, SZ_STAGE_DECODE, q);
             HIP_TRY(c, launch_huff_decode(d_fd, (int)nf, d_dboff, nblocks, d_bsum, 2 * max_R,
-                                          split ? 1 : 0, c->num_cus, q));
+                                          kind, c->num_cus, q));
         }
         uint32_t base = 0;
         for (int gi = 0; gi < kGroups; ++gi) {
@@ -1890,7 +1896,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         const std::vector<uint64_t> sig = {nf, nblocks, nitems[0], nitems[1], nitems[2], nitems[3],
                                            grp[0].size(), grp[1].size(), grp[2].size(),
                                            (uint64_t)max_R, (uint64_t)s3.per_cu, (uint64_t)s2.variant,
-                                           (uint64_t)s2.per_cu, L.off, split ? 1u : 0u, gen_block};
+                                           (uint64_t)s2.per_cu, L.off, (uint64_t)kind, gen_block};
         if ((s = graph_run(c, 0, sig, 0, staged, st, enqueue))) return s;
         HIP_TRY(c, hipStreamSynchronize(c->gstream));
         return SZ_OK;
@@ -2023,7 +2029,9 @@ sz_status sz_decompress_noalloc(sz_ctx* c, const sz_result* res, float* d_out, v
     HIP_TRY(c, launch_stage_words(reinterpret_cast<uint32_t*>(ws), sw, st));
     HIP_TRY(c, launch_dec_prep(d_fd, d_plan, 1, d_dboff, nblocks, d_bsum, st));
     HIP_TRY(c, launch_huff_decode(d_fd, 1, d_dboff, nblocks, d_bsum, 2 * geo.R,
-                                  R->d_sub != nullptr ? 1 : 0, c->num_cus, st));
+                                  decode_kind(R->d_sub != nullptr, nblocks, res->n_words, geo.npts,
+                                              (int)geo.chunk, c->num_cus),
+                                  c->num_cus, st));
     HIP_TRY(c, launch_decompress_group(c, group_of(geo), d_fd, d_plan, d_items, ngroups,
                                        shape_for(c, 1, geo.ndim, geo.R), block_points(geo), st));
     return SZ_OK;

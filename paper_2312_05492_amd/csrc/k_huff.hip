@@ -4,7 +4,7 @@
 // Encode: up to 32 consecutive chunks of one field per workgroup (4 wave64,
 // one chunk per wave at a time, C/64 consecutive symbols per lane).
 //   k_huff_stats   bit count and outlier count of every chunk; sums per
-//                  workgroup block and per 64 blocks
+//                  workgroup block and per 64 or 256 blocks
 //   k_huff_encode  chunk offsets = sums of the field's earlier blocks +
 //                  in-block prefix; packs the codewords MSB-first through
 //                  LDS and writes the outliers (index, original value) in
@@ -13,11 +13,17 @@
 // Decode: kDecChunks chunks per decode block, kSubParts lanes per chunk from
 // the bit offsets of its parts that the encoder records (one lane per chunk
 // without them).
-//   k_dec_prep     (k_plan.hip) word count of every decode block
-//   k_huff_decode  sum of the field's earlier block sums and an in-block
-//                  scan, then a table-driven canonical decode from a
-//                  two-word register window fed by a per-lane LDS word
-//                  ring; 64 symbols per lane stored at once
+//   k_dec_prep     (k_plan.hip) word count of every decode block of a field
+//                  without the offsets
+//   k_huff_decode8 (offsets at hand) persistent workgroups, eight lanes a
+//                  chunk from its recorded first word and part offsets
+//   k_huff_decode1 (none) one lane a chunk; first words from the field's
+//                  earlier block sums and an in-block scan
+//   k_huff_decode_runs (none, few chunks of short codes) the same with up to
+//                  four symbols a look-up
+//                  All: a table-driven canonical decode from a two-word
+//                  register window fed by a per-lane LDS word ring; whole
+//                  lines stored at once
 #include "dev_common.h"
 
 namespace szi {
@@ -595,25 +601,53 @@ struct LaneDec {
         pat = 0;
         la = lb = vu4{0u, 0u, 0u, 0u};
     }
+    // a code longer than the table at the top of x: the length is one more
+    // than the number of length limits at or below the next kLmax bits
+    // (canonical codes grow with their length), then one look-up
+    __device__ __forceinline__ void long_code(uint32_t x, uint32_t& ln, uint32_t& sl) const {
+        const uint32_t w = x >> (32 - kLmax);
+        ln = kLutBits + 1;
+#pragma unroll
+        for (int k = kLutBits + 1; k < kLmax; ++k) ln += w >= lim[k - kLutBits - 1] ? 1u : 0u;
+        const uint32_t i = tab_hi[kDtBase - kDtLimit + ln] + (w >> (kLmax - ln));
+        sl = tab_hi[kDtSorted - kDtLimit + (i < nsym ? i : 0u)];   // a corrupt stream stays inside
+    }
+    // up to four symbols from a table of runs (see k_huff_decode_runs), two a
+    // word; returns their number
+    __device__ __forceinline__ int some(const vu2* runs, vu2& sy) {
+        const uint32_t x = __builtin_amdgcn_alignbit(w0, w1, (uint32_t)nego);
+        const vu2 e = runs[x >> (32 - kLutBits)];
+        constexpr uint32_t kSyms = ((1u << kLutSymBits) - 1u) * 0x10001u;
+        uint32_t lo = e.x & kSyms, n = e.y >> (16 + kLutSymBits);
+        uint32_t len = (e.x >> kLutSymBits) & ((1u << (16 - kLutSymBits)) - 1u);
+        if (wave_any(len == 0)) {
+            uint32_t ln, sl;
+            long_code(x, ln, sl);
+            const bool lng = len == 0;
+            lo = lng ? sl : lo;
+            n = lng ? 1u : n;
+            len = lng ? ln : len;
+        }
+        move(len);
+        sy = vu2{lo, e.y & kSyms};
+        return (int)n;
+    }
     __device__ __forceinline__ uint32_t one() {
         // bits [o, o + 32) of w0:w1 (the shift amount is 32 - o, taken mod 32)
         const uint32_t x = __builtin_amdgcn_alignbit(w0, w1, (uint32_t)nego);
         const uint32_t e = lut[x >> (32 - kLutBits)];
         uint32_t len = e >> kLutSymBits, sym = e & ((1u << kLutSymBits) - 1u);
         if (wave_any(len == 0)) {
-            // longer than the table: the length is one more than the number
-            // of length limits at or below the next kLmax bits (canonical
-            // codes grow with their length), then one look-up
-            const uint32_t w = x >> (32 - kLmax);
-            uint32_t ln = kLutBits + 1;
-#pragma unroll
-            for (int k = kLutBits + 1; k < kLmax; ++k) ln += w >= lim[k - kLutBits - 1] ? 1u : 0u;
-            const uint32_t i = tab_hi[kDtBase - kDtLimit + ln] + (w >> (kLmax - ln));
-            const uint32_t sl = tab_hi[kDtSorted - kDtLimit + (i < nsym ? i : 0u)];   // a corrupt stream stays inside
+            uint32_t ln, sl;
+            long_code(x, ln, sl);
             const bool lng = len == 0;
             sym = lng ? sl : sym;
             len = lng ? ln : len;
         }
+        move(len);
+        return sym;
+    }
+    __device__ __forceinline__ void move(uint32_t len) {
         // o += len; past 32 the words move up by one (len <= kLmax < 32)
         nego -= (int32_t)len;
         const bool t = nego < -32;
@@ -622,7 +656,6 @@ struct LaneDec {
         nego += t ? 32 : 0;
         rd += t ? 1u : 0u;
         nxw = ring[slot(rd)];
-        return sym;
     }
     // ahead of a group of up to 8 symbols: commit the previous request,
     // maybe request 8 more words
@@ -663,6 +696,29 @@ struct LaneDec {
     }
 };
 
+// The first word of the chunk of thread tid of decode block blk of a field
+// whose blocks start at first: the words of the field's earlier blocks (the
+// sum of their word counts) and the block's exclusive scan of its chunks'
+// word counts.  scan, pre: LDS, with a barrier inside.
+__device__ __forceinline__ uint64_t first_word(uint32_t cbits, const uint32_t* __restrict__ bsum, uint64_t first,
+                                               uint64_t blk, uint32_t* scan, uint64_t* pre) {
+    const int tid = threadIdx.x;
+    uint64_t pb = 0;
+    for (uint64_t i = first + (uint64_t)tid; i < blk; i += kDecChunks) pb += bsum[i];
+    for (int o = 32; o > 0; o >>= 1) pb += __shfl_xor(pb, o);
+    uint32_t tot;
+    const uint32_t wx = wave_excl_scan((cbits + 31) >> 5, &tot);
+    if ((tid & 63) == 0) {
+        scan[tid >> 6] = tot;
+        pre[tid >> 6] = pb;
+    }
+    __syncthreads();
+    uint64_t wfirst = wx;
+    for (int k = 0; k < kDecChunks / 64; ++k) wfirst += pre[k];
+    for (int k = 0; k < (tid >> 6); ++k) wfirst += scan[k];
+    return wfirst;
+}
+
 // One lane a chunk, kDecChunks chunks a workgroup.
 __global__ __launch_bounds__(kDecChunks) void k_huff_decode1(const FieldDesc* __restrict__ F, int nfields,
                                                              const uint64_t* __restrict__ boff,
@@ -685,21 +741,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode1(const FieldDesc* __
     dec.tables(fd);
     const uint64_t ch = (pblk - boff[f]) * kDecChunks + (uint32_t)tid;
     const uint32_t cbits = ch < fd.nchunks ? (uint32_t)gp(fd.chunk_bits)[ch] : 0u;
-    // words of the field's earlier blocks (the sum of their word counts) and
-    // the workgroup's exclusive scan of its chunks' word counts
-    uint64_t pb = 0;
-    for (uint64_t i = boff[f] + (uint64_t)tid; i < pblk; i += kDecChunks) pb += bsum[i];
-    for (int o = 32; o > 0; o >>= 1) pb += __shfl_xor(pb, o);
-    uint32_t tot;
-    const uint32_t wx = wave_excl_scan((cbits + 31) >> 5, &tot);
-    if ((tid & 63) == 0) {
-        scan[tid >> 6] = tot;
-        pre[tid >> 6] = pb;
-    }
-    __syncthreads();
-    uint64_t wfirst = wx;
-    for (int k = 0; k < kDecChunks / 64; ++k) wfirst += pre[k];
-    for (int k = 0; k < (tid >> 6); ++k) wfirst += scan[k];
+    const uint64_t wfirst = first_word(cbits, bsum, boff[f], pblk, scan, pre);
     const uint64_t s0 = ch * (uint64_t)fd.chunk;
     const int cnt = s0 >= fd.npts ? 0 : (s0 + fd.chunk <= fd.npts ? fd.chunk : (int)(fd.npts - s0));
     if (cnt == 0) return;
@@ -724,6 +766,92 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode1(const FieldDesc* __
         }
     }
     dec.tail(out, k, cnt);
+}
+
+// One lane a chunk where the call has too few chunks to fill the chip, so
+// that only the length of a lane's chain counts (about 0.1 us a step; spread
+// over four times the CUs, one wave each, the plain kernel took 116 us in
+// place of 117 on a 1800x3600 field): a look-up gives up to four
+// symbols, from a table of runs that the workgroup makes out of the field's
+// (u64 entries: four symbols of 16 bits, the run's length in bits above the
+// first, its symbols' number above the last; 0 where the first code is longer
+// than the table).  A workgroup is a quarter of a decode block, one wave of
+// lanes (its scattered stores, a line each, then have a CU's memory pipe to
+// themselves); the other three waves help with the table.
+__global__ __launch_bounds__(kDecChunks) void k_huff_decode_runs(const FieldDesc* __restrict__ F, int nfields,
+                                                                 const uint64_t* __restrict__ boff,
+                                                                 const uint32_t* __restrict__ bsum) {
+    __shared__ __align__(16) vu2 runs[1 << kLutBits];
+    __shared__ __align__(16) uint32_t lut32[kDtLimit];   // 2^kLutBits u16 entries, then the rings
+    __shared__ uint32_t scan[kDecChunks / 64];
+    __shared__ uint64_t pre[kDecChunks / 64];
+    extern __shared__ uint32_t tab_hi[];   // decode-table words kDtLimit .. dtab_words(nsym)
+    static_assert(64 * kRing <= kDtLimit, "a wave's rings take the table's place");
+    const uint64_t pblk = blockIdx.x / kRunWaves;
+    const int part = (int)(blockIdx.x % kRunWaves);
+    const int f = block_field(boff, nfields, pblk);
+    const FieldDesc& fd = F[f];
+    const int tid = threadIdx.x;
+    fill_tables(fd, lut32, tab_hi);
+    const uint64_t ch = (pblk - boff[f]) * kDecChunks + (uint32_t)tid;
+    const uint32_t cbits = ch < fd.nchunks ? (uint32_t)gp(fd.chunk_bits)[ch] : 0u;
+    const uint64_t wfirst = first_word(cbits, bsum, boff[f], pblk, scan, pre);
+    const uint64_t s0 = ch * (uint64_t)fd.chunk;
+    const bool mine = tid >> 6 == part && s0 < fd.npts;
+    const int cnt = !mine ? 0 : (s0 + fd.chunk <= fd.npts ? fd.chunk : (int)(fd.npts - s0));
+    const LaneWords lw = lane_words(fd, mine, wfirst, 0u, cbits, cbits);
+    vu4 w[4];
+    first_words(lw, w);
+    const uint16_t* lut = reinterpret_cast<const uint16_t*>(lut32);
+#pragma unroll 4
+    for (int i = tid; i < 1 << kLutBits; i += kDecChunks) {
+        uint32_t sy[4] = {0u, 0u, 0u, 0u}, at = 0, n = 0;
+        bool on = true;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t e = lut[((uint32_t)i << at) & ((1u << kLutBits) - 1u)], len = e >> kLutSymBits;
+            on = on && len != 0u && at + len <= (uint32_t)kLutBits;
+            sy[j] = on ? e & ((1u << kLutSymBits) - 1u) : 0u;
+            at += on ? len : 0u;
+            n += on ? 1u : 0u;
+        }
+        runs[i] = vu2{sy[0] | (at << kLutSymBits) | (sy[1] << 16),
+                      sy[2] | (sy[3] << 16) | (n << (16 + kLutSymBits))};
+    }
+    static_assert(kLutBits < 1 << (16 - kLutSymBits), "a run's length fits above its first symbol");
+    __syncthreads();
+    if (cnt == 0) return;
+    LaneDec dec;
+    dec.lut = nullptr;
+    dec.tab_hi = tab_hi;
+    dec.ring = lut32 + (tid & 63) * kRing;
+    dec.sw = ((uint32_t)tid & (kRing / 4 - 1)) << 2;
+    dec.tables(fd);
+    dec.start(lw, w);
+    SZI_G uint16_t* out = gp(fd.codes) + s0;
+    int k = 0;
+    // a run is written whole, what is past its end over again by the next
+    while (k + 32 <= cnt) {
+        dec.refill();
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            vu2 sy;
+            const int n = dec.some(runs, sy);
+            *reinterpret_cast<SZI_G vu2a2*>(out + k) = sy;
+            k += n;
+        }
+    }
+#pragma unroll 1
+    while (k < cnt) {
+        dec.refill();
+        vu2 sy;
+        const int n = dec.some(runs, sy);
+        out[k] = (uint16_t)sy.x;
+        if (n > 1 && k + 1 < cnt) out[k + 1] = (uint16_t)(sy.x >> 16);
+        if (n > 2 && k + 2 < cnt) out[k + 2] = (uint16_t)sy.y;
+        if (n > 3 && k + 3 < cnt) out[k + 3] = (uint16_t)(sy.y >> 16);
+        k += n;
+    }
 }
 
 // Eight lanes a chunk.  A decode block is kUnits units of 32 chunks, eight a
@@ -1031,17 +1159,20 @@ hipError_t launch_huff_encode(const FieldDesc* d_fields, int nfields, const uint
 
 
 hipError_t launch_huff_decode(const FieldDesc* d_fields, int nfields, const uint64_t* d_dboff,
-                              uint64_t nblocks, const uint32_t* d_bsum, int max_nsym, int split,
+                              uint64_t nblocks, const uint32_t* d_bsum, int max_nsym, DecodeKind kind,
                               int num_cus, hipStream_t st) {
     if (nblocks == 0) return hipSuccess;
     const size_t lds = (size_t)(dtab_words(max_nsym) - kDtLimit) *
                        sizeof(uint32_t);
-    if (split) {
+    if (kind == kDecSplit) {
         // as many workgroups as are resident at once, but no more than units
         uint64_t grid = (uint64_t)num_cus * (uint64_t)resident_per_cu(k_huff_decode8, lds);
         if (grid > kUnits * nblocks) grid = kUnits * nblocks;
         hipLaunchKernelGGL(k_huff_decode8, dim3((unsigned)grid), dim3(kDecChunks), lds, st, d_fields, nfields,
                            d_dboff, kUnits * nblocks);
+    } else if (kind == kDecRuns) {
+        hipLaunchKernelGGL(k_huff_decode_runs, dim3((unsigned)(kRunWaves * nblocks)), dim3(kDecChunks), lds, st,
+                           d_fields, nfields, d_dboff, d_bsum);
     } else {
         hipLaunchKernelGGL(k_huff_decode1, dim3((unsigned)nblocks), dim3(kDecChunks), lds, st, d_fields, nfields,
                            d_dboff, d_bsum);

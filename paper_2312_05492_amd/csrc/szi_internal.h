@@ -222,9 +222,25 @@ inline uint64_t elide_tile_words(uint64_t words) {
 hipError_t launch_restore(const ElideField* d_e, int nf, const uint64_t* d_toff, uint64_t ntiles,
                           uint64_t tw, uint32_t* d_cnt, uint64_t* d_off, hipStream_t st);
 // d_bsum: the word count of every decode block (launch_dec_prep)
-// split: every field has sub-chunk offsets (kSubParts lanes per chunk)
+// the kernel for the decode: eight lanes a chunk where every field has the
+// encoder's offsets, else one
+enum DecodeKind { kDecSplit, kDecRuns, kDecPlain };
+// Without the offsets: runs of symbols per look-up pay where the chip is not
+// full of chains (a quarter of a decode block then has a CU of its own) and
+// codes are short enough that several fit a look-up; their table costs about
+// 10 us a call, which a chunk of 256 symbols wins back only with the
+// shortest.  Measured, plain against runs, us: 1024 symbols a chunk 91 / 42
+// at 1.05 bits a symbol, 105 / 58 at 2.7, 120 / 97 at 4.8, 126 / 126 at 5.8;
+// 512 50 / 30, 58 / 41, 67 / 63, 70 / 80; 256 30 / 26, 35 / 32, 39 / 45, 40 / 54.
+constexpr int kRunWaves = kDecBlockChunks / 64;
+inline DecodeKind decode_kind(bool split, uint64_t nblocks, uint64_t words, uint64_t npts, int min_chunk,
+                              int num_cus) {
+    if (split) return kDecSplit;
+    const uint64_t bits = min_chunk >= 512 ? 5 : 3;
+    return kRunWaves * nblocks <= (uint64_t)num_cus && 32 * words <= bits * npts ? kDecRuns : kDecPlain;
+}
 hipError_t launch_huff_decode(const FieldDesc* d_fields, int nfields, const uint64_t* d_dboff,
-                              uint64_t nblocks, const uint32_t* d_bsum, int max_nsym, int split,
+                              uint64_t nblocks, const uint32_t* d_bsum, int max_nsym, DecodeKind kind,
                               int num_cus, hipStream_t st);
 
 // ---- the entry point that allocates nothing (noalloc.hip) ----

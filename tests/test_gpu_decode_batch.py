@@ -1,0 +1,87 @@
+"""The eight-lane Huffman decode against the CPU oracle where its workgroups cross field boundaries: more units of
+work than the chip holds workgroups, so each takes chunks of several fields, with their own code books, chunk sizes
+and lengths."""
+import numpy as np
+import pytest
+
+import oracle as O
+import paper_2312_05492_amd as szi
+from paper_2312_05492_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    O.build(force=False)
+    c = szi.Context(0)
+    yield c
+    c.close()
+
+
+def fields(count, seed):
+    """Fields of one, a few and a few hundred chunks, most chunks' last parts short, each with a spread of its own."""
+    rng = np.random.default_rng(seed)
+    out = []
+    for i in range(count):
+        n = int(rng.choice([1, 63, 64, 65, 255, 257, 3000, 8191, 40000]))
+        out.append((np.cumsum(rng.normal(size=n)) * 10.0 ** rng.integers(-2, 3)).astype(np.float32))
+    return out
+
+
+@pytest.mark.parametrize("chunks", [(256,), (512,), (1024,), (2048,), (256, 512, 1024, 2048)])
+def test_workgroups_cross_fields(ctx, chunks):
+    # at least eight units a field: 360 fields are more than the 2048 workgroups that eight a CU would hold
+    import torch
+    xs = fields(360, sum(chunks))
+    params = [dict(chunk=chunks[i % len(chunks)], eb=[1e-2, 1e-3, 1e-4][i % 3]) for i in range(len(xs))]
+    refs = [O.compress(x, O.Params(shape=x.shape, **p)) for x, p in zip(xs, params)]
+    print("\n[decode] %d fields, chunks %s" % (len(xs), chunks), flush=True)
+    outs = ctx.compress_batch([torch.from_numpy(x).cuda() for x in xs], params)
+    for ys in (ctx.decompress_batch(outs), ctx.decompress_batch(outs[::-1])[::-1]):
+        for y, ref in zip(ys, refs):
+            assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
+    for r in outs:
+        r.free()
+
+
+def uploads(ctx, xs, params):
+    refs = [O.compress(x, O.Params(shape=x.shape, **p)) for x, p in zip(xs, params)]
+    return refs, [ctx.upload(r.blob()) for r in refs]
+
+
+@pytest.mark.parametrize("count", [1, 9, 64, 65, 90])
+@pytest.mark.parametrize("radius", [2, 100, 512, 1024])
+def test_uploaded(ctx, count, radius):
+    # without the encoder's offsets: one lane a chunk, runs of symbols up to 64 blocks (256 CUs) of short codes,
+    # single ones otherwise; short and long fields, from almost all one symbol to almost none alike
+    rng = np.random.default_rng(count + radius)
+    xs, params = [], []
+    for i in range(count):
+        n = int(rng.choice([1, 2, 3, 4, 5, 31, 33, 255, 256, 257, 1023, 3000, 8191, 60000]))
+        rough = np.cumsum(rng.normal(size=n))
+        x = [rough, np.where(rng.random(n) < 0.02, rough, 0.0), np.zeros(n), rng.normal(size=n)][i % 4]
+        xs.append(x.astype(np.float32))
+        params.append(dict(chunk=[256, 512, 1024, 2048][i // 4 % 4], eb=[1e-2, 1e-3, 1e-4][i % 3], R=radius))
+    refs, ups = uploads(ctx, xs, params)
+    print("\n[decode] %d uploads, radius %d" % (count, radius), flush=True)
+    for y, r, ref in zip(ctx.decompress_batch(ups), ups, refs):
+        assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
+        if count <= 9:   # alone, by its own codes' lengths
+            z = ctx.decompress(r).cpu().numpy()
+            assert np.array_equal(z.view(np.uint32), ref.recon.view(np.uint32))
+        r.free()
+
+
+def test_uploaded_with_long_codes(ctx):
+    # Fibonacci counts: codes of every length, the longest past the look-up table
+    x = synth.fib_spikes((96, 96, 96), n=20)
+    refs, ups = uploads(ctx, [x], [dict(eb=0.5, eb_mode=0)])
+    assert refs[0].code_len.max() > 13
+    print("\n[decode] long codes", flush=True)
+    y = ctx.decompress(ups[0]).cpu().numpy()
+    assert np.array_equal(y.view(np.uint32), refs[0].recon.view(np.uint32))
+    ups[0].free()
