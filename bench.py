@@ -86,7 +86,7 @@ def host_cpu():
 # (python bench.py --pmc-summary), kept with a hash of the kernel sources
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_512cube_rel1e-3.md")
 STAGE_KERNELS = {"range": "k_range", "interp": "k_compress<3>", "huff_stats": "k_huff_stats",
-                 "encode": "k_huff_encode", "decode": "k_huff_decode",
+                 "encode": "k_huff_encode", "decode": "k_huff_decode8",
                  "replay": "k_decompress<3>"}
 
 
@@ -225,7 +225,7 @@ def trace_summary(stats_csv, cmd, out_path, title):
                 float(r["Percentage"])))
 
 
-COUNTER_KERNELS = ("k_range", "k_compress", "k_huff_stats", "k_huff_encode", "k_elide_count",
+COUNTER_KERNELS = ("k_range", "k_compress", "k_huff_stats", "k_huff_encode", "k_elide",
                    "k_huff_decode", "k_decompress")
 
 

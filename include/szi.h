@@ -186,8 +186,8 @@ sz_status sz_ctx_read_timing(sz_ctx* ctx, double* ms, uint64_t* launches, int re
 
 /* Compress the device field d_in (n[0]*n[1]*n[2] floats, 4-byte aligned as
  * any float array is; INVALID_ARG otherwise, no 16-byte alignment needed:
- * the kernels take a faster path where rows start on 16 bytes).  Runs the whole
- * pipeline on `stream`: range and profiling (Sec. V-C.1), auto-tuning
+ * the kernels move 16 bytes at a time from any float's address).  Runs the
+ * whole pipeline on `stream`: range and profiling (Sec. V-C.1), auto-tuning
  * (Sec. V-C.2, Eq. 1), level bounds (Sec. V-B.2), the interpolation
  * predictor-quantiser with a fused histogram (Sec. V-A/B/D, VI-A), the host
  * codebook (Sec. VI-A), Huffman encoding and outlier compaction.  Returns
