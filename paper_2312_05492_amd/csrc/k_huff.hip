@@ -771,7 +771,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode1(const FieldDesc* __
 // One lane a chunk where the call has too few chunks to fill the chip, so
 // that only the length of a lane's chain counts (about 0.1 us a step; spread
 // over four times the CUs, one wave each, the plain kernel took 116 us in
-// place of 117 on a 1800x3600 field): a look-up gives up to four
+// place of 117 on a 100x150x200 field): a look-up gives up to four
 // symbols, from a table of runs that the workgroup makes out of the field's
 // (u64 entries: four symbols of 16 bits, the run's length in bits above the
 // first, its symbols' number above the last; 0 where the first code is longer
