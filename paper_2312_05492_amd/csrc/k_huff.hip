@@ -459,6 +459,16 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
 // go through their chunks on their own, a chunk's offsets requested two ahead
 // and its first words one ahead (142 us).
 constexpr int kRing = 32;   // ring words per lane (power of 2)
+// The table of the codes longer than the look-up table, where the length of
+// the chain counts: 1024 entries over their part of the code space, so that a
+// step where any lane of the wave holds one mostly takes one look-up more in
+// place of ten compares and two look-ups (78 -> 69 us on a 100x150x200 field;
+// in the eight-lane kernel 140.5 -> 139.4 us at 512^3 and 20.5 -> 21.7 on a
+// 64^3 field, whose table costs more than it saves: not used there).  Nor
+// where that part is so large (1/64 of the code space) that an entry would
+// resolve few of the codes.
+constexpr int kMidBits = 10;
+constexpr uint32_t kMidShift = 8;
 
 // Exchange among the eight lanes c, c + 8, .., c + 56 of a wave (all lanes
 // active): lane c + 8 q's piece j becomes lane c + 8 j's piece q.
@@ -557,7 +567,11 @@ struct LaneDec {
     uint32_t* ring;      // the lane's ring: word i at ring[(i ^ sw) % kRing], the 16-byte groups
     uint32_t sw;         // permuted per lane so that lanes at the same position hit different banks
     uint32_t nsym;
-    uint32_t lim[kLmax - kLutBits - 1];   // limits of the codes longer than the table (scalar registers)
+    // scalar registers: the limits of the codes longer than the table, the
+    // first of them (left-justified to kLmax bits) and their table's shift
+    uint32_t lim[kLmax - kLutBits - 1];
+    uint32_t long0, sh;
+    const uint16_t* mid;   // used by some() only
     LaneWords l;
     uint32_t wr, rd;     // next word to request, next word to read from the ring
     uint32_t w0, w1, nxw;   // the window's words, and the one the next move takes
@@ -571,6 +585,29 @@ struct LaneDec {
 #pragma unroll
         for (int k = kLutBits + 1; k < kLmax; ++k)
             lim[k - kLutBits - 1] = __builtin_amdgcn_readfirstlane(gp(fd.dtab)[kDtLimit + k]);
+    }
+    // The table of long codes, by the workgroup once fill_tables' are
+    // visible: entry j for the codes at long0 + (j << sh), all of one length
+    // and symbol where that length is at most kLmax - sh (they start at
+    // multiples of their span, long0 at one of them all); length - kLutBits
+    // above the symbol, 0: look further.
+    __device__ __forceinline__ void fill_mid(const FieldDesc& fd, uint16_t* m) {
+        mid = m;
+        long0 = __builtin_amdgcn_readfirstlane(gp(fd.dtab)[kDtLimit + kLutBits]);
+        const uint32_t span = (1u << kLmax) - long0;   // of the long codes
+        const int bits = span > 1u ? 32 - __builtin_clz(span - 1u) : 0;
+        sh = bits > kMidBits ? (uint32_t)(bits - kMidBits) : 0u;
+        if (sh > kMidShift) return;
+        for (uint32_t j = threadIdx.x; j < 1u << kMidBits; j += kDecChunks) {
+            const uint32_t c = long0 + (j << sh);
+            uint32_t e = 0u;
+            if (c < 1u << kLmax) {
+                uint32_t ln, sl;
+                long_code(c << (32 - kLmax), ln, sl);
+                if (ln <= (uint32_t)kLmax - sh) e = ((ln - (uint32_t)kLutBits) << kLutSymBits) | sl;
+            }
+            m[j] = (uint16_t)e;
+        }
     }
     __device__ __forceinline__ uint32_t slot(uint32_t i) const { return (i ^ sw) & (uint32_t)(kRing - 1); }
     __device__ __forceinline__ void put(uint32_t at, vu4 a, vu4 b) {   // words [at, at + 8) into the ring
@@ -612,6 +649,17 @@ struct LaneDec {
         const uint32_t i = tab_hi[kDtBase - kDtLimit + ln] + (w >> (kLmax - ln));
         sl = tab_hi[kDtSorted - kDtLimit + (i < nsym ? i : 0u)];   // a corrupt stream stays inside
     }
+    // the same for the lanes with lng, by the table of long codes first
+    __device__ __forceinline__ void long_lookup(uint32_t x, bool lng, uint32_t& ln, uint32_t& sl) const {
+        bool more = true;
+        if (sh <= kMidShift) {
+            const uint32_t e = mid[(((x >> (32 - kLmax)) - long0) >> sh) & ((1u << kMidBits) - 1u)];
+            ln = (e >> kLutSymBits) + (uint32_t)kLutBits;
+            sl = e & ((1u << kLutSymBits) - 1u);
+            more = wave_any(lng && e < 1u << kLutSymBits);
+        }
+        if (more) long_code(x, ln, sl);
+    }
     // up to four symbols from a table of runs (see k_huff_decode_runs), two a
     // word; returns their number
     __device__ __forceinline__ int some(const vu2* runs, vu2& sy) {
@@ -621,9 +669,9 @@ struct LaneDec {
         uint32_t lo = e.x & kSyms, n = e.y >> (16 + kLutSymBits);
         uint32_t len = (e.x >> kLutSymBits) & ((1u << (16 - kLutSymBits)) - 1u);
         if (wave_any(len == 0)) {
-            uint32_t ln, sl;
-            long_code(x, ln, sl);
             const bool lng = len == 0;
+            uint32_t ln, sl;
+            long_lookup(x, lng, ln, sl);
             lo = lng ? sl : lo;
             n = lng ? 1u : n;
             len = lng ? ln : len;
@@ -783,6 +831,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode_runs(const FieldDesc
                                                                  const uint32_t* __restrict__ bsum) {
     __shared__ __align__(16) vu2 runs[1 << kLutBits];
     __shared__ __align__(16) uint32_t lut32[kDtLimit];   // 2^kLutBits u16 entries, then the rings
+    __shared__ uint16_t mid[1 << kMidBits];
     __shared__ uint32_t scan[kDecChunks / 64];
     __shared__ uint64_t pre[kDecChunks / 64];
     extern __shared__ uint32_t tab_hi[];   // decode-table words kDtLimit .. dtab_words(nsym)
@@ -793,6 +842,12 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode_runs(const FieldDesc
     const FieldDesc& fd = F[f];
     const int tid = threadIdx.x;
     fill_tables(fd, lut32, tab_hi);
+    LaneDec dec;
+    dec.lut = nullptr;
+    dec.tab_hi = tab_hi;
+    dec.ring = lut32 + (tid & 63) * kRing;
+    dec.sw = ((uint32_t)tid & (kRing / 4 - 1)) << 2;
+    dec.tables(fd);
     const uint64_t ch = (pblk - boff[f]) * kDecChunks + (uint32_t)tid;
     const uint32_t cbits = ch < fd.nchunks ? (uint32_t)gp(fd.chunk_bits)[ch] : 0u;
     const uint64_t wfirst = first_word(cbits, bsum, boff[f], pblk, scan, pre);
@@ -802,6 +857,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode_runs(const FieldDesc
     const LaneWords lw = lane_words(fd, mine, wfirst, 0u, cbits, cbits);
     vu4 w[4];
     first_words(lw, w);
+    dec.fill_mid(fd, mid);
     const uint16_t* lut = reinterpret_cast<const uint16_t*>(lut32);
 #pragma unroll 4
     for (int i = tid; i < 1 << kLutBits; i += kDecChunks) {
@@ -821,12 +877,6 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode_runs(const FieldDesc
     static_assert(kLutBits < 1 << (16 - kLutSymBits), "a run's length fits above its first symbol");
     __syncthreads();
     if (cnt == 0) return;
-    LaneDec dec;
-    dec.lut = nullptr;
-    dec.tab_hi = tab_hi;
-    dec.ring = lut32 + (tid & 63) * kRing;
-    dec.sw = ((uint32_t)tid & (kRing / 4 - 1)) << 2;
-    dec.tables(fd);
     dec.start(lw, w);
     SZI_G uint16_t* out = gp(fd.codes) + s0;
     int k = 0;

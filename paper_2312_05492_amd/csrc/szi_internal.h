@@ -229,9 +229,9 @@ enum DecodeKind { kDecSplit, kDecRuns, kDecPlain };
 // full of chains (a quarter of a decode block then has a CU of its own) and
 // codes are short enough that several fit a look-up; their table costs about
 // 10 us a call, which a chunk of 256 symbols wins back only with the
-// shortest.  Measured, plain against runs, us: 1024 symbols a chunk 91 / 42
-// at 1.05 bits a symbol, 105 / 58 at 2.7, 120 / 97 at 4.8, 126 / 126 at 5.8;
-// 512 50 / 30, 58 / 41, 67 / 63, 70 / 80; 256 30 / 26, 35 / 32, 39 / 45, 40 / 54.
+// shortest.  Measured, plain against runs, us: 1024 symbols a chunk 91 / 43
+// at 1.05 bits a symbol, 105 / 54 at 2.7, 120 / 88 at 4.8, 126 / 126 at 5.8;
+// 512 50 / 30, 58 / 39, 67 / 57, 70 / 80; 256 30 / 26, 35 / 32, 39 / 45, 40 / 54.
 constexpr int kRunWaves = kDecBlockChunks / 64;
 inline DecodeKind decode_kind(bool split, uint64_t nblocks, uint64_t words, uint64_t npts, int min_chunk,
                               int num_cus) {
