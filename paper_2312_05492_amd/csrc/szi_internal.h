@@ -224,7 +224,7 @@ hipError_t launch_restore(const ElideField* d_e, int nf, const uint64_t* d_toff,
 // d_bsum: the word count of every decode block (launch_dec_prep)
 // the kernel for the decode: eight lanes a chunk where every field has the
 // encoder's offsets, else one
-enum DecodeKind { kDecSplit, kDecRuns, kDecPlain };
+enum DecodeKind { kDecSplit, kDecSplitScatter, kDecRuns, kDecPlain };
 // Without the offsets: runs of symbols per look-up pay where the chip is not
 // full of chains (a quarter of a decode block then has a CU of its own) and
 // codes are short enough that several fit a look-up; their table costs about
@@ -233,9 +233,14 @@ enum DecodeKind { kDecSplit, kDecRuns, kDecPlain };
 // at 1.05 bits a symbol, 105 / 54 at 2.7, 120 / 88 at 4.8, 126 / 126 at 5.8;
 // 512 50 / 30, 58 / 39, 67 / 57, 70 / 80; 256 30 / 26, 35 / 32, 39 / 45, 40 / 54.
 constexpr int kRunWaves = kDecBlockChunks / 64;
-inline DecodeKind decode_kind(bool split, uint64_t nblocks, uint64_t words, uint64_t npts, int min_chunk,
-                              int num_cus) {
-    if (split) return kDecSplit;
+//
+// With them no prologue is needed where outliers are few: a result's plan
+// holds its pass descriptors, and the decode scatters the outliers itself
+// (kDecSplitScatter: a 64^3 field's call 52 -> 50 us, a 512^3 one's 391 -> 387).  Where they are many (1 in 64 points, two rounds
+// of loads a unit) the prologue's eight times as many workgroups do it.
+inline DecodeKind decode_kind(bool split, uint64_t nblocks, uint64_t words, uint64_t npts,
+                              uint64_t outliers, int min_chunk, int num_cus) {
+    if (split) return outliers <= npts / 64 ? kDecSplitScatter : kDecSplit;
     const uint64_t bits = min_chunk >= 512 ? 5 : 3;
     return kRunWaves * nblocks <= (uint64_t)num_cus && 32 * words <= bits * npts ? kDecRuns : kDecPlain;
 }

@@ -85,3 +85,22 @@ def test_uploaded_with_long_codes(ctx):
     y = ctx.decompress(ups[0]).cpu().numpy()
     assert np.array_equal(y.view(np.uint32), refs[0].recon.view(np.uint32))
     ups[0].free()
+
+
+@pytest.mark.parametrize("every", [40, 400, 40000])
+@pytest.mark.parametrize("shape", [(200000,), (400, 500), (40, 70, 71)])
+def test_outliers_scattered(ctx, every, shape):
+    # more and fewer outliers than one in 64 points: scattered by the prologue or by the decode, alone and in a batch
+    import torch
+    rng = np.random.default_rng(every)
+    x = np.zeros(shape, np.float32)
+    at = rng.choice(x.size, x.size // every, replace=False)
+    x.ravel()[at] = rng.normal(size=at.size) * 100
+    kw = dict(eb=1e-3, eb_mode=0, chunk=256)
+    ref = O.compress(x, O.Params(shape=x.shape, **kw))
+    assert (64 * len(ref.outlier_idx) > x.size) == (every == 40)
+    print("\n[decode] %s, %d outliers" % (shape, len(ref.outlier_idx)), flush=True)
+    r = ctx.compress(torch.from_numpy(x).cuda(), **kw)
+    for y in [ctx.decompress(r)] + list(ctx.decompress_batch([r] * 3)):
+        assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
+    r.free()
