@@ -114,6 +114,11 @@ struct sz_ctx {
     std::string err;
     void* pinned = nullptr;    // host staging buffer
     size_t pinned_bytes = 0;
+    // staging of sz_serialize, kBlobStage bytes made on first use: apart from
+    // the calls' own, and under a lock, because results are read back from
+    // other threads than the one that compresses (a server's results)
+    std::mutex blob_mu;
+    void* blob_stage = nullptr;
     int grid_per_cu = 0;       // persistent workgroups per CU; 0 = resident capacity
     // launch-shape tuner: the shape of each window kernel, per (kind 0 =
     // compression / 1 = replay, ndim, radius); tuned by timing the
@@ -260,13 +265,13 @@ void pool_free(sz_ctx* c, void* p) {
 }
 
 
-constexpr size_t kPinnedLeast = (size_t)1 << 20;   // bytes of a context's pinned staging, at least
+constexpr size_t kBlobStage = (size_t)1 << 20;   // blobs up to this size are staged whole
 sz_status pinned_reserve(sz_ctx* c, size_t bytes) {
     if (c->pinned_bytes >= bytes) return SZ_OK;
     if (c->pinned) (void)hipHostFree(c->pinned);
     c->pinned = nullptr;
     c->pinned_bytes = 0;
-    size_t nb = std::max(bytes, kPinnedLeast);
+    size_t nb = std::max(bytes, (size_t)1 << 20);
     HIP_TRY(c, hipHostMalloc(&c->pinned, nb, hipHostMallocDefault));
     c->pinned_bytes = nb;
     return SZ_OK;
@@ -1038,6 +1043,7 @@ sz_status sz_ctx_destroy(sz_ctx* c) {
     }
     for (hipEvent_t e : c->ev_free) (void)hipEventDestroy(e);
     if (c->pinned) (void)hipHostFree(c->pinned);
+    if (c->blob_stage) (void)hipHostFree(c->blob_stage);
     if (c->gstream) (void)hipStreamSynchronize(c->gstream);
     graph_drop(c);
     if (c->arena) (void)hipFree(c->arena);
@@ -2092,23 +2098,32 @@ sz_status sz_serialize(sz_ctx* c, const sz_result* r, void* dst, uint64_t cap, u
         secs[3] = {R->d_esec, elided_words(r->n_words, R->nzw) * 4};
     }
     // a small blob's sections cross to the pinned staging together and are
-    // waited for once (six waited copies to pageable memory: 75 us more)
+    // waited for once (six waited copies to pageable memory: 75 us more);
+    // where another thread holds the staging, or there is none, each goes
+    // straight to the caller's buffer
     uint8_t* to = out;
-    if (total <= kPinnedLeast) {
-        sz_status s = pinned_reserve(c, kPinnedLeast);
-        if (s) return s;
-        to = static_cast<uint8_t*>(c->pinned);
+    std::unique_lock<std::mutex> stage(c->blob_mu, std::defer_lock);
+    if (total <= kBlobStage && stage.try_lock()) {
+        if (!c->blob_stage && hipHostMalloc(&c->blob_stage, kBlobStage, hipHostMallocDefault) != hipSuccess) {
+            (void)hipGetLastError();
+            c->blob_stage = nullptr;
+        }
+        if (c->blob_stage) to = static_cast<uint8_t*>(c->blob_stage);
     }
     uint64_t pos = 256;
-    for (int k = 0; k < 6; pos += pad8(secs[k].bytes), ++k) {
+    hipError_t e = hipSuccess;
+    for (int k = 0; k < 6 && e == hipSuccess; pos += pad8(secs[k].bytes), ++k) {
         if (!secs[k].bytes) continue;
-        if (to != out) HIP_TRY(c, hipMemcpyAsync(to + pos, secs[k].src, secs[k].bytes, hipMemcpyDeviceToHost, nullptr));
-        else HIP_TRY(c, hipMemcpy(to + pos, secs[k].src, secs[k].bytes, hipMemcpyDeviceToHost));
+        e = to != out ? hipMemcpyAsync(to + pos, secs[k].src, secs[k].bytes, hipMemcpyDeviceToHost, nullptr)
+                      : hipMemcpy(to + pos, secs[k].src, secs[k].bytes, hipMemcpyDeviceToHost);
     }
-    if (to != out) {
-        HIP_TRY(c, hipStreamSynchronize(nullptr));
-        std::memcpy(out + 256, to + 256, total - 256);
+    if (to != out) {   // also after an error: no copy is left on its way into the staging
+        const hipError_t w = hipStreamSynchronize(nullptr);
+        if (e == hipSuccess) e = w;
     }
+    HIP_TRY(c, e);
+    if (to != out) std::memcpy(out + 256, to + 256, total - 256);
+    if (stage.owns_lock()) stage.unlock();
     uint8_t* h = out;
     make_header(r, R, h);
     pos = 256;

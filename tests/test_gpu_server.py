@@ -137,3 +137,31 @@ def test_server_budget_admission():
         srv.submit_compress(big, tag=99)
     assert e.value.code == -3
     srv.close()
+
+
+def test_server_results_serialized_by_several_threads():
+    """blob() of different results of one server from several threads at once: every blob is the plain call's,
+    those that are staged whole (up to 1 MB) and the larger ones."""
+    _skip_without_gpu()
+    from concurrent.futures import ThreadPoolExecutor
+    fields = _mix() + [(synth.spectral_field((160, 160, 200), seed=57), dict(eb=1e-4))]
+    xs = [_gpu(f) for f, _ in fields]
+    ctx = szi.Context(0)
+    ref = [ctx.compress(x, **kw).blob() for x, (_, kw) in zip(xs, fields)]
+    assert min(map(len, ref)) < 1 << 20 < max(map(len, ref))
+    srv = szi.Server(0, slots=4)
+    for i, (x, (_, kw)) in enumerate(zip(xs, fields)):
+        srv.submit_compress(x, tag=i, **kw)
+    got = {}
+    while len(got) < len(xs):
+        for c in srv.poll(wait=True):
+            assert c["status"] == 0
+            got[c["tag"]] = c["result"]
+    with ThreadPoolExecutor(max_workers=6) as pool:
+        work = [i for _ in range(8) for i in range(len(xs))]
+        blobs = list(pool.map(lambda i: got[i].blob(), work))
+    for i, b in zip(work, blobs):
+        assert b == ref[i], "result %d" % i
+    got.clear()
+    srv.close()
+    ctx.close()
