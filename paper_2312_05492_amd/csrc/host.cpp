@@ -664,11 +664,6 @@ void release_result(sz_ctx* c, sz_result* r) {
     std::memset(r, 0, sizeof(*r));
 }
 
-// the chunks' first words, behind their parts' bit offsets
-inline uint32_t* chunk_words(uint16_t* sub, uint64_t nchunks) {
-    return sub ? reinterpret_cast<uint32_t*>(sub + (size_t)kSubParts * nchunks) : nullptr;
-}
-
 // the window kernels run per group of fields: 3D, 2D and 1D with the
 // default stride and window, then every other geometry (the generic kernels)
 constexpr int kGroups = 4, kGenGroup = 3;
@@ -1199,8 +1194,8 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         R->d_cbook = reinterpret_cast<uint32_t*>(tabs + tables_len_bytes(nsym));
         R->d_dtab = R->d_cbook + nsym;
         if ((s = res_alloc(c, R, geo[i].nchunks, &res[i].chunk_bits))) return s;
-        // bit offsets of the chunks' parts and, behind them, their first words
-        if ((s = res_alloc(c, R, (size_t)(kSubParts + 2) * geo[i].nchunks, &R->d_sub))) return s;
+        // the chunks' places and the bit offsets of their parts
+        if ((s = res_alloc(c, R, sub_entries(geo[i].nchunks), &R->d_sub))) return s;
         res[i].n = geo[i].npts;
         res[i].n_anchors = geo[i].nanch;
         res[i].n_chunks = geo[i].nchunks;
@@ -1209,7 +1204,6 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         fd[i].hist = res[i].hist;
         fd[i].chunk_bits = res[i].chunk_bits;
         fd[i].sub = R->d_sub;
-        fd[i].choff = chunk_words(R->d_sub, geo[i].nchunks);
         fd[i].cbook = R->d_cbook;
         fd[i].chunk_base = chunk_base;
         chunk_base += geo[i].nchunks;
@@ -1288,7 +1282,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
     char* d_scr = nullptr;   // the plain calls' scratch block
     const bool many = !graphs && nf >= 2;   // batch: gathered histograms, scattered tables
     uint64_t *d_items, *d_gboff;
-    uint32_t *d_cwords, *d_couts;
+    uint32_t* d_ccnt;
     const size_t hstride = 2 * (size_t)max_R;   // graph mode: histogram k at d_hist + k * hstride
     Layout L;
     const size_t o_fd = L.take<FieldDesc>(nf), o_items = L.take<uint64_t>(items.size());
@@ -1299,8 +1293,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
     const size_t o_pbad = L.take<uint32_t>((size_t)nf * kRangeBlocks);
     const size_t o_hfd = L.take<FieldDesc>(nf), o_gboff = L.take<uint64_t>(gboff.size());
     const size_t end2 = L.off;
-    const size_t o_cwords = L.take<uint32_t>(std::max<uint64_t>(total_chunks, 1));
-    const size_t o_couts = L.take<uint32_t>(std::max<uint64_t>(total_chunks, 1));
+    const size_t o_ccnt = L.take<uint32_t>(std::max<uint64_t>(total_chunks, 1));
     const size_t nblk = std::max<uint64_t>(total_blocks, 1);
     const size_t o_bw = L.take<uint32_t>(nblk), o_bo = L.take<uint32_t>(nblk);
     const size_t o_bnz = L.take<uint32_t>(nblk), o_woff = L.take<uint32_t>(nblk);
@@ -1342,8 +1335,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         d_pbad = reinterpret_cast<uint32_t*>(d + o_pbad);
         d_hfd = reinterpret_cast<FieldDesc*>(d + o_hfd);
         d_gboff = reinterpret_cast<uint64_t*>(d + o_gboff);
-        d_cwords = reinterpret_cast<uint32_t*>(d + o_cwords);
-        d_couts = reinterpret_cast<uint32_t*>(d + o_couts);
+        d_ccnt = reinterpret_cast<uint32_t*>(d + o_ccnt);
         set_sums(d);
         for (uint32_t k = 0; k < nf; ++k) fds[k].hist = d_hist + k * hstride;
     } else {
@@ -1362,8 +1354,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
         d_pbad = reinterpret_cast<uint32_t*>(d + o_pbad);
         d_hfd = reinterpret_cast<FieldDesc*>(d + o_hfd);
         d_gboff = reinterpret_cast<uint64_t*>(d + o_gboff);
-        d_cwords = reinterpret_cast<uint32_t*>(d + o_cwords);
-        d_couts = reinterpret_cast<uint32_t*>(d + o_couts);
+        d_ccnt = reinterpret_cast<uint32_t*>(d + o_ccnt);
         set_sums(d);
     }
     const size_t n_tot = sizeof(unsigned long long) * 2 * nf;   // read back at the end
@@ -1593,12 +1584,12 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
             {
                 STAGE(c, SZ_STAGE_HUFF_STATS, q);
                 HIP_TRY(c, launch_huff_stats(d_hfd + fs, (int)nfg, d_gboff + gboff_at[g], nb, chunk, ec,
-                                             d_cwords, d_couts, es, 2 * max_R, q));
+                                             d_ccnt, es, 2 * max_R, q));
             }
             {
                 STAGE(c, SZ_STAGE_ENCODE, q);
                 HIP_TRY(c, launch_huff_encode(d_hfd + fs, (int)nfg, d_gboff + gboff_at[g], nb, chunk, ec,
-                                              d_cwords, d_couts, es, 2 * max_R, q));
+                                              d_ccnt, es, 2 * max_R, q));
             }
             STAGE(c, SZ_STAGE_ELIDE, q);
             HIP_TRY(c, launch_elide(d_hfd + fs, (int)nfg, d_gboff + gboff_at[g], nb, es, q));
@@ -1821,7 +1812,6 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         f.words = res[i].words;
         f.chunk_bits = res[i].chunk_bits;
         f.sub = R->d_sub;
-        f.choff = chunk_words(R->d_sub, geo[i].nchunks);
         split = split && R->d_sub != nullptr;
         words += res[i].n_words;
         npts += geo[i].npts;
@@ -2011,7 +2001,6 @@ sz_status sz_decompress_noalloc(sz_ctx* c, const sz_result* res, float* d_out, v
     f.words = res->words;
     f.chunk_bits = res->chunk_bits;
     f.sub = R->d_sub;
-    f.choff = chunk_words(R->d_sub, geo.nchunks);
     f.outlier_idx = res->outlier_idx;
     f.outlier_val = res->outlier_val;
     f.n_outliers = res->n_outliers;

@@ -111,8 +111,7 @@ __device__ __forceinline__ void lane_syms(const FieldDesc& fd, uint64_t ch, int 
 template <int PER>
 __global__ __launch_bounds__(256) void k_huff_stats(const FieldDesc* __restrict__ F, int nfields,
                                                     const uint64_t* __restrict__ boff, int ec,
-                                                    uint32_t* cwords, uint32_t* couts,
-                                                    EncSums sums) {
+                                                    uint32_t* ccnt, EncSums sums) {
     // the last blocks first: the codes written last may still lie in the
     // memory-side cache, and the encode then starts on those read last here
     // (512^3: 58 -> 56 us, encode 95 -> 91)
@@ -152,8 +151,7 @@ __global__ __launch_bounds__(256) void k_huff_stats(const FieldDesc* __restrict_
             words = (bits + 31) >> 5;
             if (lane == 0) {
                 gp(fd.chunk_bits)[ch] = (uint16_t)bits;
-                cwords[fd.chunk_base + ch] = words;
-                couts[fd.chunk_base + ch] = zeros;
+                ccnt[fd.chunk_base + ch] = words | zeros << 16;
             }
         }
         if (lane == 0) {
@@ -290,9 +288,7 @@ __host__ __device__ constexpr int enc_chunk_words(int chunk) { return (chunk * k
 template <int PER>
 __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict__ F, int nfields,
                                                      const uint64_t* __restrict__ boff, int ec,
-                                                     const uint32_t* __restrict__ cwords,
-                                                     const uint32_t* __restrict__ couts,
-                                                     EncSums sums) {
+                                                     const uint32_t* __restrict__ ccnt, EncSums sums) {
     extern __shared__ uint32_t smem[];
     __shared__ uint32_t wnz[4], red[8];
     constexpr int C = PER * 64;
@@ -307,14 +303,15 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
     const uint64_t blk_local = blockIdx.x - boff[f];
     const uint64_t first = blk_local * (uint32_t)ec;
     // in-block exclusive prefix of the chunk word and outlier counts
-    uint32_t cw = 0, co = 0;
-    if (lane < ec && first + lane < fd.nchunks) {
-        cw = cwords[fd.chunk_base + first + lane];
-        co = couts[fd.chunk_base + first + lane];
-    }
+    uint32_t cc = 0;
+    if (lane < ec && first + lane < fd.nchunks) cc = ccnt[fd.chunk_base + first + lane];
+    // words of the unit's earlier blocks
+    const uint32_t inu = (uint32_t)(first % kUnitChunks) / (uint32_t)ec;
+    uint32_t rel0 = (uint32_t)lane < inu ? gp(sums.words)[blockIdx.x - inu + lane] : 0u;
     uint32_t tw, to;
-    const uint32_t pw = wave_excl_scan(cw, &tw);
-    const uint32_t po = wave_excl_scan(co, &to);
+    const uint32_t pw = wave_excl_scan(cc & 0xFFFFu, &tw);
+    const uint32_t po = wave_excl_scan(cc >> 16, &to);
+    if (inu) rel0 = wave_sum(rel0);   // uniform
     // words and outliers of the field's earlier blocks; the barrier inside
     // also completes the code book in LDS
     uint32_t bw0, bo0;
@@ -396,17 +393,21 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
             if (ow + k < fd.words_cap) gp(fd.words)[ow + k] = w;
         }
         if (fd.sub) {
-            // the decoder's starting bits of the chunk's eighths (symbol
-            // 8 k PER starts lane 8 k), as one 16-byte store: 0, b1 .. b7
+            // the chunk's place and the decoder's starting bits of its 2nd ..
+            // last eighth (symbol 8 k PER starts lane 8 k), as one 16-byte store
             static_assert(kSubParts == 8, "eight parts: lanes 8, 16, .., 56");
             uint32_t b[8];
-            b[0] = 0u;
+            const uint32_t uw = bw0 - rel0;   // the unit's first word
+            const uint32_t at = (uint32_t)ch % kUnitChunks;
+            b[0] = at == 0u ? uw & 0xFFFFu : (at == 1u ? uw >> 16 : (uint32_t)ow - uw);
 #pragma unroll
             for (int k = 1; k < 8; ++k) b[k] = (uint32_t)__builtin_amdgcn_readlane((int)pos, 8 * k);
-            if (lane == 0) gp(fd.choff)[ch] = (uint32_t)ow;   // and the chunk's first word
-            if (lane == 0)
+            if (lane == 0) {
                 *reinterpret_cast<SZI_G vu4*>(gp(fd.sub) + (uint64_t)kSubParts * ch) =
                     vu4{b[0] | (b[1] << 16), b[2] | (b[3] << 16), b[4] | (b[5] << 16), b[6] | (b[7] << 16)};
+                if (at == 0u && ch + 1 == fd.nchunks)   // a unit of one chunk
+                    gp(fd.sub)[(uint64_t)kSubParts * (ch + 1)] = (uint16_t)(uw >> 16);
+            }
         }
         wave_lds_sync();
     }
@@ -441,8 +442,8 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
 //
 // With Q = kSubParts (8) lanes per chunk, each lane decodes an eighth of
 // the chunk's symbols from the word and bit that the encoder recorded for it
-// (fd.choff: the chunk's first word; fd.sub: the eighths' bit offsets, the
-// first 0; both kept with a compressed result): eight times the independent
+// (fd.sub: the chunk's place and the eighths' bit offsets, kept with a
+// compressed result): eight times the independent
 // chains, each an eighth as long (against four lanes a chunk, 1 % faster at
 // rel 1e-3, 5 % at 1e-4 and 38 % on a 64^3 field), and no sums over the
 // field's earlier words ahead of them.  A workgroup then covers an eighth of
@@ -915,7 +916,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode_runs(const FieldDesc
 // wave; workgroup b takes the units [b n / G, (b + 1) n / G) of all fields'
 // n, its table filled again where the field changes.
 constexpr int kUnits = kSubParts;
-static_assert(kUnits * 32 == kDecChunks, "32 chunks a unit, eight lanes each");
+static_assert(kUnits * kUnitChunks == kDecChunks && kUnitChunks == 32, "32 chunks a unit, eight lanes each");
 
 __global__ __launch_bounds__(kDecChunks) void k_huff_decode8(const FieldDesc* __restrict__ F, int nfields,
                                                              const uint64_t* __restrict__ boff,
@@ -934,26 +935,50 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode8(const FieldDesc* __
     struct Unit {
         int f;
         uint32_t ch;         // chunk of the field (fields have fewer than 2^32)
-        uint32_t cbits, wfirst, bo, be;
+        uint32_t cbits;
+        // entry q and the next of the chunk's record: where the part starts
+        // and ends.  The first part starts at 0 and holds the chunk's place
+        // instead; the last ends with the chunk, and its lanes 0, 1 and 2
+        // hold the halves of the unit's first word and its first chunk's bits.
+        uint32_t bo, be;
     };
+    const uint32_t lane = (uint32_t)tid & 63u;
     auto request = [&](uint64_t u, Unit& n) SZI_INLINE {   // n.f: the field of the unit before
         while (u / kUnits >= boff[n.f + 1]) ++n.f;
         const FieldDesc& fd = F[n.f];
-        n.ch = (uint32_t)(u - boff[n.f] * kUnits) * 32u + (uint32_t)(8 * (tid >> 6) + (tid & 7));
-        n.cbits = n.wfirst = n.bo = n.be = 0u;
-        if (n.ch < fd.nchunks) {
-            n.cbits = (uint32_t)gp(fd.chunk_bits)[n.ch];
-            n.wfirst = gp(fd.choff)[n.ch];
-            const SZI_G uint16_t* sub = gp((const uint16_t*)fd.sub) + (uint64_t)kSubParts * n.ch;
-            if (q > 0u) n.bo = (uint32_t)sub[q];
-            n.be = q + 1u < (uint32_t)kSubParts ? (uint32_t)sub[q + 1] : 0xFFFFu;   // the last part: to the end
+        n.ch = (uint32_t)(u - boff[n.f] * kUnits) * kUnitChunks + (uint32_t)(8 * (tid >> 6) + (tid & 7));
+        n.cbits = n.bo = n.be = 0u;
+        const SZI_G uint16_t* rec = gp((const uint16_t*)fd.sub);
+        const SZI_G uint16_t* bits = gp((const uint16_t*)fd.chunk_bits);
+        const uint32_t c0 = (uint32_t)(u - boff[n.f] * kUnits) * kUnitChunks;
+        const SZI_G uint16_t* end = rec + ((uint64_t)kSubParts * n.ch + q + 1u);
+        bool has = n.ch < fd.nchunks;
+        if (has) {
+            n.cbits = (uint32_t)bits[n.ch];
+            n.bo = (uint32_t)rec[(uint64_t)kSubParts * n.ch + q];
         }
+        if (q + 1u == (uint32_t)kSubParts) {
+            has = lane < 59u && c0 < fd.nchunks;
+            end = lane == 58u ? bits + c0 : rec + (uint64_t)kSubParts * (c0 + (lane & 1u));
+        }
+        if (has) n.be = (uint32_t)*end;
+    };
+    // a requested unit's words for the lane
+    auto place = [&](const FieldDesc& fd, const Unit& n, bool any) SZI_INLINE {
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)n.be, 56);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)n.be, 57);
+        const uint32_t b0 = (uint32_t)__builtin_amdgcn_readlane((int)n.be, 58);
+        const uint32_t rel = (uint32_t)__shfl((int)n.bo, (int)(lane & 7u));
+        const uint32_t at = n.ch % kUnitChunks;
+        const uint32_t wfirst = (lo | hi << 16) + (at == 0u ? 0u : (at == 1u ? (b0 + 31u) >> 5 : rel));
+        return lane_words(fd, any, wfirst, q > 0u ? n.bo : 0u, q + 1u < (uint32_t)kSubParts ? n.be : 0xFFFFu,
+                          n.cbits);
     };
     // symbols of the lane in a unit (none from a corrupt offset)
     auto symbols = [&](const FieldDesc& fd, const Unit& n, uint64_t& s0) SZI_INLINE {
         const int SC = fd.chunk / kSubParts;
         s0 = (uint64_t)n.ch * (uint32_t)fd.chunk + q * (uint32_t)SC;
-        if (n.ch >= fd.nchunks || s0 >= fd.npts || n.bo > n.cbits) return 0;
+        if (n.ch >= fd.nchunks || s0 >= fd.npts || (q > 0u && n.bo > n.cbits)) return 0;
         return s0 + SC <= fd.npts ? SC : (int)(fd.npts - s0);
     };
     uint64_t u = (uint64_t)blockIdx.x * units / gridDim.x;
@@ -965,7 +990,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode8(const FieldDesc* __
     request(u, cu);
     uint64_t s0;
     int cnt = symbols(F[cu.f], cu, s0);
-    LaneWords lw = lane_words(F[cu.f], cnt > 0, cu.wfirst, cu.bo, cu.be, cu.cbits);
+    LaneWords lw = place(F[cu.f], cu, cnt > 0);
     vu4 w[4];
     first_words(lw, w);
     nx = cu;
@@ -994,7 +1019,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode8(const FieldDesc* __
         if (u + 1 < ue) {
             cu = nx;
             cnt = symbols(F[cu.f], cu, s0);
-            lw = lane_words(F[cu.f], cnt > 0, cu.wfirst, cu.bo, cu.be, cu.cbits);
+            lw = place(F[cu.f], cu, cnt > 0);
             first_words(lw, w);
             if (u + 2 < ue) request(u + 2, nx);
         }
@@ -1187,35 +1212,35 @@ hipError_t launch_restore(const ElideField* d_e, int nf, const uint64_t* d_toff,
 }
 
 hipError_t launch_huff_stats(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
-                             uint64_t nblocks, int chunk, int ec, uint32_t* d_cwords,
-                             uint32_t* d_couts, EncSums sums, int max_nsym, hipStream_t st) {
+                             uint64_t nblocks, int chunk, int ec, uint32_t* d_ccnt, EncSums sums,
+                             int max_nsym, hipStream_t st) {
     if (nblocks == 0) return hipSuccess;
     if (ec < 4 || ec > kEncBlockMax || ec % 4 != 0) return hipErrorInvalidValue;
     const size_t lds = (size_t)max_nsym * sizeof(uint32_t);
     const dim3 g((unsigned)nblocks), b(256);
     switch (chunk) {
-    case 256: hipLaunchKernelGGL(k_huff_stats<4>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
-    case 512: hipLaunchKernelGGL(k_huff_stats<8>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
-    case 1024: hipLaunchKernelGGL(k_huff_stats<16>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
-    case 2048: hipLaunchKernelGGL(k_huff_stats<32>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
+    case 256: hipLaunchKernelGGL(k_huff_stats<4>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
+    case 512: hipLaunchKernelGGL(k_huff_stats<8>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
+    case 1024: hipLaunchKernelGGL(k_huff_stats<16>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
+    case 2048: hipLaunchKernelGGL(k_huff_stats<32>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
 hipError_t launch_huff_encode(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
-                              uint64_t nblocks, int chunk, int ec, const uint32_t* d_cwords,
-                              const uint32_t* d_couts, EncSums sums, int max_nsym, hipStream_t st) {
+                              uint64_t nblocks, int chunk, int ec, const uint32_t* d_ccnt, EncSums sums,
+                              int max_nsym, hipStream_t st) {
     if (nblocks == 0) return hipSuccess;
     if (ec < 4 || ec > kEncBlockMax || ec % 4 != 0) return hipErrorInvalidValue;
     const int mcw = enc_chunk_words(chunk);
     const size_t lds = ((size_t)max_nsym + 4 * (size_t)mcw) * sizeof(uint32_t);
     const dim3 g((unsigned)nblocks), b(256);
     switch (chunk) {
-    case 256: hipLaunchKernelGGL(k_huff_encode<4>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
-    case 512: hipLaunchKernelGGL(k_huff_encode<8>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
-    case 1024: hipLaunchKernelGGL(k_huff_encode<16>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
-    case 2048: hipLaunchKernelGGL(k_huff_encode<32>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_cwords, d_couts, sums); break;
+    case 256: hipLaunchKernelGGL(k_huff_encode<4>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
+    case 512: hipLaunchKernelGGL(k_huff_encode<8>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
+    case 1024: hipLaunchKernelGGL(k_huff_encode<16>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
+    case 2048: hipLaunchKernelGGL(k_huff_encode<32>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
     default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

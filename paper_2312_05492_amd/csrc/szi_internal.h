@@ -56,8 +56,7 @@ struct FieldDesc {
     const uint32_t* dtab;  // decode tables (see DecodeTables layout)
     unsigned long long* tot;  // compress: receives the field's words and non-zero words
     uint32_t* esec;        // compress: its words section with the zero words elided
-    uint16_t* sub;         // per chunk kSubParts bit offsets: 0, then where its 2nd .. last eighth starts (or null)
-    uint32_t* choff;       // per chunk its first word (with sub)
+    uint16_t* sub;         // per chunk kSubParts entries: its place, then the bits where its 2nd .. last eighth starts (or null)
 };
 
 // One pass of the interpolation (Sec. V-A: levels from stride S/2 to 1, one
@@ -192,12 +191,22 @@ struct EncSums {
     uint32_t* supnz;    // per 2^shift blocks: non-zero words
     int shift;          // 6, or 8 where the sums would be more than a few hundred
 };
+// A chunk's place, where its first part's bit offset (always 0) would be, so
+// that a result's record costs no more than the offsets: units of kUnitChunks
+// chunks (the decoder's), entry 0 of the unit's first two chunks the low and
+// high half of the unit's first word, of the others the chunk's first word
+// counted from there (the second chunk's follows from the first one's bits).
+// A unit of one chunk has its high half past the field's last entry.
+constexpr int kUnitChunks = 32;
+static_assert(kUnitChunks * ((2048 * kLmax + 31) / 32) < 65536, "a unit's words count in 16 bits");
+inline uint64_t sub_entries(uint64_t chunks) { return kSubParts * chunks + (chunks % kUnitChunks == 1 ? 1 : 0); }
+// d_ccnt: per chunk its words, and its outliers above them (16 bits each)
 hipError_t launch_huff_stats(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
-                             uint64_t nblocks, int chunk, int ec, uint32_t* d_cwords,
-                             uint32_t* d_couts, EncSums sums, int max_nsym, hipStream_t st);
+                             uint64_t nblocks, int chunk, int ec, uint32_t* d_ccnt, EncSums sums,
+                             int max_nsym, hipStream_t st);
 hipError_t launch_huff_encode(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
-                              uint64_t nblocks, int chunk, int ec, const uint32_t* d_cwords,
-                              const uint32_t* d_couts, EncSums sums, int max_nsym, hipStream_t st);
+                              uint64_t nblocks, int chunk, int ec, const uint32_t* d_ccnt, EncSums sums,
+                              int max_nsym, hipStream_t st);
 // Zero-word elision of the words that the encode left: into each field's
 // esec (bitmap words, then the non-zero words; capacity (n_words + 31) / 32 +
 // n_words) where that is shorter.

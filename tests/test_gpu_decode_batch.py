@@ -48,6 +48,27 @@ def test_workgroups_cross_fields(ctx, chunks):
         r.free()
 
 
+@pytest.mark.parametrize("chunk", [256, 2048])
+def test_units_of_chunks(ctx, chunk):
+    # a chunk's place is counted from its unit of 32, whose first word lies in the first two chunks' records: fields
+    # that end at each place of a unit, the largest words a unit has (random codes of a wide range), alone and together
+    import torch
+    counts = [1, 2, 3, 31, 32, 33, 34, 63, 64, 65, 66, 97, 129, 161]
+    xs = [np.random.default_rng(n).integers(-1000, 1000, chunk * n - n % 3).astype(np.float32) for n in counts]
+    kw = dict(chunk=chunk, eb=0.5, eb_mode=0, R=1024)
+    refs = [O.compress(x, O.Params(shape=x.shape, **kw)) for x in xs]
+    gk = dict(chunk=chunk, eb=0.5, eb_mode=0, radius=1024)
+    print("\n[decode] units, chunk %d" % chunk, flush=True)
+    gs = [torch.from_numpy(x).cuda() for x in xs]
+    rs = ctx.compress_batch(gs, [gk] * len(xs))
+    ones = [ctx.compress(g, **gk) for g in gs]
+    for ys in (ctx.decompress_batch(rs), [ctx.decompress(r) for r in ones]):
+        for y, ref in zip(ys, refs):
+            assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
+    for r in rs + ones:
+        r.free()
+
+
 def uploads(ctx, xs, params):
     refs = [O.compress(x, O.Params(shape=x.shape, **p)) for x, p in zip(xs, params)]
     return refs, [ctx.upload(r.blob()) for r in refs]
