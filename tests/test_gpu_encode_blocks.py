@@ -89,6 +89,17 @@ def test_given_code_with_many_outliers_runs_the_encode_again(ctx):
     res.free()
 
 
+@pytest.mark.parametrize("chunk", [256, 512, 1024, 2048])
+@pytest.mark.parametrize("every", [0, 1, 3, 50, 3000])
+def test_outlier_lists(ctx, chunk, every):
+    # a chunk's outliers: all its symbols (every 0: a bound of zero), most, one in 50, one in several chunks; the last
+    # chunk ends inside a lane's symbols
+    x = rough(chunk * 41 + 5)
+    if every > 1:
+        x[np.arange(x.size) % every != 0] = 0.0
+    check(ctx, x, chunk=chunk, eb=0.0 if every == 0 else 1e-6, eb_mode=0)
+
+
 def test_more_blocks_than_short_sums(ctx):
     # 2^27 points in chunks of 256: more than 16384 blocks of 32 chunks
     x = smooth(2 ** 27 + 12345)
