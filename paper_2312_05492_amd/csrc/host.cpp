@@ -1797,7 +1797,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
     for (int gi = 0; gi < kGroups; ++gi) perm.insert(perm.end(), grp[gi].begin(), grp[gi].end());
     uint64_t cb = 0;
     bool split = true;   // every field has sub-chunk offsets: kSubParts decode lanes per chunk
-    uint64_t words = 0, npts = 0, outliers = 0;
+    uint64_t words = 0, npts = 0;
     int min_chunk = INT32_MAX;
     std::vector<uint64_t> dboff(nf + 1, 0);
     for (uint32_t k = 0; k < nf; ++k) {
@@ -1815,7 +1815,6 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         split = split && R->d_sub != nullptr;
         words += res[i].n_words;
         npts += geo[i].npts;
-        outliers += res[i].n_outliers;
         min_chunk = std::min(min_chunk, (int)geo[i].chunk);
         f.outlier_idx = res[i].outlier_idx;
         f.outlier_val = res[i].outlier_val;
@@ -1840,7 +1839,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
         nitems[gi] = grp[gi].empty() ? 0 : io[grp[gi].size()];
     }
     const uint64_t nblocks = dboff[nf];
-    const DecodeKind kind = decode_kind(split, nblocks, words, npts, outliers, min_chunk, c->num_cus);
+    const DecodeKind kind = decode_kind(split, nblocks, words, npts, min_chunk, c->num_cus);
     FieldDesc* d_fd;
     FieldPlan* d_plan;
     uint64_t *d_items, *d_dboff;
@@ -1848,7 +1847,7 @@ sz_status sz_decompress_batch(sz_ctx* c, uint32_t nf, const sz_result* res, floa
     sz_status s;
     // the device work of the call
     auto enqueue = [&](hipStream_t q) -> sz_status {
-        if (kind != kDecSplitScatter) {
+        if (kind != kDecSplit) {
             // block word counts, the outlier scatter and the pass descriptors
             STAGE(c, SZ_STAGE_SCAN, q);
             HIP_TRY(c, launch_dec_prep(d_fd, d_plan, (int)nf, d_dboff, nblocks, d_bsum, q));
@@ -2024,8 +2023,8 @@ sz_status sz_decompress_noalloc(sz_ctx* c, const sz_result* res, float* d_out, v
     uint32_t* d_bsum = reinterpret_cast<uint32_t*>(ws + o_bsum);
     HIP_TRY(c, launch_stage_words(reinterpret_cast<uint32_t*>(ws), sw, st));
     const DecodeKind kind = decode_kind(R->d_sub != nullptr, nblocks, res->n_words, geo.npts,
-                                        res->n_outliers, (int)geo.chunk, c->num_cus);
-    if (kind != kDecSplitScatter)
+                                        (int)geo.chunk, c->num_cus);
+    if (kind != kDecSplit)
         HIP_TRY(c, launch_dec_prep(d_fd, d_plan, 1, d_dboff, nblocks, d_bsum, st));
     HIP_TRY(c, launch_huff_decode(d_fd, 1, d_dboff, nblocks, d_bsum, 2 * geo.R, kind, c->num_cus, st));
     HIP_TRY(c, launch_decompress_group(c, group_of(geo), d_fd, d_plan, d_items, ngroups,

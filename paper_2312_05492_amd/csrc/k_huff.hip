@@ -13,11 +13,11 @@
 // Decode: kDecChunks chunks per decode block, kSubParts lanes per chunk from
 // the bit offsets of its parts that the encoder records (one lane per chunk
 // without them).
-//   k_dec_prep     (k_plan.hip) word count of every decode block of a field
-//                  without the offsets; outliers where they are many
+//   k_dec_prep     (k_plan.hip) ahead of the kernels without the offsets: word
+//                  count of every decode block, outliers, pass descriptors
 //   k_huff_decode8 (offsets at hand) persistent workgroups, eight lanes a
 //                  chunk from its recorded first word and part offsets; it
-//                  scatters the outliers for the replay where they are few
+//                  scatters the outliers for the replay
 //   k_huff_decode1 (none) one lane a chunk; first words from the field's
 //                  earlier block sums and an in-block scan
 //   k_huff_decode_runs (none, few chunks of short codes) the same with up to
@@ -934,7 +934,7 @@ static_assert(kUnits * kUnitChunks == kDecChunks && kUnitChunks == 32, "32 chunk
 
 __global__ __launch_bounds__(kDecChunks) void k_huff_decode8(const FieldDesc* __restrict__ F, int nfields,
                                                              const uint64_t* __restrict__ boff,
-                                                             uint64_t units, bool scatter) {
+                                                             uint64_t units) {
     __shared__ __align__(16) uint32_t rings[kDecChunks * kRing];
     __shared__ __align__(16) uint32_t lut32[kDtLimit];   // 2^kLutBits u16 entries
     extern __shared__ uint32_t tab_hi[];   // decode-table words kDtLimit .. dtab_words(nsym)
@@ -1020,7 +1020,7 @@ __global__ __launch_bounds__(kDecChunks) void k_huff_decode8(const FieldDesc* __
             tf = cu.f;
         }
         dec.start(lw, w);
-        if (scatter) {   // the unit's share of the field's outliers, into the output for the replay
+        {   // the unit's share of the field's outliers, into the output for the replay
             const uint64_t u0 = boff[cu.f] * kUnits, nu = boff[cu.f + 1] * kUnits - u0;
             for (uint64_t k = (u - u0) * kDecChunks + (uint32_t)tid; k < fd.n_outliers; k += nu * kDecChunks) {
                 const uint32_t idx = gp(fd.outlier_idx)[k];
@@ -1267,12 +1267,12 @@ hipError_t launch_huff_decode(const FieldDesc* d_fields, int nfields, const uint
     if (nblocks == 0) return hipSuccess;
     const size_t lds = (size_t)(dtab_words(max_nsym) - kDtLimit) *
                        sizeof(uint32_t);
-    if (kind == kDecSplit || kind == kDecSplitScatter) {
+    if (kind == kDecSplit) {
         // as many workgroups as are resident at once, but no more than units
         uint64_t grid = (uint64_t)num_cus * (uint64_t)resident_per_cu(k_huff_decode8, lds);
         if (grid > kUnits * nblocks) grid = kUnits * nblocks;
         hipLaunchKernelGGL(k_huff_decode8, dim3((unsigned)grid), dim3(kDecChunks), lds, st, d_fields, nfields,
-                           d_dboff, kUnits * nblocks, kind == kDecSplitScatter);
+                           d_dboff, kUnits * nblocks);
     } else if (kind == kDecRuns) {
         hipLaunchKernelGGL(k_huff_decode_runs, dim3((unsigned)(kRunWaves * nblocks)), dim3(kDecChunks), lds, st,
                            d_fields, nfields, d_dboff, d_bsum);

@@ -236,9 +236,8 @@ __device__ void make_pass(const FieldDesc& f, FieldPlan& p, const PlanIn& in, in
 }
 
 
-// Decompression prologue, where the decode kernel does not do without it
-// (decode_kind): one workgroup of kDecBlockChunks threads per
-// Huffman decode block: the block's word count (the decoder's offsets come
+// Decompression prologue of fields without the encoder's offsets (uploaded
+// blobs): one workgroup of kDecBlockChunks threads per Huffman decode block: the block's word count (the decoder's offsets come
 // from these sums), a share of the field's outlier values scattered into
 // the output (where the replay reads them), and, in the field's first
 // block, the pass descriptors of the plan the header carried.

@@ -230,29 +230,34 @@ inline uint64_t elide_tile_words(uint64_t words) {
 // 2048); cnt and off (u32[ntiles], u64[ntiles + 1]) are scratch.
 hipError_t launch_restore(const ElideField* d_e, int nf, const uint64_t* d_toff, uint64_t ntiles,
                           uint64_t tw, uint32_t* d_cnt, uint64_t* d_off, hipStream_t st);
-// d_bsum: the word count of every decode block (launch_dec_prep)
-// the kernel for the decode: eight lanes a chunk where every field has the
-// encoder's offsets, else one
-enum DecodeKind { kDecSplit, kDecSplitScatter, kDecRuns, kDecPlain };
-// Without the offsets: runs of symbols per look-up pay where the chip is not
-// full of chains (a quarter of a decode block then has a CU of its own) and
-// codes are short enough that several fit a look-up; their table costs about
-// 10 us a call, which a chunk of 256 symbols wins back only with the
-// shortest.  Measured, plain against runs, us: 1024 symbols a chunk 91 / 43
-// at 1.05 bits a symbol, 105 / 54 at 2.7, 120 / 88 at 4.8, 126 / 126 at 5.8;
-// 512 50 / 30, 58 / 39, 67 / 57, 70 / 80; 256 30 / 26, 35 / 32, 39 / 45, 40 / 54.
-constexpr int kRunWaves = kDecBlockChunks / 64;
+// The kernel for the decode: eight lanes a chunk where every field has the
+// encoder's offsets (kDecSplit), else one.
 //
-// With them no prologue is needed where outliers are few: a result's plan
-// holds its pass descriptors, and the decode scatters the outliers itself
-// (kDecSplitScatter: a 64^3 field's call 52 -> 50 us, a 512^3 one's 391 -> 387).  Where they are many (1 in 64 points, two rounds
-// of loads a unit) the prologue's eight times as many workgroups do it.
-inline DecodeKind decode_kind(bool split, uint64_t nblocks, uint64_t words, uint64_t npts,
-                              uint64_t outliers, int min_chunk, int num_cus) {
-    if (split) return outliers <= npts / 64 ? kDecSplitScatter : kDecSplit;
+// With the offsets no prologue is launched: a result's plan holds its pass
+// descriptors, and the decode scatters the outliers itself, a unit its share.
+// Decode and prologue (an eighth as many workgroups as there are units)
+// together, us, without / with it, by the share of outliers: 64^3 20 / 27 at
+// 0.4 %, 21 / 33 at 1.7 %, 35 / 98 at 22 %; 256^3 40 / 50, 35 / 54, 55 / 171;
+// 512^3 209 / 226, 220 / 249, 447 / 488; 64 fields of 64^3, one of them all
+// outliers, 39 / 123.
+//
+// Without the offsets runs of symbols per look-up (kDecRuns) pay where the
+// chip is not full of chains (a quarter of a decode block then has a CU of
+// its own) and codes are short enough that several fit a look-up; their table
+// costs about 10 us a call, which a chunk of 256 symbols wins back only with
+// the shortest.  Plain against runs, us: 1024 symbols a chunk 91 / 43 at 1.05
+// bits a symbol, 105 / 54 at 2.7, 120 / 88 at 4.8, 126 / 126 at 5.8; 512
+// 50 / 30, 58 / 39, 67 / 57, 70 / 80; 256 30 / 26, 35 / 32, 39 / 45, 40 / 54.
+enum DecodeKind { kDecSplit, kDecRuns, kDecPlain };
+constexpr int kRunWaves = kDecBlockChunks / 64;
+inline DecodeKind decode_kind(bool split, uint64_t nblocks, uint64_t words, uint64_t npts, int min_chunk,
+                              int num_cus) {
+    if (split) return kDecSplit;
     const uint64_t bits = min_chunk >= 512 ? 5 : 3;
     return kRunWaves * nblocks <= (uint64_t)num_cus && 32 * words <= bits * npts ? kDecRuns : kDecPlain;
 }
+// d_bsum: the word count of every decode block (launch_dec_prep), not read
+// for kDecSplit
 hipError_t launch_huff_decode(const FieldDesc* d_fields, int nfields, const uint64_t* d_dboff,
                               uint64_t nblocks, const uint32_t* d_bsum, int max_nsym, DecodeKind kind,
                               int num_cus, hipStream_t st);

@@ -125,3 +125,21 @@ def test_outliers_scattered(ctx, every, shape):
     for y in [ctx.decompress(r)] + list(ctx.decompress_batch([r] * 3)):
         assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
     r.free()
+
+
+@pytest.mark.parametrize("at", [0, 3, 7])
+def test_outliers_of_one_field(ctx, at):
+    # a batch in which one field is nothing but outliers and the others have none: each unit scatters its own field's
+    import torch
+    xs = [np.zeros((20, 30, 40 + i), np.float32) for i in range(8)]
+    xs[at] = np.random.default_rng(at).normal(size=(40, 50, 61)).astype(np.float32)
+    kw = dict(eb=1e-30, eb_mode=0, chunk=256)
+    refs = [O.compress(x, O.Params(shape=x.shape, **kw)) for x in xs]
+    assert [len(r.outlier_idx) > 0 for r in refs] == [i == at for i in range(8)]
+    print("\n[decode] outliers of field %d" % at, flush=True)
+    rs = ctx.compress_batch([torch.from_numpy(x).cuda() for x in xs], [kw] * 8)
+    outs = [torch.full(x.shape, float("nan"), device="cuda") for x in xs]
+    for y, ref in zip(ctx.decompress_batch(rs, outs), refs):
+        assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
+    for r in rs:
+        r.free()
