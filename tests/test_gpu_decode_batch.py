@@ -69,6 +69,20 @@ def test_units_of_chunks(ctx, chunk):
         r.free()
 
 
+@pytest.mark.parametrize("chunks", [32 * 255, 32 * 768 - 1, 32 * 768 + 1, 32 * 1537])
+def test_one_field_in_turn(ctx, chunks):
+    # one field's units taken in turn by a grid of fewer, as many and more workgroups than units
+    import torch
+    x = np.random.default_rng(chunks).normal(size=chunks * 256 - 100).astype(np.float32)
+    x[::7] = 0.0
+    kw = dict(chunk=256, eb=1e-3)
+    ref = O.compress(x, O.Params(shape=x.shape, **kw))
+    print("\n[decode] one field, %d chunks" % chunks, flush=True)
+    r = ctx.compress(torch.from_numpy(x).cuda(), **kw)
+    assert np.array_equal(ctx.decompress(r).cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
+    r.free()
+
+
 def uploads(ctx, xs, params):
     refs = [O.compress(x, O.Params(shape=x.shape, **p)) for x, p in zip(xs, params)]
     return refs, [ctx.upload(r.blob()) for r in refs]
