@@ -33,17 +33,51 @@ constexpr int kDecChunks = 256;
 static_assert(kDecChunks == kDecBlockChunks,
               "the host sizes the decode grid with the same chunk count");
 
+// The long sums of a field into what lies before each and, behind the last,
+// their total: a workgroup a field.
+template <int COLS>
+__global__ __launch_bounds__(256) void k_scan_long(const uint64_t* __restrict__ boff, uint32_t* sup, int shift) {
+    __shared__ uint32_t tot[4][COLS];
+    const uint64_t b0 = boff[blockIdx.x];
+    const uint32_t n = (uint32_t)((boff[blockIdx.x + 1] - b0) >> shift);
+    SZI_G uint32_t* s = gp(sup) + ((b0 >> shift) + blockIdx.x) * kSuperLine;
+    uint32_t before[COLS] = {};
+    for (uint32_t i0 = 0; i0 <= n; i0 += 256) {
+        const uint32_t i = i0 + threadIdx.x;
+        uint32_t x[COLS], t[COLS];
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) x[c] = wave_excl_scan(i < n ? s[(uint64_t)i * kSuperLine + c] : 0u, &t[c]);
+        __syncthreads();
+        if ((threadIdx.x & 63) == 0)
+#pragma unroll
+            for (int c = 0; c < COLS; ++c) tot[threadIdx.x >> 6][c] = t[c];
+        __syncthreads();
+#pragma unroll
+        for (int c = 0; c < COLS; ++c) {
+            uint32_t y = before[c] + x[c];
+            for (uint32_t k = 0; k < 4; ++k) {
+                if (k < threadIdx.x >> 6) y += tot[k][c];
+                before[c] += tot[k][c];
+            }
+            if (i <= n) s[(uint64_t)i * kSuperLine + c] = y;
+        }
+    }
+}
+
 // Sum over the blocks [first, blk) of field f of one number a block or two
 // (b, the second of a line of sup), by the 256 threads of a workgroup; red:
 // 8 words of LDS, with a barrier inside.
 __device__ __forceinline__ void sum_before(const uint32_t* __restrict__ a, const uint32_t* __restrict__ b,
-                                           const uint32_t* __restrict__ sup, int shift, int f,
+                                           const uint32_t* __restrict__ sup, const EncSums& sums, int f,
                                            uint64_t first, uint64_t blk, uint32_t* red, uint32_t& ra,
                                            uint32_t& rb) {
+    const int shift = sums.shift;
     const uint32_t nsup = (uint32_t)((blk - first) >> shift);
     const uint64_t sb0 = (first >> shift) + (uint32_t)f;
     uint32_t xa = 0, xb = 0;
-    for (uint32_t i = threadIdx.x; i < nsup; i += 256) {
+    // scanned: the first thread reads the one behind them
+    const uint32_t end = sums.scanned() ? nsup + 1u : nsup;
+    for (uint32_t i = (sums.scanned() ? nsup : 0u) + threadIdx.x; i < end; i += 256) {
         xa += gp(sup)[(sb0 + i) * kSuperLine];
         if (b) xb += gp(sup)[(sb0 + i) * kSuperLine + 1];
     }
@@ -315,7 +349,7 @@ __global__ __launch_bounds__(256) void k_huff_encode(const FieldDesc* __restrict
     // words and outliers of the field's earlier blocks; the barrier inside
     // also completes the code book in LDS
     uint32_t bw0, bo0;
-    sum_before(sums.words, sums.outs, sums.sup, sums.shift, f, boff[f], blockIdx.x, red, bw0, bo0);
+    sum_before(sums.words, sums.outs, sums.sup, sums, f, boff[f], blockIdx.x, red, bw0, bo0);
     if (threadIdx.x == 0) sums.woff[blockIdx.x] = bw0;
     uint32_t nz = 0;   // non-zero words written, for the zero-word elision of the blob
     for (int j = wave; j < ec; j += 4) {
@@ -1099,7 +1133,7 @@ __global__ __launch_bounds__(256) void k_elide(const FieldDesc* __restrict__ F, 
     const FieldDesc& fd = F[f];
     const uint64_t bf = boff[f], be = boff[f + 1];
     uint32_t nz, before, none;
-    sum_before(sums.nz, nullptr, sums.supnz, sums.shift, f, bf, be, red, nz, none);
+    sum_before(sums.nz, nullptr, sums.supnz, sums, f, bf, be, red, nz, none);
     const uint64_t nw = (uint64_t)sums.woff[be - 1] + sums.words[be - 1], nbm = (nw + 31) / 32;
     if (blockIdx.x == be - 1 && threadIdx.x == 0) {
         fd.tot[0] = nw;
@@ -1107,7 +1141,7 @@ __global__ __launch_bounds__(256) void k_elide(const FieldDesc* __restrict__ F, 
     }
     if (nbm + nz >= nw) return;   // uniform: the field keeps its words
     __syncthreads();
-    sum_before(sums.nz, nullptr, sums.supnz, sums.shift, f, bf, blockIdx.x, red, before, none);
+    sum_before(sums.nz, nullptr, sums.supnz, sums, f, bf, blockIdx.x, red, before, none);
     const uint64_t w0 = sums.woff[blockIdx.x], w1 = w0 + sums.words[blockIdx.x];
     const uint64_t base = w0 & ~(uint64_t)63;
     const uint32_t rounds = (uint32_t)((w1 - base + 63) / 64), each = (rounds + 3) / 4;
@@ -1220,6 +1254,8 @@ __global__ __launch_bounds__(256) void k_restore_write(const ElideField* __restr
 hipError_t launch_elide(const FieldDesc* d_fields, int nfields, const uint64_t* d_boff,
                         uint64_t nblocks, EncSums sums, hipStream_t st) {
     if (nblocks == 0) return hipSuccess;
+    if (sums.scanned())
+        hipLaunchKernelGGL(k_scan_long<1>, dim3((unsigned)nfields), dim3(256), 0, st, d_boff, sums.supnz, sums.shift);
     hipLaunchKernelGGL(k_elide, dim3((unsigned)nblocks), dim3(256), 0, st, d_fields, nfields, d_boff, sums);
     return hipGetLastError();
 }
@@ -1263,6 +1299,8 @@ hipError_t launch_huff_encode(const FieldDesc* d_fields, int nfields, const uint
     const int mcw = enc_chunk_words(chunk);
     const size_t lds = ((size_t)max_nsym + 4 * (size_t)mcw) * sizeof(uint32_t);
     const dim3 g((unsigned)nblocks), b(256);
+    if (sums.scanned())
+        hipLaunchKernelGGL(k_scan_long<2>, dim3((unsigned)nfields), dim3(256), 0, st, d_boff, sums.sup, sums.shift);
     switch (chunk) {
     case 256: hipLaunchKernelGGL(k_huff_encode<4>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;
     case 512: hipLaunchKernelGGL(k_huff_encode<8>, g, b, lds, st, d_fields, nfields, d_boff, ec, d_ccnt, sums); break;

@@ -173,13 +173,20 @@ inline int enc_block_chunks(uint64_t chunks) {
 }
 // Sums over the encode blocks of a group: per block, and over every 2^shift
 // of a field's blocks (its last ones, fewer than that, are not summed), so
-// that a block finds what lies before it from a few hundred numbers even in
-// the largest field, without a scan between the kernels.  The long sums are
-// added to by atomics and start at zero (launch_plan clears them), each in a
-// 128-byte line of its own: atomics on one line take 25 ns each, one after
-// another (one counter per field had bounded the encode of 512^3, 4096
-// blocks, at 91 us; sums over 256 blocks cost 6 us at 100x500x500).  Those
-// of field f of the group start at (boff[f] >> shift) + f.
+// that a block finds what lies before it from at most 256 long sums and 63
+// short ones, without a scan between the kernels.  The long sums are added to
+// by atomics and start at zero (launch_plan clears them), each in a 128-byte
+// line of its own: atomics on one line take 25 ns each, one after another
+// (one counter per field had bounded the encode of 512^3, 4096 blocks, at
+// 91 us; sums over 256 blocks cost 6 us at 100x500x500).  Those of field f of
+// the group start at (boff[f] >> shift) + f, with a place to spare behind
+// them.  Calls of more than 16384 blocks take sums over 256 blocks and scan
+// them in place, a launch ahead of the kernels that read them, so that a block
+// reads one of them and at most 255 short ones: added up by every block they
+// cost the square of the size (1625^3 in chunks of 256, 2048 long sums:
+// elision 3862 us, now 231, encode 6113, now 4315; in chunks of 1024 elision
+// 215, now 68).  A launch takes 5 us (820^3, just above the line, elision 12
+// us with 66 long sums added, now 17 of a call of 2200).
 inline int enc_super_shift(uint64_t blocks) { return blocks <= 16384 ? 6 : 8; }
 constexpr int kSuperLine = 32;   // words
 struct EncSums {
@@ -189,7 +196,8 @@ struct EncSums {
     uint32_t* woff;     // per block: words of the field's earlier blocks
     uint32_t* sup;      // per 2^shift blocks: words, outliers
     uint32_t* supnz;    // per 2^shift blocks: non-zero words
-    int shift;          // 6, or 8 where the sums would be more than a few hundred
+    int shift;          // 6, or 8 with the long sums scanned
+    __host__ __device__ bool scanned() const { return shift == 8; }
 };
 // A chunk's place, where its first part's bit offset (always 0) would be, so
 // that a result's record costs no more than the offsets: units of kUnitChunks

@@ -105,3 +105,30 @@ def test_more_blocks_than_short_sums(ctx):
     x = smooth(2 ** 27 + 12345)
     blob = check(ctx, x, chunk=256, eb=1e-4)
     assert blob[124] & 1   # elided
+
+
+@pytest.mark.parametrize("given", [False, True])
+def test_long_sums_of_a_batch(ctx, given):
+    # more than 16384 blocks over fields of 0 to about 9500, whose long sums (over 256 blocks, scanned) lie side by
+    # side: a field of none, of one less a block, of exactly one and of many, elided and not
+    import torch
+    block = 32 * 256
+    sizes = [(100, rough), (255 * block, smooth), (256 * block, smooth), (256 * block + 1, rough), (5, smooth),
+             (9500 * block - 3, smooth), (6500 * block, rough)]
+    xs = [g(n) for n, g in sizes]
+    p = dict(chunk=256, eb=1e-3)
+    refs = [O.compress(x, O.Params(shape=x.shape, **p)) for x in xs]
+    gs = [torch.from_numpy(x).cuda() for x in xs]
+    print("\n[encode] batch of long sums, given %s" % given, flush=True)
+    if given:
+        books = [szi.code_lengths(r.hist) for r in refs]
+        refs = [O.compress(x, O.Params(shape=x.shape, **p), lengths=b) for x, b in zip(xs, books)]
+        outs = ctx.compress_batch_with_code(gs, books, [p] * len(xs))
+    else:
+        outs = ctx.compress_batch(gs, [p] * len(xs))
+    for r, ref in zip(outs, refs):
+        assert r.blob() == ref.blob()
+    for y, ref in zip(ctx.decompress_batch(outs), refs):
+        assert np.array_equal(y.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
+    for r in outs:
+        r.free()
