@@ -1246,7 +1246,7 @@ sz_status compress_fields(sz_ctx* c, uint32_t nf, const float* const* d_in, cons
     for (uint32_t k = 0; k < nf; ++k) hord[k] = k;
     std::stable_sort(hord.begin(), hord.end(),
                      [&](uint32_t x, uint32_t y) { return fds[x].chunk < fds[y].chunk; });
-    const int ec = enc_block_chunks(total_chunks);
+    const int ec = enc_block_chunks(total_chunks, c->num_cus);
     std::vector<uint64_t> hboff(nf + 1, 0);   // global block prefix in hord order
     for (uint32_t j = 0; j < nf; ++j)
         hboff[j + 1] = hboff[j] + (fds[hord[j]].nchunks + (uint64_t)ec - 1) / (uint64_t)ec;

@@ -166,9 +166,9 @@ hipError_t launch_decompress(int ndim, const FieldDesc* d_fields, const FieldPla
 // leaves eight workgroups a CU, fewer on smaller calls, where a workgroup's
 // chunks follow each other with nothing beside them (64^3, 256 chunks: stats
 // 10 -> 7 us and encode 18 -> 8 us with 4 instead of 32).
-inline int enc_block_chunks(uint64_t chunks) {
+inline int enc_block_chunks(uint64_t chunks, int num_cus) {
     int ec = kEncBlockMax;
-    while (ec > 4 && chunks < 2048ull * (uint64_t)ec) ec /= 2;
+    while (ec > 4 && chunks < 8ull * (uint64_t)num_cus * (uint64_t)ec) ec /= 2;
     return ec;
 }
 // Sums over the encode blocks of a group: per block, and over every 2^shift
