@@ -100,3 +100,51 @@ def test_other_window_orders_and_rare_branches(ctx):
     rng = np.random.default_rng(108)
     check(ctx, np.where(rng.random(x.shape) < 0.01, x + np.float32(1e3), x).astype(np.float32), S=4, eb=1e-3, eb_mode=0)
     check(ctx, x + np.float32(1000.0), S=4, eb=2.0 ** -12, eb_mode=0, interp=(2, 2, 2))
+
+
+def off_alignment(x, shift):
+    """x on the GPU, shift floats past a 16-byte boundary, and its buffer with guard values around it."""
+    import torch
+    buf = torch.full((x.size + 8,), -7.0, dtype=torch.float32, device="cuda")
+    view = buf[4 + shift:4 + shift + x.size].view(x.shape)
+    view.copy_(torch.from_numpy(np.ascontiguousarray(x)))
+    return view, buf
+
+
+@pytest.mark.parametrize("shift", [1, 2, 3])
+@pytest.mark.parametrize("shape,stride,window", [((33, 34, 25), 8, (16, 16, 8)), ((34, 130), 16, (32, 96)),
+                                                 ((5000,), 256, (768,))])
+def test_other_windows_off_alignment(ctx, shape, stride, window, shift):
+    x = synth.spectral_field(shape, seed=109)
+    kw = dict(S=stride, window=window, eb=1e-3)
+    ref = O.compress(x, O.Params(shape=shape, **kw))
+    print("\n[passes] %s off by %d" % (shape, shift), flush=True)
+    res = ctx.compress(off_alignment(x, shift)[0], **kw)
+    assert res.blob() == ref.blob()
+    out, buf = off_alignment(np.zeros_like(x), shift)
+    ctx.decompress(res, out)
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32))
+    y = buf.cpu().numpy()
+    assert (y[:4 + shift] == -7.0).all() and (y[4 + shift + x.size:] == -7.0).all()   # nothing outside
+    res.free()
+
+
+def test_lines_of_a_batch_on_and_off_alignment(ctx):
+    # a workgroup's windows come from fields on and one to three floats off 16 bytes by turns: loaded ahead or not
+    xs = [synth.spectral_field((n,), seed=110 + i) for i, n in
+          enumerate([9000, 4096, 70001, 2047, 2048, 2049, 30000, 8192, 6143, 12288, 5, 20480])]
+    kws = [dict(eb=1e-3)] * len(xs)
+    refs = [O.compress(x, O.Params(shape=x.shape, **kw)) for x, kw in zip(xs, kws)]
+    print("\n[passes] lines on and off alignment", flush=True)
+    for turn in range(2):
+        res = ctx.compress_batch([off_alignment(x, (i + turn) % 4)[0] for i, x in enumerate(xs)], kws)
+        for r, ref in zip(res, refs):
+            assert r.blob() == ref.blob()
+        outs = [off_alignment(np.zeros_like(x), (3 * i + turn) % 4) for i, x in enumerate(xs)]
+        ctx.decompress_batch(res, [o for o, _ in outs])
+        for i, ((o, buf), ref) in enumerate(zip(outs, refs)):
+            assert np.array_equal(o.cpu().numpy().view(np.uint32), ref.recon.view(np.uint32)), i
+            s, y = 4 + (3 * i + turn) % 4, buf.cpu().numpy()
+            assert (y[:s] == -7.0).all() and (y[s + xs[i].size:] == -7.0).all()
+        for r in res:
+            r.free()
