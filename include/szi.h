@@ -26,9 +26,10 @@
  *    sz_result_free.
  *  - A context may be used by one host thread at a time.  Independent
  *    contexts on the same device may run concurrently on different streams.
- *  - Limits: ndim in {2, 3}; 1 <= total points < 2^32; radius R in
- *    [2, 1024]; Huffman chunk in {256, 512, 1024, 2048}; anchor stride and
- *    window fixed to the defaults below.
+ *  - Limits: ndim in {1, 2, 3}; 1 <= total points < 2^32 - 1; radius R in
+ *    [2, 1024]; Huffman chunk in {256, 512, 1024, 2048}; anchor strides that
+ *    are powers of two, windows that are multiples of them (other than the
+ *    defaults: blocks of at most 4096 points, 1024 along a dimension).
  */
 #ifndef SZI_H
 #define SZI_H
@@ -66,7 +67,7 @@ typedef enum {
 } sz_interp;
 
 typedef struct {
-    uint32_t ndim;      /* 2 or 3 */
+    uint32_t ndim;      /* 1, 2 or 3 */
     uint32_t reserved;  /* 0 */
     uint64_t n[3];      /* n[0] fastest; entries >= ndim ignored */
 } sz_dims;
@@ -83,9 +84,10 @@ typedef struct {
                                <= 0 = Eq. 1; 1 = the same bound everywhere */
     uint32_t radius;        /* R: codes q+R in 1..2R-1, 0 = outlier; 0 = 512 */
     uint32_t huff_chunk;    /* symbols per Huffman chunk; 0 = 1024 */
-    uint32_t anchor_stride; /* 0 = default: 8 in 3D, 16 in 2D (Sec. V-A) */
+    uint32_t anchor_stride; /* 0 = default: 8 in 3D, 16 in 2D, 512 in 1D (Sec. V-A) */
     uint32_t window[3];     /* 0 = default: (32, 8, 8) in 3D, (64, 16) in 2D,
-                               i.e. four basic blocks along x (Sec. V-D) */
+                               2048 in 1D, i.e. four basic blocks along x
+                               (Sec. V-D) */
 } sz_params;
 
 /* A compressed field.  Device pointers are owned by the context until
@@ -186,8 +188,10 @@ sz_status sz_ctx_read_timing(sz_ctx* ctx, double* ms, uint64_t* launches, int re
 
 /* Compress the device field d_in (n[0]*n[1]*n[2] floats, 4-byte aligned as
  * any float array is; INVALID_ARG otherwise, no 16-byte alignment needed:
- * the kernels move 16 bytes at a time from any float's address).  Runs the
- * whole pipeline on `stream`: range and profiling (Sec. V-C.1), auto-tuning
+ * the default 3D and 2D windows move 16 bytes at a time from any float's
+ * address; 1D fields that start on 16 bytes are faster, and the other
+ * windows move a value at a time wherever they start).  Runs the whole
+ * pipeline on `stream`: range and profiling (Sec. V-C.1), auto-tuning
  * (Sec. V-C.2, Eq. 1), level bounds (Sec. V-B.2), the interpolation
  * predictor-quantiser with a fused histogram (Sec. V-A/B/D, VI-A), the host
  * codebook (Sec. VI-A), Huffman encoding and outlier compaction.  Returns

@@ -4,7 +4,8 @@
 // Encode: up to 32 consecutive chunks of one field per workgroup (4 wave64,
 // one chunk per wave at a time, C/64 consecutive symbols per lane).
 //   k_huff_stats   bit count and outlier count of every chunk; sums per
-//                  workgroup block and per 64 or 256 blocks
+//                  workgroup block and per 64 blocks (large calls: per 256,
+//                  scanned by k_scan_long)
 //   k_huff_encode  chunk offsets = sums of the field's earlier blocks +
 //                  in-block prefix; packs the codewords MSB-first through
 //                  LDS and writes the outliers (index, original value) in
@@ -210,12 +211,12 @@ __global__ __launch_bounds__(256) void k_huff_stats(const FieldDesc* __restrict_
     }
 }
 
-// Exclusive scan of a u32 array of length n into u64 offsets; one
-// workgroup of 1024 threads, a contiguous run per thread: run sums, wave
-// scans, the 16 wave totals through LDS (one barrier), then the run's
-// offsets.  off[n] receives the total.  LONG = false takes runs of at
-// most kRun (n <= 16384) in registers; LONG = true, longer runs kRun
-// elements a round (the launchers choose by n).
+// Exclusive scan of a u32 array of length n into u64 offsets (the upload's
+// tile counts); one workgroup of 1024 threads, a contiguous run per thread:
+// run sums, wave scans, the 16 wave totals through LDS (one barrier), then
+// the run's offsets.  off[n] receives the total.  LONG = false takes runs of
+// at most kRun (n <= 16384) in registers; LONG = true, longer runs kRun
+// elements a round (the launcher chooses by n).
 template <bool LONG>
 __global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict__ a, uint64_t n,
                                                       uint64_t* aoff) {
@@ -235,47 +236,33 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict
             va[k] = i < end ? a[i] : 0u;
         }
 #pragma unroll
-        for (int k = 0; k < kRun; ++k) {
-            sa += va[k];
-        }
+        for (int k = 0; k < kRun; ++k) sa += va[k];
     } else if (LONG) {
-        // longer runs (the LONG instance): kRun elements a round, their
-        // loads issued together
         for (uint64_t i0 = beg; i0 < end; i0 += kRun) {
 #pragma unroll
             for (int k = 0; k < kRun; ++k) {
                 const uint64_t i = i0 + k;
                 va[k] = i < end ? a[i] : 0u;
-                }
+            }
 #pragma unroll
-            for (int k = 0; k < kRun; ++k) {
-                sa += va[k];
-                }
+            for (int k = 0; k < kRun; ++k) sa += va[k];
         }
     }
-    uint64_t xa = sa;   // inclusive scans over the wave's lanes
+    uint64_t xa = sa;   // inclusive scan over the wave's lanes
     for (int o = 1; o < 64; o <<= 1) {
         const uint64_t ya = __shfl_up(xa, o);
-        if (lane >= o) {
-            xa += ya;
-        }
+        if (lane >= o) xa += ya;
     }
     __shared__ uint64_t wa[16];
-    if (lane == 63) {
-        wa[wave] = xa;
-    }
+    if (lane == 63) wa[wave] = xa;
     __syncthreads();
-    for (int k = 0; k < wave; ++k) {
-        xa += wa[k];
-    }
+    for (int k = 0; k < wave; ++k) xa += wa[k];
     uint64_t ra = xa - sa;
     if (regs) {
 #pragma unroll
         for (int k = 0; k < kRun; ++k) {
             const uint64_t i = beg + k;
-            if (i < end) {
-                aoff[i] = ra;
-            }
+            if (i < end) aoff[i] = ra;
             ra += va[k];
         }
     } else if (LONG) {
@@ -284,20 +271,16 @@ __global__ __launch_bounds__(1024) void k_scan_blocks(const uint32_t* __restrict
             for (int k = 0; k < kRun; ++k) {
                 const uint64_t i = i0 + k;
                 va[k] = i < end ? a[i] : 0u;
-                }
+            }
 #pragma unroll
             for (int k = 0; k < kRun; ++k) {
                 const uint64_t i = i0 + k;
-                if (i < end) {
-                    aoff[i] = ra;
-                    }
+                if (i < end) aoff[i] = ra;
                 ra += va[k];
-                }
+            }
         }
     }
-    if (t == 1023) {
-        aoff[n] = xa;
-    }
+    if (t == 1023) aoff[n] = xa;
 }
 
 // Orders the LDS accesses of one wave around this point (a wave's LDS
@@ -1111,8 +1094,6 @@ __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
 }
 
-// restore = 0: non-zero words per tile of the words; 1: set bits per tile
-// of the bitmap (the tile's 64 bitmap words)
 // ------------------------------------------------------- zero-word elision
 // The de-redundancy step after Huffman coding (taking the place of the
 // closed pass of Sec. VI-B): the words section becomes a bitmap of the
