@@ -719,15 +719,17 @@ struct LaneDec {
         // bits [o, o + 32) of w0:w1 (the shift amount is 32 - o, taken mod 32)
         const uint32_t x = __builtin_amdgcn_alignbit(w0, w1, left >> 27);
         const uint32_t e = lut[x >> (32 - kLutBits)];
-        uint32_t len = (e << 16) & kLenMask, sym = e & ((1u << kLutSymBits) - 1u);
+        // (one shift to the top for either kind of code: shifted each by
+        // itself, an upload of long codes in chunks of 2048 took 418 us for 408)
+        uint32_t len = e >> kLutSymBits, sym = e & ((1u << kLutSymBits) - 1u);
         if (wave_any(len == 0)) {
             uint32_t ln, sl;
             long_code(x, ln, sl);
             const bool lng = len == 0;
             sym = lng ? sl : sym;
-            len = lng ? ln << 27 : len;
+            len = lng ? ln : len;
         }
-        move(len);
+        move(len << 27);
         return sym;
     }
     // len: a code's length in the top five bits.  Past the end of w0 the
